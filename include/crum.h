@@ -430,8 +430,10 @@ void crum_server_destroy(crum_server* server);
  * CRUM_PARAM_PIECE_SHIFT: log2 of the largest piece of a page one wave packs,
  *   verifies or scatters, 12..16 (14); larger pages are split into pieces
  *   whose CRCs are combined afterwards.
- * CRUM_PARAM_PACK_DEPTH: 16-byte loads each lane keeps in flight in the pack
- *   and verify kernels, 4, 8 or 16 (4).
+ * CRUM_PARAM_PACK_DEPTH: 4, 8 or 16 (4).  CRUM_PARAM_CRC_VARIANT: 0..6 (6).
+ *   CRUM_PARAM_PACK_PREFETCH: 0 or 1 (0).  Shapes of the table-driven CRC that
+ *   the pack and verify kernels had before the CRC moved to the matrix cores:
+ *   checked and kept, without effect.
  * CRUM_PARAM_DIFF_PRIORITY: issue priority of the diff kernel's waves on
  *   their compute units relative to co-running kernels, 0..3 (0).
  * CRUM_PARAM_PLAN_ORDER: processing order of a plan's requests, 0 = the
@@ -440,18 +442,10 @@ void crum_server_destroy(crum_server* server);
  *   most this many bytes are built straight in the pinned host image (see
  *   crum_snapshot), an opt-in alternative to the staged drain; 0 turns the
  *   direct order off (0: every image is drained by hipMemcpyAsync).
- * CRUM_PARAM_CRC_VARIANT: how the pack and verify kernels' CRC step splits
- *   its table lookups between 256-entry byte tables (bank conflicts) and
- *   16-entry nibble tables (conflict-free, more ALU work): 0 = byte tables
- *   only, 1..5 = mixes, 6 = byte tables for pack and mix 3 for verify, the
- *   fastest of each on MI355X (6).
  * CRUM_PARAM_CHUNK_GROWTH: factor, 2..16, by which successive pipelined
  *   chunks and plan groups grow, up to their maximum (4).
  * CRUM_PARAM_PACK_NT_STORE: 1 writes the image with non-temporal stores in
  *   the pack kernel (0).
- * CRUM_PARAM_PACK_PREFETCH: 1 makes each lane of the pack and verify kernels
- *   issue its next loads before folding the current ones into its CRC (0);
- *   it applies with cached loads only (CRUM_PARAM_PACK_NT_LOAD 0).
  * CRUM_PARAM_PACK_NT_LOAD: 1 reads the pages in the pack and verify kernels
  *   with non-temporal loads, which are not kept in the caches (1).
  * CRUM_PARAM_DIFF_GROUP: 4 KiB diff units per wave of the diff kernel, 1, 2

@@ -291,10 +291,8 @@ int crum_ctx_create(int device, const char* tuning_cache, crum_ctx** out)
         c->cus = cus;
     c->shape.diff_blocks = c->cus * 8;
     c->shape.pack_blocks = c->cus * 4;
-    CrcTables host;
-    build_crc_tables(&host);
     bool ok = hipMalloc(reinterpret_cast<void**>(&c->d_tabs), sizeof(CrcTables)) == hipSuccess &&
-              hipMemcpy(c->d_tabs, &host, sizeof(CrcTables), hipMemcpyHostToDevice) ==
+              hipMemcpy(c->d_tabs, &crc_tables(), sizeof(CrcTables), hipMemcpyHostToDevice) ==
                   hipSuccess &&
               hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) == hipSuccess &&
               hipEventCreateWithFlags(&c->ev_upload, hipEventDisableTiming) == hipSuccess &&
@@ -426,7 +424,7 @@ int set_param_raw(crum_ctx* c, int param, uint64_t v)
         return CRUM_OK;
     }
     if (param == CRUM_PARAM_CRC_VARIANT) {
-        if (v > (uint64_t)kCrcVariantAuto)
+        if (v > 6)
             return CRUM_EINVAL;
         c->crc_variant = (int)v;
         return CRUM_OK;
@@ -746,8 +744,7 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
             SlotRange sr{0, 0, d_bounds, 0, G};
             CRUM_TRY(launch_pack(kModePack, d_regs, n_regions, d_reqs, d_out, d_list, sr,
                                  np_shift, pc_shift, d_flags, himg, d_crcs, d_partials,
-                                 c->d_tabs, d_glob, c->shape.pack_blocks, c->pack_depth,
-                                 c->crc_variant, stream, ctx_pack_flags(c)));
+                                 c->d_tabs, d_glob, c->shape.pack_blocks, stream, ctx_pack_flags(c)));
             sp.end();  // k_finalize is not part of the pack's timing
             CRUM_TRY(launch_finalize(kModePack, d_regs, n_regions, d_reqs, d_out, d_list, sr,
                                      np_shift, pc_shift, d_partials, d_crcs, himg, d_glob,
@@ -793,8 +790,7 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
                 SlotRange sr{0, 0, d_bounds, (uint32_t)ci, g1 - g0};
                 CRUM_TRY(launch_pack(kModePack, d_regs, n_regions, d_reqs, d_out, d_list, sr,
                                      np_shift, pc_shift, d_flags, staging, d_crcs,
-                                     d_partials, c->d_tabs, d_glob, c->shape.pack_blocks,
-                                     c->pack_depth, c->crc_variant, stream, ctx_pack_flags(c)));
+                                     d_partials, c->d_tabs, d_glob, c->shape.pack_blocks, stream, ctx_pack_flags(c)));
                 sp.end();  // k_finalize is not part of the pack's timing
                 CRUM_TRY(launch_finalize(kModePack, d_regs, n_regions, d_reqs, d_out, d_list, sr,
                                          np_shift, pc_shift, d_partials, d_crcs, staging, d_glob,
@@ -876,8 +872,7 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
                 SlotRange sr{k0, k1, nullptr, 0, k1 - k0};
                 CRUM_TRY(launch_pack(kModePack, d_regs, n_regions, d_reqs, d_out, d_list, sr,
                                      np_shift, pc_shift, d_flags, staging, d_crcs,
-                                     d_partials, c->d_tabs, d_glob, c->shape.pack_blocks,
-                                     c->pack_depth, c->crc_variant, stream, ctx_pack_flags(c)));
+                                     d_partials, c->d_tabs, d_glob, c->shape.pack_blocks, stream, ctx_pack_flags(c)));
                 sp.end();  // k_finalize is not part of the pack's timing
                 CRUM_TRY(launch_finalize(kModePack, d_regs, n_regions, d_reqs, d_out, d_list, sr,
                                          np_shift, pc_shift, d_partials, d_crcs, staging, d_glob,
@@ -1065,8 +1060,7 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
         SlotRange sr{0, D, nullptr, 0, D};
         CRUM_TRY(launch_pack(kModeVerify, d_regs, n_regions, d_reqs, d_out, d_list, sr, np_shift,
                              pc_shift, nullptr, staging, d_crcs, d_partials, c->d_tabs,
-                             d_glob, c->shape.pack_blocks, c->pack_depth, c->crc_variant,
-                             stream, ctx_pack_flags(c)));
+                             d_glob, c->shape.pack_blocks, stream, ctx_pack_flags(c)));
         sp.end();  // k_finalize is not part of the verify's timing
         CRUM_TRY(launch_finalize(kModeVerify, d_regs, n_regions, d_reqs, d_out, d_list, sr,
                                  np_shift, pc_shift, d_partials, d_crcs, staging, d_glob,

@@ -17,9 +17,9 @@ constexpr uint32_t kPieceShiftMin = 12;
 // 4.15-4.43 TB/s pipelined and 5.27-5.32 TB/s in one launch with 16 KiB
 // pieces, against 3.87-3.92 and 5.13-5.26 TB/s with 64 KiB ones.
 constexpr uint32_t kPieceShiftDefault = 14;
-// CRC step variants 0..5 (see launch_pack); kCrcVariantAuto picks the one
-// measured fastest per kernel: byte tables for pack, variant 3 for verify.
-constexpr int kCrcVariantAuto = 6;
+// Flags of launch_pack.
+constexpr int kPackNtStore = 1;  // the image is written with non-temporal stores
+constexpr int kPackNtLoad = 2;   // pages are read with non-temporal loads
 constexpr uint32_t kNoBad = 0xFFFFFFFFu;
 
 // One region of the flattened page space (host-built, uploaded per call).
@@ -90,15 +90,15 @@ static_assert(sizeof(DevGlobal) == 64, "DevGlobal layout");
 // with L_j = 32, 64, 128, 256, 512, 1024 for j = 0..5.
 // t[k][b] = b * x^(8(k+1)) (slicing by 16); z[j][i][b] = (b << 8i) * x^(8 L_j)
 // for L = 32, 64, 128, 256, 512, 1024, 4096 bytes; xp[i] = x^(8 * 2^i).
-// nib[k] splits a byte table by nibbles (a table is linear in its index):
-// nib[k][0][n] = T[n] and nib[k][1][n] = T[n << 4] for T = t[k] (k < 16) or
-// T = z[5][k - 16] (the shift by 1 KiB), so T[b] = nib[k][0][b & 15] ^
-// nib[k][1][b >> 4] with two 16-entry lookups that never conflict in LDS banks.
+// mf[4t + p][l]: lane l's FP4 operand of the pack's CRC matrix for 1 KiB step
+// t of a 4 KiB batch and bit plane p; col[k][n][j] = (n << 4k) * x^(128 (31 - j)):
+// nibble k of column j's state carried past the columns after it.
 struct CrcTables {
     uint32_t t[16][256];
     uint32_t z[7][4][256];
     uint32_t xp[64];
-    uint32_t nib[20][2][16];
+    uint32_t col[8][16][32];
+    uint32_t mf[16][64][4];
 };
 
 enum PackMode { kModePack = 0, kModeVerify = 1 };
@@ -118,7 +118,7 @@ struct SlotRange {
 };
 
 // Kernel launchers (crum_kernels.hip).  All enqueue on `s`.
-void build_crc_tables(CrcTables* host);
+const CrcTables& crc_tables();  // the constants, in host memory
 // cand (may be null): bitmap over global pages; pages whose bit is clear are
 // flagged clean without being read (they are known to equal their shadow).
 // stamp (may be null): two words, the wall clock at the launch's start and
@@ -148,19 +148,16 @@ hipError_t launch_list(const uint64_t* bitmap, const uint32_t* prefix, uint64_t 
 // Pack, verify and scatter work on (slot, piece) items: a page of 2^ps bytes
 // is cut into pieces of 2^min(ps, piece_shift) bytes, np_shift is log2 of the
 // largest piece count per slot in the launch, and finalize combines the piece
-// CRCs of pages larger than one piece.  depth: 16-byte loads in flight per
-// lane (4, 8 or 16).  variant (0..5): how the CRC step splits its table
-// lookups between byte and nibble tables.  Pack updates the shadows of regions whose flags bit 0
-// is set.  unit_flags (pack only, may be null): the diff's per-unit flags of
-// the same page space; units flagged clean are then read from the shadow.
-// nt_store: bit 0 (pack only) writes the image with non-temporal stores;
-// bit 1 issues each lane's next loads before folding the current ones.
+// CRCs of pages larger than one piece.  Pack updates the shadows of regions
+// whose flags bit 0 is set.  unit_flags (pack only, may be null): the diff's
+// per-unit flags of the same page space (4-byte aligned, padded to whole
+// words); units flagged clean are then read from the shadow.  nt: kPackNt*
+// bits.
 hipError_t launch_pack(int mode, const DevRegion* regs, uint32_t n_regs, const DevRequest* reqs,
                        const DevReqOut* out, const uint32_t* list, SlotRange range,
                        uint32_t np_shift, uint32_t piece_shift, const uint8_t* unit_flags,
                        uint8_t* staging, uint32_t* crc_out, uint32_t* partials,
-                       const CrcTables* tabs, DevGlobal* glob, int blocks, int depth,
-                       int variant, hipStream_t s, int nt_store = 0);
+                       const CrcTables* tabs, DevGlobal* glob, int blocks, hipStream_t s, int nt);
 hipError_t launch_finalize(int mode, const DevRegion* regs, uint32_t n_regs,
                            const DevRequest* reqs, const DevReqOut* out, const uint32_t* list,
                            SlotRange range, uint32_t np_shift, uint32_t piece_shift,

@@ -146,16 +146,16 @@ struct crum_ctx {
     bool diff_nt = true;
     uint64_t drain_chunk_bytes = 8ull << 20;
     uint32_t piece_shift = crum::kPieceShiftDefault;
-    int pack_depth = 4;
+    int pack_depth = 4;  // pack_depth, crc_variant, pack_pf: kept for get_param, see crum.h
     int diff_prio = 0;
-    int crc_variant = crum::kCrcVariantAuto;
+    int crc_variant = 6;
     int plan_order = 0;
     uint64_t direct_bytes = 0;  // opt-in: worst-case images up to this size go straight to the host
     uint32_t chunk_growth = 4;  // growth factor of pipelined chunks and plan groups
     bool pack_nt = false;       // non-temporal image stores in the pack
     bool pack_ntl = true;       // pack/verify: non-temporal page loads
     uint8_t diff_group = 2;     // diff: 4 KiB units per wave (1, 2 or 4)
-    bool pack_pf = false;       // pack/verify: next loads issued before folding the current
+    bool pack_pf = false;
     // tuned shapes per workload class (crum_ctx_create's tuning cache), applied
     // to a call's parameters that crum_ctx_set_param has not set
     std::vector<crum::TunedClass> tuned;
@@ -198,9 +198,7 @@ inline const CrcTables* ctx_tables(const crum_ctx* c) { return c->d_tabs; }
 inline int ctx_diff_nt(const crum_ctx* c) { return c->diff_nt ? 1 : 0; }
 inline hipStream_t ctx_side_stream(const crum_ctx* c) { return c->side; }
 inline uint32_t ctx_piece_shift(const crum_ctx* c) { return c->piece_shift; }
-inline int ctx_pack_depth(const crum_ctx* c) { return c->pack_depth; }
 inline int ctx_diff_prio(const crum_ctx* c) { return c->diff_prio; }
-inline int ctx_crc_variant(const crum_ctx* c) { return c->crc_variant; }
 inline int ctx_plan_order(const crum_ctx* c) { return c->plan_order; }
 inline bool ctx_times(const crum_ctx* c, int cls) { return (c->timing_mask >> cls) & 1u; }
 inline void ctx_add_timing(crum_ctx* c, int cls, double ms)
@@ -210,18 +208,16 @@ inline void ctx_add_timing(crum_ctx* c, int cls, double ms)
 }
 inline uint32_t ctx_chunk_growth(const crum_ctx* c) { return c->chunk_growth; }
 inline int ctx_pack_nt(const crum_ctx* c) { return c->pack_nt ? 1 : 0; }
-// launch_pack's flag bits: 1 non-temporal image stores, 2 prefetching loop
-// bit 0: non-temporal image stores; bit 1: next loads issued early (cached
-// loads only); bit 2: non-temporal page loads
 // Units per wave of a diff launch whose smallest unit is 1 << min_us bytes:
 // the context's group for 4 KiB units, else one.
 inline int ctx_diff_group(const crum_ctx* c, uint32_t min_us)
 {
     return min_us == 12 ? c->diff_group : 1;
 }
+// launch_pack's flags.
 inline int ctx_pack_flags(const crum_ctx* c)
 {
-    return (c->pack_nt ? 1 : 0) | (c->pack_pf ? 2 : 0) | (c->pack_ntl ? 4 : 0);
+    return (c->pack_nt ? kPackNtStore : 0) | (c->pack_ntl ? kPackNtLoad : 0);
 }
 
 // Applies the context's tuned shapes for one call's workload class, for the

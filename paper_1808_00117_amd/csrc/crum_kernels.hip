@@ -22,20 +22,19 @@
 // Restore: k_restore_check (the image's own checks, also over one or more
 // workgroups), k_scan, k_list, k_pack (verify), k_scatter.
 //
-// CRC-32C on the device.  The polynomial arithmetic is in gf2.h.  A wave
-// processes a piece of n = 64*T 16-byte words; lane l takes words l, l+64,
-// ..., so every load is coalesced.  Lane l keeps a Horner accumulator
-//   C_l = sum_t raw(w_{l+64t}) * x^(8*1024*(T-1-t)),
-// stepping with "shift by 1024 bytes" (4 table lookups) plus slicing-by-16 of
-// the new word (16 lookups).  The piece's raw CRC is
-//   sum_l C_l * x^(8*16*(63-l)),
-// formed by a 6-level butterfly over lanes (level k shifts the lower half by
-// 16*2^k bytes).  Pieces of one page combine the same way with a shift by the
-// piece length; the standard CRC adds crc_init_fix(page bytes).  Each table
-// lookup may also be done as two lookups into 16-entry nibble tables, which
-// never conflict in LDS banks (CrcVariant).
+// CRC-32C on the device.  The polynomial arithmetic is in gf2.h.  Page bytes go
+// through the matrix cores (k_pack): a raw CRC is linear over GF(2), so the 32
+// CRC bits of a 4 KiB batch are a 32 x 32768 bit matrix times its bits, and
+// the FP4 matrix instruction counts, per CRC bit, the set bits that reach it;
+// the count's parity is the bit.  See fold_4k.  The header and image-check
+// kernels work on short messages with byte tables in LDS (slicing by 16, a
+// Horner step and a butterfly over lanes; see wg_crc_steps).  Pieces of one
+// page combine by a shift by the piece length; the standard CRC adds
+// crc_init_fix(page bytes).
 #include "crum_dev.h"
 #include "gf2.h"
+
+#include <cstring>
 
 namespace crum {
 
@@ -56,7 +55,7 @@ typedef uint32_t __attribute__((address_space(1)))* gu32;
 
 // ------------------------------------------------------------ CRC tables
 
-void build_crc_tables(CrcTables* h)
+static void fill_crc_tables(CrcTables* h)
 {
     for (int k = 0; k < 16; ++k) {
         const uint32_t xk = gf2_xpow8n((uint64_t)k + 1);
@@ -72,13 +71,41 @@ void build_crc_tables(CrcTables* h)
     }
     for (int i = 0; i < 64; ++i)
         h->xp[i] = gf2_xpow8n(1ull << i);
-    for (int k = 0; k < 20; ++k) {
-        const uint32_t* T = k < 16 ? h->t[k] : h->z[5][k - 16];
-        for (int n = 0; n < 16; ++n) {
-            h->nib[k][0][n] = T[n];
-            h->nib[k][1][n] = T[n << 4];
-        }
+    // fold_4k's matrix: the CRC bit of matrix row r, and what each data bit adds
+    // to it (see there for the layout)
+    static const uint32_t unit[4] = {4, 2, 1, 4};  // FP4 2.0, 1.0, 0.5, 2.0
+    std::memset(h->mf, 0, sizeof(h->mf));
+    for (int step = 0; step < 4; ++step)
+        for (int half = 0; half < 2; ++half)
+            for (int d = 0; d < 4; ++d) {
+                const uint32_t x = gf2_xpow8n(16 - 4 * d + 512 * (7 - (2 * step + half)));
+                for (int bit = 0; bit < 32; ++bit) {
+                    const uint32_t c = gf2_mulmod(1u << bit, x);
+                    const int n = bit >> 2, plane = bit & 3;
+                    for (int r = 0; r < 32; ++r) {
+                        const int crc_bit = 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3);
+                        if ((c >> crc_bit) & 1u)
+                            h->mf[step * 4 + plane][32 * half + r][d] |= unit[plane] << (4 * n);
+                    }
+                }
+            }
+    for (int j = 0; j < 32; ++j) {
+        const uint32_t x = gf2_xpow8n(16 * (31 - j));
+        for (int k = 0; k < 8; ++k)
+            for (int n = 0; n < 16; ++n)
+                h->col[k][n][j] = gf2_mulmod((uint32_t)n << (4 * k), x);
     }
+}
+
+// Filled at the first use: every context uploads the same constants.
+const CrcTables& crc_tables()
+{
+    static const CrcTables* t = [] {
+        CrcTables* h = new CrcTables;
+        fill_crc_tables(h);
+        return h;
+    }();
+    return *t;
 }
 
 // LDS layout of the header and restore-check kernels (words): the slicing
@@ -86,13 +113,10 @@ void build_crc_tables(CrcTables* h)
 constexpr int kSliceWords = 16 * 256;                      // 16 KiB
 constexpr int kAllTabWords = kSliceWords + 7 * 4 * 256;    // 44 KiB
 
-// LDS layout of the pack and verify kernels (words): slicing tables, nibble
-// tables, shift-by-1-KiB tables; 22.5 KiB.  The butterfly's shift tables
-// (used once per piece) are read from global memory: holding nibble versions
-// of them in LDS as well (25 KiB) measured no faster.
-constexpr int kNibOff = kSliceWords;
-constexpr int kZ5Off = kNibOff + 20 * 2 * 16;
-constexpr int kPackLdsWords = kZ5Off + 4 * 256;
+// LDS layout of the pack and verify kernels (words): the column tables (col),
+// then the shift-by-4-KiB byte tables (z[6]); 20 KiB.
+constexpr int kColWords = 8 * 16 * 32;
+constexpr int kPackLdsWords = kColWords + 4 * 256;
 
 // Every kernel of this file runs 256-thread workgroups.
 constexpr int kBlock = 256;
@@ -127,24 +151,10 @@ __device__ __forceinline__ void stage_words(uint32_t* __restrict__ dst,
 
 __device__ __forceinline__ void load_pack_tables(uint32_t* lds, const CrcTables* tabs)
 {
-    stage_words<kSliceWords>(lds, &tabs->t[0][0]);
-    stage_words<20 * 2 * 16>(lds + kNibOff, &tabs->nib[0][0][0]);
-    stage_words<4 * 256>(lds + kZ5Off, &tabs->z[5][0][0]);
+    stage_words<kColWords>(lds, &tabs->col[0][0][0]);
+    stage_words<4 * 256>(lds + kColWords, &tabs->z[6][0][0]);
     __syncthreads();
 }
-
-// Variants of the per-word CRC step that trade LDS bank conflicts (a byte
-// lookup into a 256-entry table) against VALU work (two conflict-free nibble
-// lookups): the first NB of the 16 data bytes use byte tables, the rest
-// nibble tables; SB selects byte tables for the 4-byte shift by 1 KiB.
-template <int V> struct CrcVariant;
-template <> struct CrcVariant<0> { static constexpr int NB = 16, SB = 1; };
-template <> struct CrcVariant<1> { static constexpr int NB = 8, SB = 0; };
-template <> struct CrcVariant<2> { static constexpr int NB = 6, SB = 0; };
-template <> struct CrcVariant<3> { static constexpr int NB = 4, SB = 0; };
-template <> struct CrcVariant<4> { static constexpr int NB = 0, SB = 0; };
-template <> struct CrcVariant<5> { static constexpr int NB = 6, SB = 1; };
-constexpr int kCrcVariants = 6;
 
 // raw CRC of one 16-byte word (bytes b0..b15, b0 = low byte of w.x)
 __device__ __forceinline__ uint32_t word_crc(const uint32_t* __restrict__ T, uint4 w)
@@ -187,89 +197,10 @@ __device__ __forceinline__ uint32_t lds_at(const uint32_t* __restrict__ L, uint3
     return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(L) + off);
 }
 
-// byte jj of q in the low byte, zeros above (one v_perm_b32)
-__device__ __forceinline__ uint32_t byte_of(uint32_t q, int jj)
-{
-    return __builtin_amdgcn_perm(0u, q, 0x0c0c0c00u | (uint32_t)jj);
-}
-
 // a ^ b ^ c in one instruction
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
 {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
-}
-
-// XOR of the table entries of the 4 bytes of q, byte jj at table position
-// k0 - jj (k0 = 15 - 4*word for data words).  Nibble lookups take their
-// addresses from two masked copies of q that hold 4*nibble in every byte, so
-// each lookup costs one byte extract; byte lookups shift the extracted byte.
-// `nb` (constant after unrolling) is how many of the 4 bytes use byte tables.
-__device__ __forceinline__ uint32_t word4_crc(const uint32_t* __restrict__ L, uint32_t q,
-                                              int nb, int byte_base0, int byte_step,
-                                              int nib_k0, uint32_t r)
-{
-    const uint32_t lo4 = (q << 2) & 0x3C3C3C3Cu;
-    const uint32_t hi4 = (q >> 2) & 0x3C3C3C3Cu;
-    uint32_t pend = 0;  // a byte-table value waiting for a partner in xor3
-    bool have = false;
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-        if (jj < nb) {
-            const uint32_t a = byte_of(q, jj) << 2;
-            const uint32_t v = lds_at(L, 4u * (uint32_t)(byte_base0 + jj * byte_step) + a);
-            if (have) {
-                r = xor3(r, pend, v);
-                have = false;
-            } else {
-                pend = v;
-                have = true;
-            }
-        } else {
-            const uint32_t base = 4u * (uint32_t)(kNibOff + (nib_k0 - jj) * 32);
-            r = xor3(r, lds_at(L, base + byte_of(lo4, jj)), lds_at(L, base + 64u + byte_of(hi4, jj)));
-        }
-    }
-    return have ? r ^ pend : r;
-}
-
-// raw CRC of one 16-byte word with the pack layout (as word_crc): byte j of
-// the word uses table position 15 - j; the first NB bytes use byte tables
-template <int V>
-__device__ __forceinline__ uint32_t word_crc_v(const uint32_t* __restrict__ L, uint4 w)
-{
-    constexpr int NB = CrcVariant<V>::NB;
-    const uint32_t v[4] = {w.x, w.y, w.z, w.w};
-    uint32_t r = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int nb = NB - 4 * q < 0 ? 0 : (NB - 4 * q > 4 ? 4 : NB - 4 * q);
-        r = word4_crc(L, v[q], nb, (15 - 4 * q) * 256, -256, 15 - 4 * q, r);
-    }
-    return r;
-}
-
-// state carried through 1024 zero bytes with the pack layout: byte i of the
-// state uses z[5][i], i.e. nibble position 16 + i
-template <int V>
-__device__ __forceinline__ uint32_t shift1k_v(const uint32_t* __restrict__ L, uint32_t s)
-{
-    constexpr int SB = CrcVariant<V>::SB;
-    if (SB) {
-        return lds_at(L, 4u * kZ5Off + ((s << 2) & 0x3FCu)) ^
-               lds_at(L, 4u * (kZ5Off + 256) + ((s >> 6) & 0x3FCu)) ^
-               lds_at(L, 4u * (kZ5Off + 512) + ((s >> 14) & 0x3FCu)) ^
-               lds_at(L, 4u * (kZ5Off + 768) + ((s >> 22) & 0x3FCu));
-    }
-    // nibble positions 16..19 ascend with the byte index
-    const uint32_t lo4 = (s << 2) & 0x3C3C3C3Cu;
-    const uint32_t hi4 = (s >> 2) & 0x3C3C3C3Cu;
-    uint32_t r = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t base = 4u * (uint32_t)(kNibOff + (16 + i) * 32);
-        r = xor3(r, lds_at(L, base + byte_of(lo4, i)), lds_at(L, base + 64u + byte_of(hi4, i)));
-    }
-    return r;
 }
 
 // Butterfly over the 64 lanes: afterwards every lane holds sum_l C_l*x^(128(63-l)).
@@ -297,147 +228,99 @@ __device__ __forceinline__ uint32_t lane_combine(const uint32_t* __restrict__ ld
     return lane_combine_z(lds, lds + kSliceWords, s, lane);
 }
 
-// Source of a piece, 1 KiB step by step.  Bit j of `dirty` tells whether
-// diff unit j of the piece (units of 2^(ush+10) bytes) differed from the
-// shadow; a clean unit's bytes equal the shadow's, so they may be read from
-// `alt` (the shadow) instead of `cur`.  That keeps re-reads off the host link
-// when the current bytes live in host memory.  alt == nullptr: always cur.
-struct PieceSrc {
-    gcv4 cur;
-    gcv4 alt;
-    uint32_t dirty;
-    uint32_t ush;
-    __device__ __forceinline__ bool is_dirty(uint32_t t) const { return (dirty >> (t >> ush)) & 1u; }
-    __device__ __forceinline__ gcv4 at(uint32_t t) const
-    {
-        return (alt && !is_dirty(t)) ? alt : cur;
-    }
+// ------------------------------------------------------------ matrix-core CRC
+
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// The constant operands of fold_4k: per 1 KiB step and bit plane, this lane's
+// 32 FP4 values of the matrix (64 registers for the life of the kernel).
+struct CrcMatrix {
+    u32x4 a[16];
 };
 
-// lds: the pack layout (kPackLdsWords); V: the CRC step variant.  STORE: 0
-// reads only (verify), 1 copies into dst, 2 copies with non-temporal stores
-// (the image is streamed out and not read again by the kernels).
-template <int LD>
-__device__ __forceinline__ u32x4 piece_load(gcv4 p)
+__device__ __forceinline__ void load_crc_matrix(CrcMatrix& m, const CrcTables* __restrict__ tabs,
+                                                uint32_t lane)
 {
-    if (LD)
-        return __builtin_nontemporal_load(p);
-    return *p;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        m.a[i] = *(gcv4)(&tabs->mf[i][lane][0]);
 }
 
-template <int STORE, int U, int V, int LD = 0>
-__device__ __forceinline__ uint32_t piece_steps(const PieceSrc& src, gv4 __restrict__ dst,
-                                                gv4 __restrict__ sh, uint32_t* t_io,
-                                                uint32_t steps, uint32_t lane,
-                                                const uint32_t* __restrict__ lds, uint32_t s)
+__device__ __forceinline__ f32x16 mfma_fp4(u32x4 a, u32x4 b, f32x16 c)
 {
-    uint32_t t = *t_io;
-    for (; t + U <= steps; t += U) {
-        u32x4 w[U];
+    const i32x8 A = {(int)a.x, (int)a.y, (int)a.z, (int)a.w, 0, 0, 0, 0};
+    const i32x8 B = {(int)b.x, (int)b.y, (int)b.z, (int)b.w, 0, 0, 0, 0};
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, B, c, 4, 4, 0, 0, 0, 0);
+}
+
+// Raw CRCs of a 4 KiB batch by columns.  w[t]: this lane's 16 bytes of 1 KiB
+// step t (word 64t + lane).  Matrix column j = lane % 32 takes the eight words
+// j, j + 32, ... , j + 224; lane half h = lane / 32 holds every second one.
+// Masking a word with 0x11111111, 0x22222222 and 0x44444444 leaves nibbles
+// that are FP4 numbers, 0 or 0.5, 1 or 2, one per data bit (bit 3 of a nibble is
+// FP4's sign, so that plane is shifted down to 0.5 first); the matrix holds
+// the reciprocal where the bit reaches the CRC bit of the row and 0
+// elsewhere.  Every product is then 0 or 1 and every sum a whole number of at
+// most 1024: float32 holds them exactly, and their parities are the CRC bits.
+// Adding 2^23 puts a count's lowest bit into the lowest bit of the word.  Rows
+// are ordered so that the 16 results of a lane of half h are CRC bits 16h ..
+// 16h + 15, in order.  Returns those bits in place, zeros elsewhere: the
+// column's raw CRC is the XOR of its two lanes.
+__device__ __forceinline__ uint32_t fold_4k(const CrcMatrix& m, const u32x4* __restrict__ w,
+                                            uint32_t half)
+{
+    f32x16 c;
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            w[u] = piece_load<LD>(src.at(t + u) + (t + u) * 64 + lane);
-        if (STORE) {
+    for (int i = 0; i < 16; ++i)
+        c[i] = 0.0f;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (STORE == 2)
-                    __builtin_nontemporal_store(w[u], dst + (t + u) * 64 + lane);
-                else
-                    dst[(t + u) * 64 + lane] = w[u];
-            }
-            if (sh) {
-                // clean units already hold these bytes in the shadow
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (src.is_dirty(t + u))
-                        sh[(t + u) * 64 + lane] = w[u];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            s = shift1k_v<V>(lds, s) ^
-                word_crc_v<V>(lds, make_uint4(w[u].x, w[u].y, w[u].z, w[u].w));
+    for (int t = 0; t < 4; ++t) {
+        c = mfma_fp4(m.a[4 * t], w[t] & 0x11111111u, c);
+        c = mfma_fp4(m.a[4 * t + 1], w[t] & 0x22222222u, c);
+        c = mfma_fp4(m.a[4 * t + 2], w[t] & 0x44444444u, c);
+        c = mfma_fp4(m.a[4 * t + 3], (w[t] >> 3) & 0x11111111u, c);
     }
-    *t_io = t;
-    return s;
+    uint32_t r = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        r = __builtin_amdgcn_alignbit(__float_as_uint(c[i] + 8388608.0f), r, 1);
+    return half ? r & 0xFFFF0000u : r >> 16;
 }
 
-// As piece_steps, with the loads of the next U steps issued before the
-// stores and CRC of the current ones, so a wave keeps page loads in flight
-// while it works through its LDS table lookups.
-template <int STORE, int U, int V, int LD = 0>
-__device__ __forceinline__ uint32_t piece_steps_pf(const PieceSrc& src, gv4 __restrict__ dst,
-                                                   gv4 __restrict__ sh, uint32_t* t_io,
-                                                   uint32_t steps, uint32_t lane,
-                                                   const uint32_t* __restrict__ lds, uint32_t s)
+// The lane's state carried through 4 KiB of zeros (lds: the pack layout).
+__device__ __forceinline__ uint32_t shift_4k(const uint32_t* __restrict__ lds, uint32_t s)
 {
-    uint32_t t = *t_io;
-    if (t + U > steps)
-        return s;
-    u32x4 w[U];
+    return xor3(lds_at(lds, 4u * kColWords + ((s << 2) & 0x3FCu)),
+                lds_at(lds, 4u * (kColWords + 256) + ((s >> 6) & 0x3FCu)),
+                lds_at(lds, 4u * (kColWords + 512) + ((s >> 14) & 0x3FCu))) ^
+           lds_at(lds, 4u * (kColWords + 768) + ((s >> 22) & 0x3FCu));
+}
+
+// Raw CRC of the piece from the lanes' column states: column j is followed by
+// 31 - j more words, so its state is multiplied by x^(128(31-j)) (eight nibble
+// lookups in the column's own tables, one bank per lane) and all lanes are
+// XORed.  Uniform over the wave.
+__device__ __forceinline__ uint32_t columns_crc(const uint32_t* __restrict__ lds, uint32_t s,
+                                                uint32_t lane)
+{
+    const uint32_t j4 = (lane & 31u) * 4u;
+    uint32_t v[8];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-        w[u] = piece_load<LD>(src.at(t + u) + (t + u) * 64 + lane);
-    for (;;) {
-        const bool more = t + 2 * U <= steps;
-        u32x4 nx[U];
-        if (more) {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                nx[u] = piece_load<LD>(src.at(t + U + u) + (t + U + u) * 64 + lane);
-        }
-        if (STORE) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (STORE == 2)
-                    __builtin_nontemporal_store(w[u], dst + (t + u) * 64 + lane);
-                else
-                    dst[(t + u) * 64 + lane] = w[u];
-            }
-            if (sh) {
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (src.is_dirty(t + u))
-                        sh[(t + u) * 64 + lane] = w[u];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            s = shift1k_v<V>(lds, s) ^
-                word_crc_v<V>(lds, make_uint4(w[u].x, w[u].y, w[u].z, w[u].w));
-        t += U;
-        if (!more)
-            break;
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            w[u] = nx[u];
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t n = k == 0 ? s << 7 : k == 1 ? s << 3 : s >> (4 * k - 7);
+        v[k] = lds_at(lds, 2048u * k + ((n & 0x780u) | j4));
     }
-    *t_io = t;
-    return s;
-}
-
-// Raw (zero-initialised) CRC of `steps` KiB, copied to dst (and to the shadow
-// sh, dirty units only) when STORE.  DEPTH: 16-byte loads each lane issues
-// before it folds them into its CRC; PF: the next DEPTH loads are issued
-// before the current ones are folded.  All lanes return the same value.
-// gz: z[0] of the shift tables in global memory (the butterfly's shifts).
-template <int STORE, int DEPTH, int V, bool PF, int LD = 0>
-__device__ __forceinline__ uint32_t wave_piece_crc(const PieceSrc& src, gv4 __restrict__ dst,
-                                                   gv4 __restrict__ sh, uint32_t steps,
-                                                   uint32_t lane,
-                                                   const uint32_t* __restrict__ lds,
-                                                   const uint32_t* __restrict__ gz)
-{
-    uint32_t s = 0;
-    uint32_t t = 0;
-    if (PF)
-        s = piece_steps_pf<STORE, DEPTH, V, LD>(src, dst, sh, &t, steps, lane, lds, s);
-    else
-        s = piece_steps<STORE, DEPTH, V, LD>(src, dst, sh, &t, steps, lane, lds, s);
-    if (DEPTH > 4)
-        s = piece_steps<STORE, 4, V, LD>(src, dst, sh, &t, steps, lane, lds, s);
-    s = piece_steps<STORE, 1, V, LD>(src, dst, sh, &t, steps, lane, lds, s);
-    return lane_combine_z(lds, gz, s, lane);
+    uint32_t r = xor3(xor3(v[0], v[1], v[2]), xor3(v[3], v[4], v[5]), v[6] ^ v[7]);
+    // lanes of each row of 16: xor 1, xor 2, then mirrored halves and rows
+    r ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)r, 0xB1, 0xF, 0xF, true);
+    r ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)r, 0x4E, 0xF, 0xF, true);
+    r ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)r, 0x141, 0xF, 0xF, true);
+    r ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)r, 0x140, 0xF, 0xF, true);
+    return (uint32_t)__builtin_amdgcn_readlane((int)r, 0) ^
+           (uint32_t)__builtin_amdgcn_readlane((int)r, 16) ^
+           (uint32_t)__builtin_amdgcn_readlane((int)r, 32) ^
+           (uint32_t)__builtin_amdgcn_readlane((int)r, 48);
 }
 
 // ------------------------------------------------------------ region lookup
@@ -902,12 +785,48 @@ __device__ __forceinline__ void slot_range(const SlotRange& sr, uint64_t* lo, ui
     }
 }
 
+// A work item of k_pack found to be a piece of a page: where its bytes are and
+// where they go (wave-uniform).
+struct Piece {
+    const uint8_t* src;   // current bytes (pack) or the packed page (verify)
+    uint8_t* shadow;      // the piece's shadow, null if the region has none
+    uint8_t* dst;         // pack: the piece's place in the image
+    uint64_t unit;        // first diff unit of the piece
+    uint32_t unit_shift;
+    uint32_t batches;     // 4 KiB batches in the piece
+    uint32_t update;      // the shadow receives the piece's dirty units
+    uint32_t region;
+    uint64_t item, slot;
+};
+
+// Flag of diff unit u, read as part of an aligned word so that a wave-uniform
+// u is a scalar load (a byte load counts against the vector loads in flight).
+// The flags are padded to whole words.
+__device__ __forceinline__ bool unit_dirty(const uint8_t* __restrict__ flags, uint64_t u)
+{
+    const uint32_t w = reinterpret_cast<const uint32_t*>(flags)[u >> 2];
+    return (w >> (8 * (uint32_t)(u & 3))) & 0xFFu;
+}
+
 // Work item = (slot, piece); pieces per slot = 2^np_shift for the launch.
 // Pack: copy the dirty page into the image's page area (and the shadow) and
 // write its CRC to crc_out[slot].  Verify: recompute the CRC of a packed page
 // of the image and compare with the image's CRC array.
-template <int MODE, int DEPTH, int V>
-__global__ __launch_bounds__(256) void k_pack(const DevRegion* __restrict__ regs, uint32_t n_regs,
+//
+// A wave works through its items as one stream of 4 KiB batches, whichever
+// page they belong to: the loads of the next batch are in flight while the
+// current one is stored and folded into its CRC.
+//
+// Bound by memory.  A 1 KiB step of the CRC costs a wave four matrix
+// instructions and about 25 vector ones, against 20 LDS lookups in byte tables
+// (or 32 and more in nibble tables) before, which kept the LDS of each compute
+// unit busy for about 160 cycles per KiB: the verify of 768 MB of 4 KiB pages
+// went from 236 to 129 us (3.3 to 5.9 TB/s), the pack of a 1 GiB first
+// snapshot (2 MiB pages) from 428 to 418 us, of 570 MB of 4 KiB pages with
+// their shadows from 412 to 402.  The matrix takes 64 registers, so a SIMD
+// holds four waves; their 8 KiB each in flight cover the memory's latency.
+template <int MODE, bool NT_LOAD, bool NT_STORE>
+__global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ regs, uint32_t n_regs,
                                               const DevRequest* __restrict__ reqs,
                                               const DevReqOut* __restrict__ out,
                                               const uint32_t* __restrict__ list, SlotRange sr,
@@ -917,7 +836,7 @@ __global__ __launch_bounds__(256) void k_pack(const DevRegion* __restrict__ regs
                                               uint32_t* __restrict__ crc_out,
                                               uint32_t* __restrict__ partials,
                                               const CrcTables* __restrict__ tabs,
-                                              DevGlobal* __restrict__ glob, uint32_t nt_store)
+                                              DevGlobal* __restrict__ glob)
 {
     __shared__ __attribute__((aligned(16))) uint32_t lds[kPackLdsWords];
     if (MODE == kModeVerify && glob->fmt_bad)
@@ -929,167 +848,149 @@ __global__ __launch_bounds__(256) void k_pack(const DevRegion* __restrict__ regs
     // the items leave before staging their tables
     if ((uint64_t)blockIdx.x * 4 >= n_items)
         return;
-    load_pack_tables(lds, tabs);
-    const uint32_t* gz = &tabs->z[0][0][0];
     const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t half = lane >> 5;
+    CrcMatrix mat;
+    load_crc_matrix(mat, tabs, lane);
+    load_pack_tables(lds, tabs);
     const uint64_t wave =
         (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t n_waves = (uint64_t)gridDim.x * 4;
     uint32_t r = 0;
     uint64_t r_lo = 1, r_hi = 0;
-    for (uint64_t item = wave; item < n_items; item += n_waves) {
-        const uint64_t k = slot0 + (item >> np_shift);
-        const uint32_t piece = (uint32_t)(item & ((1ull << np_shift) - 1));
-        const uint64_t g = list[k];
-        if (g < r_lo || g >= r_hi) {
-            r = find_region<3>(regs, n_regs, g);
-            r_lo = regs[r].first_page;
-            r_hi = r_lo + (regs[r].len >> regs[r].page_shift);
-        }
-        const DevRegion& R = regs[r];
-        if (g < r_lo || g >= r_hi)
-            continue;  // only reachable for a corrupt restore bitmap (gated above)
-        const DevRequest& Q = reqs[R.req];
-        const DevReqOut& O = out[R.req];
-        if (MODE == kModePack && O.code != 0)
-            continue;  // the request's image did not fit: nothing is written
-        const uint32_t ps = R.page_shift;
-        const uint32_t pb_shift = ps < piece_shift ? ps : piece_shift;
-        if (piece >= (1u << (ps - pb_shift)))
-            continue;
-        const uint64_t local = k - O.slot_base;
-        const uint64_t page_off = (g - R.first_page) << ps;
-        const uint64_t piece_off = (uint64_t)piece << pb_shift;
-        uint8_t* img = staging + O.img_base;
-        uint8_t* slot_ptr = img + Q.data_off + (local << ps) + piece_off;
-        const uint32_t steps = 1u << (pb_shift - 10);
-        uint32_t raw;
-        if (MODE == kModePack) {
-            PieceSrc src{(gcv4)(R.cur + page_off + piece_off), nullptr,
-                         ~0u, 0};
-            if (unit_flags && R.shadow) {
-                // the piece's diff units: clean ones are read from the shadow
-                const uint32_t us = R.unit_shift;
-                const uint64_t u0 = R.first_unit + ((page_off + piece_off) >> us);
-                const uint32_t n_u = pb_shift > us ? 1u << (pb_shift - us) : 1u;
-                uint32_t m = 0;
-                for (uint32_t j = 0; j < n_u; ++j)
-                    m |= (unit_flags[u0 + j] ? 1u : 0u) << j;
-                src.alt = (gcv4)(R.shadow + page_off + piece_off);
-                src.dirty = m;
-                src.ush = us - 10;
+
+    // the first item at or after `item` (this wave's items) that is a piece
+    auto find = [&](uint64_t item, Piece& p) -> bool {
+        for (; item < n_items; item += n_waves) {
+            const uint64_t k = slot0 + (item >> np_shift);
+            const uint32_t piece = (uint32_t)(item & ((1ull << np_shift) - 1));
+            const uint64_t g = list[k];
+            if (g < r_lo || g >= r_hi) {
+                r = find_region<3>(regs, n_regs, g);
+                r_lo = regs[r].first_page;
+                r_hi = r_lo + (regs[r].len >> regs[r].page_shift);
             }
-            gv4 sh = ((R.flags & 1u) && R.shadow)
-                            ? (gv4)(R.shadow + page_off + piece_off)
-                            : nullptr;
-            if (nt_store & 4u)
-                raw = (nt_store & 1u) ? wave_piece_crc<2, DEPTH, V, false, 1>(
-                                            src, (gv4)slot_ptr, sh, steps, lane, lds, gz)
-                                      : wave_piece_crc<1, DEPTH, V, false, 1>(
-                                            src, (gv4)slot_ptr, sh, steps, lane, lds, gz);
-            else if (nt_store & 2u)
-                raw = (nt_store & 1u) ? wave_piece_crc<2, DEPTH, V, true>(
-                                            src, (gv4)slot_ptr, sh, steps, lane, lds, gz)
-                                      : wave_piece_crc<1, DEPTH, V, true>(
-                                            src, (gv4)slot_ptr, sh, steps, lane, lds, gz);
-            else
-                raw = (nt_store & 1u) ? wave_piece_crc<2, DEPTH, V, false>(
-                                            src, (gv4)slot_ptr, sh, steps, lane, lds, gz)
-                                      : wave_piece_crc<1, DEPTH, V, false>(
-                                            src, (gv4)slot_ptr, sh, steps, lane, lds, gz);
-        } else {
-            const PieceSrc src{(gcv4)slot_ptr, nullptr, ~0u, 0};
-            raw = (nt_store & 4u)
-                      ? wave_piece_crc<0, DEPTH, V, false, 1>(src, nullptr, nullptr, steps, lane,
-                                                              lds, gz)
-                  : (nt_store & 2u)
-                      ? wave_piece_crc<0, DEPTH, V, true>(src, nullptr, nullptr, steps, lane, lds,
-                                                          gz)
-                      : wave_piece_crc<0, DEPTH, V, false>(src, nullptr, nullptr, steps, lane,
-                                                           lds, gz);
+            const DevRegion& R = regs[r];
+            if (g < r_lo || g >= r_hi)
+                continue;  // only reachable for a corrupt restore bitmap (gated above)
+            const DevReqOut& O = out[R.req];
+            if (MODE == kModePack && O.code != 0)
+                continue;  // the request's image did not fit: nothing is written
+            const uint32_t ps = R.page_shift;
+            const uint32_t pb_shift = ps < piece_shift ? ps : piece_shift;
+            if (piece >= (1u << (ps - pb_shift)))
+                continue;
+            const uint64_t off = ((g - R.first_page) << ps) + ((uint64_t)piece << pb_shift);
+            uint8_t* packed = staging + O.img_base + reqs[R.req].data_off +
+                              ((k - O.slot_base) << ps) + ((uint64_t)piece << pb_shift);
+            p.item = item;
+            p.slot = k;
+            p.region = r;
+            p.batches = 1u << (pb_shift - 12);
+            p.dst = packed;
+            if (MODE == kModePack) {
+                p.src = R.cur + off;
+                p.shadow = R.shadow ? R.shadow + off : nullptr;
+                p.update = R.flags & 1u;
+                p.unit_shift = R.unit_shift;
+                p.unit = R.first_unit + (off >> R.unit_shift);
+            } else {
+                p.src = packed;
+            }
+            return true;
         }
-        if (lane != 0)
-            continue;
-        if (ps > pb_shift) {
-            partials[item] = raw;
-            continue;
+        return false;
+    };
+    // whether batch b of the piece lies in a diff unit that differs from the
+    // shadow; a clean unit's bytes equal the shadow's
+    auto dirty = [&](const Piece& p, uint32_t b) -> bool {
+        return !(unit_flags && p.shadow) || unit_dirty(unit_flags, p.unit + ((b << 12) >> p.unit_shift));
+    };
+    // clean batches are read from the shadow, which keeps re-reads off the
+    // host link when the current bytes live in host memory
+    auto load = [&](const Piece& p, uint32_t b, bool d, u32x4* w) {
+        const gcv4 a = (gcv4)((MODE == kModePack && !d ? p.shadow : p.src) + (b << 12)) + lane;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            w[t] = NT_LOAD ? __builtin_nontemporal_load(a + 64 * t) : a[64 * t];
+    };
+
+    Piece cur;
+    if (!find(wave, cur))
+        return;
+    uint32_t b = 0, s = 0;
+    bool d = MODE == kModePack ? dirty(cur, 0) : true;
+    u32x4 wa[4], wb[4];
+    load(cur, 0, d, wa);
+    // one batch: issue the next one's loads into nx, then finish w
+    auto step = [&](u32x4* w, u32x4* nx) -> bool {
+        Piece next = cur;
+        uint32_t nb = b + 1;
+        bool more = true, nd = true;
+        if (nb == cur.batches) {
+            nb = 0;
+            more = find(cur.item + n_waves, next);
         }
-        const uint32_t crc = raw ^ Q.init_fix;
+        if (more) {
+            nd = MODE == kModePack ? dirty(next, nb) : true;
+            load(next, nb, nd, nx);
+        }
         if (MODE == kModePack) {
-            crc_out[k] = crc;
-        } else {
-            const uint32_t* img_crc =
-                reinterpret_cast<const uint32_t*>(img + Q.data_off + (O.n_dirty << ps));
-            if (crc != img_crc[local])
-                atomicMin(&glob->crc_bad, (uint32_t)local);
+            const gv4 o = (gv4)(cur.dst + (b << 12)) + lane;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                if (NT_STORE)
+                    __builtin_nontemporal_store(w[t], o + 64 * t);
+                else
+                    o[64 * t] = w[t];
+            }
+            if (cur.update && cur.shadow && d) {
+                const gv4 h = (gv4)(cur.shadow + (b << 12)) + lane;
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    h[64 * t] = w[t];
+            }
         }
+        const uint32_t f = fold_4k(mat, w, half);
+        s = b ? shift_4k(lds, s) ^ f : f;
+        if (b + 1 == cur.batches) {
+            const uint32_t raw = columns_crc(lds, s, lane);
+            const DevRegion& R = regs[cur.region];
+            const uint32_t ps = R.page_shift;
+            if (ps > piece_shift) {
+                if (lane == 0)
+                    partials[cur.item] = raw;
+            } else {
+                const DevRequest& Q = reqs[R.req];
+                const uint32_t crc = raw ^ Q.init_fix;
+                if (MODE == kModePack) {
+                    if (lane == 0)
+                        crc_out[cur.slot] = crc;
+                } else {
+                    const DevReqOut& O = out[R.req];
+                    const uint64_t local = cur.slot - O.slot_base;
+                    const uint32_t* img_crc = reinterpret_cast<const uint32_t*>(
+                        staging + O.img_base + Q.data_off + (O.n_dirty << ps));
+                    if (crc != img_crc[local] && lane == 0)
+                        atomicMin(&glob->crc_bad, (uint32_t)local);
+                }
+            }
+        }
+        cur = next;
+        b = nb;
+        d = nd;
+        return more;
+    };
+    while (step(wa, wb) && step(wb, wa)) {
     }
-}
-
-template <int MODE, int DEPTH, int V>
-static void launch_pack_one(dim3 grid, hipStream_t s, const DevRegion* regs, uint32_t n_regs,
-                            const DevRequest* reqs, const DevReqOut* out, const uint32_t* list,
-                            SlotRange range, uint32_t np_shift, uint32_t piece_shift,
-                            const uint8_t* unit_flags, uint8_t* staging, uint32_t* crc_out,
-                            uint32_t* partials, const CrcTables* tabs, DevGlobal* glob,
-                            uint32_t nt_store)
-{
-    hipLaunchKernelGGL((k_pack<MODE, DEPTH, V>), grid, dim3(256), 0, s, regs, n_regs, reqs, out,
-                       list, range, np_shift, piece_shift, unit_flags, staging, crc_out,
-                       partials, tabs, glob, nt_store);
-}
-
-template <int MODE, int DEPTH>
-static void launch_pack_depth(int variant, dim3 grid, hipStream_t s, const DevRegion* regs,
-                              uint32_t n_regs, const DevRequest* reqs, const DevReqOut* out,
-                              const uint32_t* list, SlotRange range, uint32_t np_shift,
-                              uint32_t piece_shift, const uint8_t* unit_flags, uint8_t* staging,
-                              uint32_t* crc_out, uint32_t* partials, const CrcTables* tabs,
-                              DevGlobal* glob, uint32_t nt_store)
-{
-#define CRUM_PACK_V(v)                                                                        \
-    launch_pack_one<MODE, DEPTH, v>(grid, s, regs, n_regs, reqs, out, list, range, np_shift, \
-                                    piece_shift, unit_flags, staging, crc_out, partials, tabs, \
-                                    glob, nt_store)
-    switch (variant) {
-    case 0: CRUM_PACK_V(0); break;
-    case 1: CRUM_PACK_V(1); break;
-    case 2: CRUM_PACK_V(2); break;
-    case 3: CRUM_PACK_V(3); break;
-    case 4: CRUM_PACK_V(4); break;
-    default: CRUM_PACK_V(5); break;
-    }
-#undef CRUM_PACK_V
-}
-
-template <int MODE>
-static void launch_pack_mode(dim3 grid, int depth, int variant, hipStream_t s,
-                             const DevRegion* regs, uint32_t n_regs, const DevRequest* reqs,
-                             const DevReqOut* out, const uint32_t* list, SlotRange range,
-                             uint32_t np_shift, uint32_t piece_shift, const uint8_t* unit_flags,
-                             uint8_t* staging, uint32_t* crc_out, uint32_t* partials,
-                             const CrcTables* tabs, DevGlobal* glob, uint32_t nt_store)
-{
-    if (depth == 16)
-        launch_pack_depth<MODE, 16>(variant, grid, s, regs, n_regs, reqs, out, list, range,
-                                    np_shift, piece_shift, unit_flags, staging, crc_out,
-                                    partials, tabs, glob, nt_store);
-    else if (depth == 8)
-        launch_pack_depth<MODE, 8>(variant, grid, s, regs, n_regs, reqs, out, list, range,
-                                   np_shift, piece_shift, unit_flags, staging, crc_out, partials,
-                                   tabs, glob, nt_store);
-    else
-        launch_pack_depth<MODE, 4>(variant, grid, s, regs, n_regs, reqs, out, list, range,
-                                   np_shift, piece_shift, unit_flags, staging, crc_out, partials,
-                                   tabs, glob, nt_store);
 }
 
 hipError_t launch_pack(int mode, const DevRegion* regs, uint32_t n_regs, const DevRequest* reqs,
                        const DevReqOut* out, const uint32_t* list, SlotRange range,
                        uint32_t np_shift, uint32_t piece_shift, const uint8_t* unit_flags,
                        uint8_t* staging, uint32_t* crc_out, uint32_t* partials,
-                       const CrcTables* tabs, DevGlobal* glob, int blocks, int depth,
-                       int variant, hipStream_t s, int nt_store)
+                       const CrcTables* tabs, DevGlobal* glob, int blocks, hipStream_t s,
+                       int nt)
 {
     const uint64_t max_items = range.max_slots << np_shift;
     if (max_items == 0)
@@ -1099,16 +1000,27 @@ hipError_t launch_pack(int mode, const DevRegion* regs, uint32_t n_regs, const D
     const uint64_t need = (max_items + 3) / 4;
     const uint64_t nb = need < (uint64_t)blocks ? need : (uint64_t)blocks;
     const dim3 grid((unsigned)nb);
-    if (variant == kCrcVariantAuto)
-        variant = mode == kModePack ? 0 : 3;
-    if (mode == kModePack)
-        launch_pack_mode<kModePack>(grid, depth, variant, s, regs, n_regs, reqs, out, list,
-                                    range, np_shift, piece_shift, unit_flags, staging, crc_out,
-                                    partials, tabs, glob, (uint32_t)nt_store);
-    else
-        launch_pack_mode<kModeVerify>(grid, depth, variant, s, regs, n_regs, reqs, out, list,
-                                      range, np_shift, piece_shift, nullptr, staging, crc_out,
-                                      partials, tabs, glob, (uint32_t)nt_store & 6u);
+#define CRUM_PACK(M, L, S, F)                                                                  \
+    hipLaunchKernelGGL((k_pack<M, L, S>), grid, dim3(256), 0, s, regs, n_regs, reqs, out, list, \
+                       range, np_shift, piece_shift, F, staging, crc_out, partials, tabs, glob)
+    const bool ntl = (nt & kPackNtLoad) != 0, nts = (nt & kPackNtStore) != 0;
+    if (mode == kModeVerify) {
+        if (ntl)
+            CRUM_PACK(kModeVerify, true, false, nullptr);
+        else
+            CRUM_PACK(kModeVerify, false, false, nullptr);
+    } else if (ntl) {
+        if (nts)
+            CRUM_PACK(kModePack, true, true, unit_flags);
+        else
+            CRUM_PACK(kModePack, true, false, unit_flags);
+    } else {
+        if (nts)
+            CRUM_PACK(kModePack, false, true, unit_flags);
+        else
+            CRUM_PACK(kModePack, false, false, unit_flags);
+    }
+#undef CRUM_PACK
     return hipGetLastError();
 }
 
