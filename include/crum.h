@@ -417,8 +417,8 @@ void crum_server_destroy(crum_server* server);
  *   workgroups (8 per compute unit).  CRUM_PARAM_PACK_BLOCKS: grid of the
  *   pack, verify and scatter kernels (4 per compute unit).
  * CRUM_PARAM_CHUNK_BYTES / CRUM_PARAM_CHUNK_MAX_BYTES: scanned bytes of the
- *   first and of the largest chunk when the snapshot is pipelined by chunks
- *   (128 MiB / 4 GiB); chunks grow by CRUM_PARAM_CHUNK_GROWTH up to the maximum.
+ *   first and of the largest chunk when a snapshot with a host image is
+ *   pipelined by chunks (128 MiB / 4 GiB); chunks grow by CRUM_PARAM_CHUNK_GROWTH up to the maximum.
  * CRUM_PARAM_EAGER: 1 pipelines the snapshot by chunks whenever the staging
  *   and host capacities hold an image with every page dirty (so ENOSPC is
  *   impossible); 0 always runs the whole diff first (1).
@@ -444,8 +444,9 @@ void crum_server_destroy(crum_server* server);
  *   direct order off (0: every image is drained by hipMemcpyAsync).
  * CRUM_PARAM_CHUNK_GROWTH: factor, 2..16, by which successive pipelined
  *   chunks and plan groups grow, up to their maximum (4).
- * CRUM_PARAM_PACK_NT_STORE: 1 writes the image with non-temporal stores in
- *   the pack kernel (0).
+ * CRUM_PARAM_PACK_NT_STORE: 1 always writes pages (image and shadows) with
+ *   non-temporal stores; 0 does so only for images of more than 256 MiB scanned
+ *   that stay on the device and restores that write as much (0).
  * CRUM_PARAM_PACK_NT_LOAD: 1 reads the pages in the pack and verify kernels
  *   with non-temporal loads, which are not kept in the caches (1).
  * CRUM_PARAM_DIFF_GROUP: 4 KiB diff units per wave of the diff kernel, 1, 2

@@ -101,7 +101,7 @@ struct CrcTables {
     uint32_t mf[16][64][4];
 };
 
-enum PackMode { kModePack = 0, kModeVerify = 1 };
+enum PackMode { kModePack = 0, kModeVerify = 1, kModeScatter = 2 };
 
 struct LaunchShape {
     int diff_blocks;   // persistent grid of the diff kernel (256-thread blocks)
@@ -152,12 +152,13 @@ hipError_t launch_list(const uint64_t* bitmap, const uint32_t* prefix, uint64_t 
 // whose flags bit 0 is set.  unit_flags (pack only, may be null): the diff's
 // per-unit flags of the same page space (4-byte aligned, padded to whole
 // words); units flagged clean are then read from the shadow.  nt: kPackNt*
-// bits.
+// bits.  update_shadow (scatter only): pages go to the shadows as well.
 hipError_t launch_pack(int mode, const DevRegion* regs, uint32_t n_regs, const DevRequest* reqs,
                        const DevReqOut* out, const uint32_t* list, SlotRange range,
                        uint32_t np_shift, uint32_t piece_shift, const uint8_t* unit_flags,
                        uint8_t* staging, uint32_t* crc_out, uint32_t* partials,
-                       const CrcTables* tabs, DevGlobal* glob, int blocks, hipStream_t s, int nt);
+                       const CrcTables* tabs, DevGlobal* glob, int blocks, hipStream_t s, int nt,
+                       int update_shadow = 0);
 hipError_t launch_finalize(int mode, const DevRegion* regs, uint32_t n_regs,
                            const DevRequest* reqs, const DevReqOut* out, const uint32_t* list,
                            SlotRange range, uint32_t np_shift, uint32_t piece_shift,
@@ -184,11 +185,6 @@ hipError_t launch_plan_status(const DevReqOut* out, uint32_t n, uint8_t* dst, hi
 hipError_t launch_restore_check(const DevRequest* reqs, uint32_t n_reqs, uint32_t blocks,
                                 DevReqOut* out, const uint8_t* staging, const CrcTables* tabs,
                                 DevGlobal* glob, hipStream_t s);
-hipError_t launch_scatter(const DevRegion* regs, uint32_t n_regs, const DevRequest* reqs,
-                          const DevReqOut* out, const uint32_t* list, uint64_t n_slots,
-                          uint32_t np_shift, uint32_t piece_shift, const uint8_t* staging,
-                          int update_shadow,
-                          const DevGlobal* glob, int blocks, hipStream_t s);
 hipError_t launch_restore_finish(DevReqOut* out, uint32_t n_reqs, DevGlobal* glob,
                                  hipStream_t s);
 

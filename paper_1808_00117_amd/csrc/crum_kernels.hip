@@ -547,8 +547,35 @@ hipError_t launch_diff(const DevRegion* regs, uint32_t n_regs, uint64_t u0, uint
 
 // ------------------------------------------------------------ k_bitmap
 
+// OR of the n = 2^n_shift flag bytes at f: 16 or 4 bytes at a time where they
+// are aligned (a page's flags start at a multiple of n, unless smaller pages
+// of another request of a plan come before it).
+__device__ __forceinline__ bool any_flag(const uint8_t* __restrict__ f, uint32_t n_shift)
+{
+    const uint32_t n = 1u << n_shift;
+    uint32_t acc = 0;
+    if (n >= 16 && ((uintptr_t)f & 15u) == 0) {
+        const gcv4 v = (gcv4)f;
+        u32x4 o = v[0];
+#pragma unroll 8
+        for (uint32_t i = 1; i < n / 16; ++i)
+            o |= v[i];
+        acc = o.x | o.y | o.z | o.w;
+    } else if (n >= 4 && ((uintptr_t)f & 3u) == 0) {
+        const gcu32 v = (gcu32)f;
+        for (uint32_t i = 0; i < n / 4; ++i)
+            acc |= v[i];
+    } else {
+        for (uint32_t i = 0; i < n; ++i)
+            acc |= f[i];
+    }
+    return acc != 0;
+}
+
 // One wave per bitmap word in [w0, w1): lane l owns global page 64w + l, ORs
-// its unit flags, and a ballot forms the word.
+// its unit flags (none are needed without a shadow: every page is dirty), and
+// a ballot forms the word.  Bound by latency; 2 MiB pages (128 flags each) took
+// 14-18 us a byte at a time and take 5.
 __global__ __launch_bounds__(256) void k_bitmap(const DevRegion* __restrict__ regs,
                                                 uint32_t n_regs, uint64_t w0, uint64_t w1,
                                                 const uint8_t* __restrict__ unit_flags,
@@ -567,11 +594,8 @@ __global__ __launch_bounds__(256) void k_bitmap(const DevRegion* __restrict__ re
     if (g >= R.first_page && g - R.first_page < np) {
         const uint64_t pi = g - R.first_page;
         const uint32_t upp_shift = R.page_shift - R.unit_shift;
-        const uint8_t* f = unit_flags + R.first_unit + (pi << upp_shift);
-        uint32_t acc = 0;
-        for (uint32_t i = 0; i < (1u << upp_shift); ++i)
-            acc |= f[i];
-        dirty = acc != 0;
+        dirty = R.shadow == nullptr ||
+                any_flag(unit_flags + R.first_unit + (pi << upp_shift), upp_shift);
     }
     const uint64_t m = __ballot(dirty);
     if (lane == 0)
@@ -788,9 +812,9 @@ __device__ __forceinline__ void slot_range(const SlotRange& sr, uint64_t* lo, ui
 // A work item of k_pack found to be a piece of a page: where its bytes are and
 // where they go (wave-uniform).
 struct Piece {
-    const uint8_t* src;   // current bytes (pack) or the packed page (verify)
+    const uint8_t* src;   // current bytes (pack) or the packed page
     uint8_t* shadow;      // the piece's shadow, null if the region has none
-    uint8_t* dst;         // pack: the piece's place in the image
+    uint8_t* dst;         // its place in the image (pack) or in the region (scatter)
     uint64_t unit;        // first diff unit of the piece
     uint32_t unit_shift;
     uint32_t batches;     // 4 KiB batches in the piece
@@ -811,7 +835,9 @@ __device__ __forceinline__ bool unit_dirty(const uint8_t* __restrict__ flags, ui
 // Work item = (slot, piece); pieces per slot = 2^np_shift for the launch.
 // Pack: copy the dirty page into the image's page area (and the shadow) and
 // write its CRC to crc_out[slot].  Verify: recompute the CRC of a packed page
-// of the image and compare with the image's CRC array.
+// of the image and compare with the image's CRC array.  Scatter: copy the
+// packed page to its page (and, with update_shadow, its shadow), unless a check
+// before found the image bad.
 //
 // A wave works through its items as one stream of 4 KiB batches, whichever
 // page they belong to: the loads of the next batch are in flight while the
@@ -836,10 +862,14 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
                                               uint32_t* __restrict__ crc_out,
                                               uint32_t* __restrict__ partials,
                                               const CrcTables* __restrict__ tabs,
-                                              DevGlobal* __restrict__ glob)
+                                              DevGlobal* __restrict__ glob,
+                                              uint32_t update_shadow)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t lds[kPackLdsWords];
-    if (MODE == kModeVerify && glob->fmt_bad)
+    constexpr bool CRC = MODE != kModeScatter;
+    __shared__ __attribute__((aligned(16))) uint32_t lds[CRC ? kPackLdsWords : 4];
+    if (MODE != kModePack && glob->fmt_bad)
+        return;
+    if (MODE == kModeScatter && glob->crc_bad != kNoBad)
         return;
     uint64_t slot0, slot1;
     slot_range(sr, &slot0, &slot1);
@@ -851,8 +881,10 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t half = lane >> 5;
     CrcMatrix mat;
-    load_crc_matrix(mat, tabs, lane);
-    load_pack_tables(lds, tabs);
+    if (CRC) {
+        load_crc_matrix(mat, tabs, lane);
+        load_pack_tables(lds, tabs);
+    }
     const uint64_t wave =
         (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t n_waves = (uint64_t)gridDim.x * 4;
@@ -860,7 +892,7 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
     uint64_t r_lo = 1, r_hi = 0;
 
     // the first item at or after `item` (this wave's items) that is a piece
-    auto find = [&](uint64_t item, Piece& p) -> bool {
+    auto find = [&](uint64_t item, Piece& p) __attribute__((always_inline)) -> bool {
         for (; item < n_items; item += n_waves) {
             const uint64_t k = slot0 + (item >> np_shift);
             const uint32_t piece = (uint32_t)(item & ((1ull << np_shift) - 1));
@@ -887,15 +919,24 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
             p.slot = k;
             p.region = r;
             p.batches = 1u << (pb_shift - 12);
-            p.dst = packed;
+            p.src = packed;
+            p.dst = nullptr;
+            p.shadow = nullptr;
+            p.update = 0;
+            p.unit = 0;
+            p.unit_shift = 0;
+            if (MODE == kModeScatter) {
+                p.dst = const_cast<uint8_t*>(R.cur) + off;
+                p.shadow = R.shadow ? R.shadow + off : nullptr;
+                p.update = update_shadow;
+            }
             if (MODE == kModePack) {
                 p.src = R.cur + off;
+                p.dst = packed;
                 p.shadow = R.shadow ? R.shadow + off : nullptr;
                 p.update = R.flags & 1u;
                 p.unit_shift = R.unit_shift;
                 p.unit = R.first_unit + (off >> R.unit_shift);
-            } else {
-                p.src = packed;
             }
             return true;
         }
@@ -915,6 +956,16 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
             w[t] = NT_LOAD ? __builtin_nontemporal_load(a + 64 * t) : a[64 * t];
     };
 
+    auto store = [&](gv4 o, const u32x4* w) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if (NT_STORE)
+                __builtin_nontemporal_store(w[t], o + 64 * t);
+            else
+                o[64 * t] = w[t];
+        }
+    };
+
     Piece cur;
     if (!find(wave, cur))
         return;
@@ -923,7 +974,7 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
     u32x4 wa[4], wb[4];
     load(cur, 0, d, wa);
     // one batch: issue the next one's loads into nx, then finish w
-    auto step = [&](u32x4* w, u32x4* nx) -> bool {
+    auto step = [&](u32x4* w, u32x4* nx) __attribute__((always_inline)) -> bool {
         Piece next = cur;
         uint32_t nb = b + 1;
         bool more = true, nd = true;
@@ -935,25 +986,16 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
             nd = MODE == kModePack ? dirty(next, nb) : true;
             load(next, nb, nd, nx);
         }
-        if (MODE == kModePack) {
-            const gv4 o = (gv4)(cur.dst + (b << 12)) + lane;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                if (NT_STORE)
-                    __builtin_nontemporal_store(w[t], o + 64 * t);
-                else
-                    o[64 * t] = w[t];
-            }
-            if (cur.update && cur.shadow && d) {
-                const gv4 h = (gv4)(cur.shadow + (b << 12)) + lane;
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    h[64 * t] = w[t];
-            }
+        if (MODE != kModeVerify) {
+            store((gv4)(cur.dst + (b << 12)) + lane, w);
+            if (cur.update && cur.shadow && d)
+                store((gv4)(cur.shadow + (b << 12)) + lane, w);
         }
-        const uint32_t f = fold_4k(mat, w, half);
-        s = b ? shift_4k(lds, s) ^ f : f;
-        if (b + 1 == cur.batches) {
+        if (CRC) {
+            const uint32_t f = fold_4k(mat, w, half);
+            s = b ? shift_4k(lds, s) ^ f : f;
+        }
+        if (CRC && b + 1 == cur.batches) {
             const uint32_t raw = columns_crc(lds, s, lane);
             const DevRegion& R = regs[cur.region];
             const uint32_t ps = R.page_shift;
@@ -990,7 +1032,7 @@ hipError_t launch_pack(int mode, const DevRegion* regs, uint32_t n_regs, const D
                        uint32_t np_shift, uint32_t piece_shift, const uint8_t* unit_flags,
                        uint8_t* staging, uint32_t* crc_out, uint32_t* partials,
                        const CrcTables* tabs, DevGlobal* glob, int blocks, hipStream_t s,
-                       int nt)
+                       int nt, int update_shadow)
 {
     const uint64_t max_items = range.max_slots << np_shift;
     if (max_items == 0)
@@ -1002,30 +1044,37 @@ hipError_t launch_pack(int mode, const DevRegion* regs, uint32_t n_regs, const D
     const dim3 grid((unsigned)nb);
 #define CRUM_PACK(M, L, S, F)                                                                  \
     hipLaunchKernelGGL((k_pack<M, L, S>), grid, dim3(256), 0, s, regs, n_regs, reqs, out, list, \
-                       range, np_shift, piece_shift, F, staging, crc_out, partials, tabs, glob)
-    const bool ntl = (nt & kPackNtLoad) != 0, nts = (nt & kPackNtStore) != 0;
-    if (mode == kModeVerify) {
-        if (ntl)
+                       range, np_shift, piece_shift, F, staging, crc_out, partials, tabs, glob, \
+                       (uint32_t)update_shadow)
+#define CRUM_PACK_NT(M, F)                                                                     \
+    switch (nt & (kPackNtLoad | kPackNtStore)) {                                               \
+    case 0: CRUM_PACK(M, false, false, F); break;                                              \
+    case kPackNtStore: CRUM_PACK(M, false, true, F); break;                                    \
+    case kPackNtLoad: CRUM_PACK(M, true, false, F); break;                                     \
+    default: CRUM_PACK(M, true, true, F); break;                                               \
+    }
+    if (mode == kModeScatter) {
+        CRUM_PACK_NT(kModeScatter, nullptr);
+    } else if (mode == kModeVerify) {
+        if (nt & kPackNtLoad)
             CRUM_PACK(kModeVerify, true, false, nullptr);
         else
             CRUM_PACK(kModeVerify, false, false, nullptr);
-    } else if (ntl) {
-        if (nts)
-            CRUM_PACK(kModePack, true, true, unit_flags);
-        else
-            CRUM_PACK(kModePack, true, false, unit_flags);
     } else {
-        if (nts)
-            CRUM_PACK(kModePack, false, true, unit_flags);
-        else
-            CRUM_PACK(kModePack, false, false, unit_flags);
+        CRUM_PACK_NT(kModePack, unit_flags);
     }
+#undef CRUM_PACK_NT
 #undef CRUM_PACK
     return hipGetLastError();
 }
 
-// One thread per slot: combine the slot's piece CRCs (pages above 64 KiB).
-// partials are indexed by the item of the matching pack launch.
+// Combines the piece CRCs of the pages larger than one piece; partials are
+// indexed by the item of the matching pack launch.  L = min(64, 2^np_shift)
+// lanes per slot: lane l folds the pieces l, l + 64, ... (Horner, a shift by 64
+// pieces per step), then pairs of neighbours, of pairs, ... combine by
+// crc(A||B) = crc(A) x^(8|B|) + crc(B).  A chain of dependent products, so it
+// is bound by latency: one thread per slot took 30 us for pages of 128 pieces,
+// this takes 5.
 template <int MODE>
 __global__ __launch_bounds__(256) void k_finalize(const DevRegion* __restrict__ regs,
                                                   uint32_t n_regs,
@@ -1044,33 +1093,49 @@ __global__ __launch_bounds__(256) void k_finalize(const DevRegion* __restrict__ 
         return;
     uint64_t slot0, slot1;
     slot_range(sr, &slot0, &slot1);
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= slot1 - slot0)
-        return;
+    const uint32_t l_shift = np_shift < 6 ? np_shift : 6;
+    const uint64_t i = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> l_shift;
+    const uint32_t l = threadIdx.x & ((1u << l_shift) - 1);
+    // a slot's lanes stay together through the shuffles: none leaves early
     const uint64_t k = slot0 + i;
-    const uint64_t g = list[k];
-    const DevRegion& R = regs[find_region<3>(regs, n_regs, g)];
-    if (g < R.first_page || g - R.first_page >= (R.len >> R.page_shift))
+    uint32_t e = 0;  // log2 of the slot's pieces, 0: nothing to combine
+    uint32_t r = 0;
+    if (i < slot1 - slot0) {
+        const uint64_t g = list[k];
+        r = find_region<3>(regs, n_regs, g);
+        const DevRegion& R = regs[r];
+        if (g >= R.first_page && g - R.first_page < (R.len >> R.page_shift) &&
+            R.page_shift > piece_shift && !(MODE == kModePack && out[R.req].code != 0))
+            e = R.page_shift - piece_shift;
+    }
+    const uint32_t np = 1u << e;
+    uint32_t s = 0;
+    if (e != 0 && l < np) {
+        const uint32_t* p = partials + (i << np_shift) + l;
+        const uint32_t K = tabs->xp[piece_shift + 6];  // x^(8 * 64 pieces)
+        s = p[0];
+        for (uint32_t j = 64; j < np; j += 64)
+            s = gf2_mulmod(s, K) ^ p[j];
+    }
+    for (uint32_t v = 0; v < l_shift; ++v) {
+        const uint32_t other = (uint32_t)__shfl_xor((int)s, 1 << v);
+        if (v < e) {
+            const bool upper = (l >> v) & 1u;
+            s = gf2_mulmod(upper ? other : s, tabs->xp[piece_shift + v]) ^ (upper ? s : other);
+        }
+    }
+    if (e == 0 || l != 0)
         return;
-    const uint32_t ps = R.page_shift;
-    if (ps <= piece_shift)
-        return;
+    const DevRegion& R = regs[r];
     const DevRequest& Q = reqs[R.req];
     const DevReqOut& O = out[R.req];
-    if (MODE == kModePack && O.code != 0)
-        return;
-    const uint32_t np = 1u << (ps - piece_shift);
-    const uint32_t K = tabs->xp[piece_shift];  // x^(8 * piece bytes)
-    uint32_t s = 0;
-    for (uint32_t j = 0; j < np; ++j)
-        s = gf2_mulmod(s, K) ^ partials[(i << np_shift) + j];
     const uint32_t crc = s ^ Q.init_fix;
     if (MODE == kModePack) {
         crc_out[k] = crc;
     } else {
         const uint64_t local = k - O.slot_base;
         const uint32_t* img_crc = reinterpret_cast<const uint32_t*>(
-            staging + O.img_base + Q.data_off + (O.n_dirty << ps));
+            staging + O.img_base + Q.data_off + (O.n_dirty << R.page_shift));
         if (crc != img_crc[local])
             atomicMin(&glob->crc_bad, (uint32_t)local);
     }
@@ -1084,7 +1149,8 @@ hipError_t launch_finalize(int mode, const DevRegion* regs, uint32_t n_regs,
 {
     if (range.max_slots == 0 || np_shift == 0)
         return hipSuccess;
-    const unsigned nb = (unsigned)((range.max_slots + 255) / 256);
+    const uint32_t l_shift = np_shift < 6 ? np_shift : 6;
+    const unsigned nb = (unsigned)(((range.max_slots << l_shift) + 255) / 256);
     if (mode == kModePack)
         hipLaunchKernelGGL(k_finalize<kModePack>, dim3(nb), dim3(256), 0, s, regs, n_regs, reqs,
                            out, list, range, np_shift, piece_shift, partials, crc_out, staging,
@@ -1619,85 +1685,6 @@ hipError_t launch_restore_check(const DevRequest* reqs, uint32_t n_reqs, uint32_
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_restore_check, dim3(n_reqs * blocks), dim3(256), 0, s, reqs, out,
                        staging, blocks, tabs, glob);
-    return hipGetLastError();
-}
-
-// Wave per (slot, piece): packed page -> its page (and shadow).
-__global__ __launch_bounds__(256) void k_scatter(const DevRegion* __restrict__ regs,
-                                                 uint32_t n_regs,
-                                                 const DevRequest* __restrict__ reqs,
-                                                 const DevReqOut* __restrict__ out,
-                                                 const uint32_t* __restrict__ list,
-                                                 uint64_t n_items, uint32_t np_shift,
-                                                 uint32_t piece_shift,
-                                                 const uint8_t* __restrict__ staging,
-                                                 int update_shadow,
-                                                 const DevGlobal* __restrict__ glob)
-{
-    if (glob->fmt_bad || glob->crc_bad != kNoBad)
-        return;
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t wave = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t n_waves = (uint64_t)gridDim.x * 4;
-    uint32_t r = 0;
-    uint64_t r_lo = 1, r_hi = 0;
-    for (uint64_t item = wave; item < n_items; item += n_waves) {
-        const uint64_t k = item >> np_shift;
-        const uint32_t piece = (uint32_t)(item & ((1ull << np_shift) - 1));
-        const uint64_t g = list[k];
-        if (g < r_lo || g >= r_hi) {
-            r = find_region<3>(regs, n_regs, g);
-            r_lo = regs[r].first_page;
-            r_hi = r_lo + (regs[r].len >> regs[r].page_shift);
-        }
-        const DevRegion& R = regs[r];
-        if (g < r_lo || g >= r_hi)
-            continue;
-        const DevRequest& Q = reqs[R.req];
-        const DevReqOut& O = out[R.req];
-        const uint32_t ps = R.page_shift;
-        const uint32_t pb_shift = ps < piece_shift ? ps : piece_shift;
-        if (piece >= (1u << (ps - pb_shift)))
-            continue;
-        const uint64_t page_off = (g - R.first_page) << ps;
-        const uint64_t piece_off = (uint64_t)piece << pb_shift;
-        const gcv4 src =
-            (gcv4)(staging + O.img_base + Q.data_off + ((k - O.slot_base) << ps) + piece_off);
-        const gv4 dst = (gv4)(R.cur + page_off + piece_off);
-        const gv4 sh = (update_shadow && R.shadow) ? (gv4)(R.shadow + page_off + piece_off)
-                                                   : nullptr;
-        const uint32_t n16 = 1u << (pb_shift - 4);
-        for (uint32_t i = lane; i < n16; i += 64 * 4) {
-            u32x4 w[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (i + 64 * u < n16)
-                    w[u] = src[i + 64 * u];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (i + 64 * u < n16) {
-                    dst[i + 64 * u] = w[u];
-                    if (sh)
-                        sh[i + 64 * u] = w[u];
-                }
-        }
-    }
-}
-
-hipError_t launch_scatter(const DevRegion* regs, uint32_t n_regs, const DevRequest* reqs,
-                             const DevReqOut* out, const uint32_t* list, uint64_t n_slots,
-                             uint32_t np_shift, uint32_t piece_shift, const uint8_t* staging,
-                             int update_shadow, const DevGlobal* glob, int blocks, hipStream_t s)
-{
-    if (n_slots == 0)
-        return hipSuccess;
-    if (piece_shift < kPieceShiftMin || piece_shift > kPieceShift)
-        return hipErrorInvalidValue;
-    const uint64_t n_items = n_slots << np_shift;
-    const uint64_t need = (n_items + 3) / 4;
-    const uint64_t nb = need < (uint64_t)blocks ? need : (uint64_t)blocks;
-    hipLaunchKernelGGL(k_scatter, dim3((unsigned)nb), dim3(256), 0, s, regs, n_regs, reqs, out,
-                       list, n_items, np_shift, piece_shift, staging, update_shadow, glob);
     return hipGetLastError();
 }
 

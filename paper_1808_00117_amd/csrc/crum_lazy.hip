@@ -167,10 +167,9 @@ hipError_t run_kernels(crum_lazy* z, uint64_t k0, uint64_t k1, uint8_t* src, hip
         if (e != hipSuccess)
             return e;
     }
-    // the scatter numbers slots from the list pointer and finds a slot's
-    // packed page from the source pointer, so both start at slot k0
-    return launch_scatter(regs, nr, req, out, list + k0, n, nps, pcs, src + (k0 << ps),
-                          (z->flags & CRUM_UPDATE_SHADOW) ? 1 : 0, glob, z->pack_blocks, s);
+    return launch_pack(kModeScatter, regs, nr, req, out, list, SlotRange{k0, k1, nullptr, 0, n},
+                       nps, pcs, nullptr, src, crcs, partials, ctx_tables(z->ctx), glob,
+                       z->pack_blocks, s, 0, (z->flags & CRUM_UPDATE_SHADOW) ? 1 : 0);
 }
 
 // Fetch every absent image page of global pages [g0, g1): the copies of the

@@ -331,7 +331,7 @@ int crum_plan_create(crum_ctx* c, const crum_request* reqs, uint32_t n_reqs, voi
         if (e == hipSuccess)
             e = launch_pack(kModePack, d_regs, p->n_regs, d_reqs, d_out, d_list, sr, np_shift,
                             pc_shift, d_flags, p->staging, d_crcs, d_part, tabs, d_glob,
-                            shape.pack_blocks, s, ctx_pack_flags(c));
+                            shape.pack_blocks, s, ctx_pack_flags(c, h_images ? 0 : all_bytes));
         if (e == hipSuccess)
             e = launch_finalize(kModePack, d_regs, p->n_regs, d_reqs, d_out, d_list, sr, np_shift,
                                 pc_shift, d_part, d_crcs, p->staging, d_glob, tabs, s);
