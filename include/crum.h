@@ -413,9 +413,11 @@ void crum_server_destroy(crum_server* server);
 
 /* Launch and pipeline parameters of a context (defaults in parentheses).
  * They change speed only: every image is the same whatever their values.
- * CRUM_PARAM_DIFF_BLOCKS: persistent grid of the diff kernel, in 256-thread
- *   workgroups (8 per compute unit).  CRUM_PARAM_PACK_BLOCKS: grid of the
- *   pack, verify and scatter kernels (4 per compute unit).
+ * CRUM_PARAM_DIFF_BLOCKS: largest grid of the diff kernel, in 256-thread
+ *   workgroups, each striding over its share of the units (8 per compute unit;
+ *   at this default only launches with a candidate set are limited).
+ *   CRUM_PARAM_PACK_BLOCKS: grid of the pack, verify and scatter kernels (4 per
+ *   compute unit).
  * CRUM_PARAM_CHUNK_BYTES / CRUM_PARAM_CHUNK_MAX_BYTES: scanned bytes of the
  *   first and of the largest chunk when a snapshot with a host image is
  *   pipelined by chunks (128 MiB / 4 GiB); chunks grow by CRUM_PARAM_CHUNK_GROWTH up to the maximum.

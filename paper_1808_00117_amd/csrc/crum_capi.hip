@@ -671,6 +671,8 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
     const uint32_t np_shift = ps > pc_shift ? ps - pc_shift : 0;
     const uint32_t us = std::min<uint32_t>(ps, c->unit_shift_max);
     const int pack_flags = ctx_pack_flags(c, h_image ? 0 : G << ps);
+    const int diff_blocks = ctx_diff_blocks(c, h_cand != nullptr);
+    const bool need_diff = any_shadow(regions, n_regions);
     std::vector<DevRegion> dregs(std::max<uint32_t>(1, n_regions));
     uint64_t n_pages = 0, n_units = 0;
     flatten_regions(regions, n_regions, ps, c->unit_shift_max,
@@ -730,9 +732,9 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
     if (direct) {
         // ---- direct order: diff, scan (with the capacity check), list, then
         // pack and header into the host image; slot counts stay on the device
-        {
+        if (need_diff) {
             Span sp(c, kTDiff, stream);
-            CRUM_TRY(launch_diff(d_regs, n_regions, 0, n_units, d_flags, c->shape.diff_blocks,
+            CRUM_TRY(launch_diff(d_regs, n_regions, 0, n_units, d_flags, diff_blocks,
                                  c->diff_nt, c->diff_prio, stream, d_cand, nullptr,
                                  ctx_diff_group(c, us)));
         }
@@ -771,10 +773,10 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
         for (size_t ci = 0; ci < n_chunks; ++ci) {
             const uint64_t g0 = cuts[ci], g1 = cuts[ci + 1];
             const uint64_t w0 = g0 / 64, w1 = (g1 + 63) / 64;
-            {
+            if (need_diff) {
                 Span sp(c, kTDiff, stream);
                 CRUM_TRY(launch_diff(d_regs, n_regions, g0 << (ps - us), g1 << (ps - us), d_flags,
-                                     c->shape.diff_blocks, c->diff_nt, c->diff_prio, stream,
+                                     diff_blocks, c->diff_nt, c->diff_prio, stream,
                                      d_cand, nullptr,
                                      ctx_diff_group(c, us)));
             }
@@ -828,9 +830,9 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
         image_bytes = data_off + (D << ps) + round_up(4 * D, 8);
     } else {
         // ---- checked order: whole diff, scan with the capacity check, readback
-        {
+        if (need_diff) {
             Span sp(c, kTDiff, stream);
-            CRUM_TRY(launch_diff(d_regs, n_regions, 0, n_units, d_flags, c->shape.diff_blocks,
+            CRUM_TRY(launch_diff(d_regs, n_regions, 0, n_units, d_flags, diff_blocks,
                                  c->diff_nt, c->diff_prio, stream, d_cand, nullptr,
                                  ctx_diff_group(c, us)));
         }

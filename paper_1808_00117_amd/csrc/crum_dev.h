@@ -124,6 +124,7 @@ const CrcTables& crc_tables();  // the constants, in host memory
 // stamp (may be null): two words, the wall clock at the launch's start and
 // the latest end of its workgroups (stamp[1] must start below any clock
 // value, e.g. zeroed once).
+// blocks: largest grid, 0 for as many as the units need.
 // group 2 or 4: each wave takes that many consecutive units (as many 4 KiB
 // units of a region read as one span); other values: one unit per wave.
 hipError_t launch_diff(const DevRegion* regs, uint32_t n_regs, uint64_t u0, uint64_t u1,

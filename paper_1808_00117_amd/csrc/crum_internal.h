@@ -208,6 +208,24 @@ inline void ctx_add_timing(crum_ctx* c, int cls, double ms)
 }
 inline uint32_t ctx_chunk_growth(const crum_ctx* c) { return c->chunk_growth; }
 inline int ctx_pack_nt(const crum_ctx* c) { return c->pack_nt ? 1 : 0; }
+// Grid limit of a diff launch (0: none).  By default every wave of a launch
+// takes one unit (or group) and the dispatcher balances them: 8 GiB in 64 KiB
+// pages 2505 us persistent (8 workgroups per compute unit), 2440 this way, 1.5
+// GiB of 4 KiB pages 487 and 470.  A candidate set leaves most units unread, and
+// those are cheaper to stride over than to dispatch.
+inline int ctx_diff_blocks(const crum_ctx* c, bool cand)
+{
+    return c->shape.diff_blocks == c->cus * 8 && !cand ? 0 : c->shape.diff_blocks;
+}
+// Whether a region table needs the diff: units of regions without a shadow
+// are dirty unread, and their flags are not looked at.
+inline bool any_shadow(const crum_region* regs, uint32_t n)
+{
+    for (uint32_t i = 0; i < n; ++i)
+        if (regs[i].shadow)
+            return true;
+    return false;
+}
 // Units per wave of a diff launch whose smallest unit is 1 << min_us bytes:
 // the context's group for 4 KiB units, else one.
 inline int ctx_diff_group(const crum_ctx* c, uint32_t min_us)

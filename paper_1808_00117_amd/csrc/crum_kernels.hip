@@ -522,7 +522,9 @@ hipError_t launch_diff(const DevRegion* regs, uint32_t n_regs, uint64_t u0, uint
     if (group != 2 && group != 4)
         group = 1;
     const uint64_t need = ((u1 - u0 + group - 1) / group + 3) / 4;
-    const uint64_t nb = need < (uint64_t)blocks ? need : (uint64_t)blocks;
+    const uint64_t nb = blocks <= 0 || need < (uint64_t)blocks ? need : (uint64_t)blocks;
+    if (nb > 0x7FFFFFFFull)
+        return hipErrorInvalidValue;
 #define CRUM_DIFF(NTV, GV)                                                                   \
     hipLaunchKernelGGL((k_diff<NTV, GV>), dim3((unsigned)nb), dim3(256), 0, s, regs, n_regs, \
                        u0, u1, unit_flags, (uint32_t)prio, cand, stamp)

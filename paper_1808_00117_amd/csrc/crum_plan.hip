@@ -315,7 +315,7 @@ int crum_plan_create(crum_ctx* c, const crum_request* reqs, uint32_t n_reqs, voi
         if (gi == 0)
             e = launch_plan_init(d_glob, s);
         if (e == hipSuccess)
-            e = launch_diff(d_regs, p->n_regs, u0, u1, d_flags, shape.diff_blocks,
+            e = launch_diff(d_regs, p->n_regs, u0, u1, d_flags, ctx_diff_blocks(c, false),
                             ctx_diff_nt(c), ctx_diff_prio(c), s, nullptr,
                             p->d_stamp ? p->d_stamp + 2 * gi : nullptr,
                             ctx_diff_group(c, min_us));
