@@ -694,6 +694,7 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
     rq.n_pages = G;
     rq.first_region = 0;
     rq.n_regions = n_regions;
+    rq.flags = any_shadow(regions, n_regions) ? kReqShadow : 0;
     rq.data_off = data_off;
     rq.seq = seq;
     rq.page_shift = ps;
@@ -1021,6 +1022,7 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
     rq.n_words = W;
     rq.n_pages = G;
     rq.n_regions = n_regions;
+    rq.flags = any_shadow(regions, n_regions) ? kReqShadow : 0;
     rq.data_off = data_off;
     rq.seq = seq;
     rq.page_shift = ps;

@@ -40,13 +40,16 @@ struct DevRegion {
 };
 static_assert(sizeof(DevRegion) == 64, "DevRegion layout");
 
+constexpr uint32_t kReqShadow = 1;  // some region has a shadow
+
 // One request (one image) of a launch.
 struct DevRequest {
     uint64_t first_word;   // first bitmap word (global)
     uint64_t n_words;
     uint64_t n_pages;      // pages of the request (unpadded G)
     uint64_t first_region; // index into the region table
-    uint64_t n_regions;
+    uint32_t n_regions;
+    uint32_t flags;        // kReq* bits
     uint64_t data_off;     // image prefix bytes
     uint64_t seq;
     uint32_t page_shift;
@@ -84,19 +87,18 @@ struct DevGlobal {
 };
 static_assert(sizeof(DevGlobal) == 64, "DevGlobal layout");
 
-// CRC lookup tables held in device memory and staged into LDS:
-//   t[k][b]    = b * x^(8(k+1))        (slicing-by-16 for one 16-byte word)
-//   z[j][i][b] = (b << 8i) * x^(8 L_j)  (shift of a 32-bit state by L_j bytes)
-// with L_j = 32, 64, 128, 256, 512, 1024 for j = 0..5.
-// t[k][b] = b * x^(8(k+1)) (slicing by 16); z[j][i][b] = (b << 8i) * x^(8 L_j)
-// for L = 32, 64, 128, 256, 512, 1024, 4096 bytes; xp[i] = x^(8 * 2^i).
+// CRC constants held in device memory:
+// z4k[i][b] = (b << 8i) * x^(8 * 4096): byte i of a state carried through 4 KiB
+// of zeros (staged into LDS); xp[i] = x^(8 * 2^i); xb[k][i] = x^(8 * 4096 *
+// 256^k * i); xr[i] = x^(8 * 4i).
 // mf[4t + p][l]: lane l's FP4 operand of the pack's CRC matrix for 1 KiB step
 // t of a 4 KiB batch and bit plane p; col[k][n][j] = (n << 4k) * x^(128 (31 - j)):
-// nibble k of column j's state carried past the columns after it.
+// nibble k of column j's state carried past the columns after it (LDS).
 struct CrcTables {
-    uint32_t t[16][256];
-    uint32_t z[7][4][256];
+    uint32_t z4k[4][256];
     uint32_t xp[64];
+    uint32_t xb[3][256];
+    uint32_t xr[1024];
     uint32_t col[8][16][32];
     uint32_t mf[16][64][4];
 };

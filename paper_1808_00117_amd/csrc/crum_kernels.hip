@@ -26,11 +26,10 @@
 // through the matrix cores (k_pack): a raw CRC is linear over GF(2), so the 32
 // CRC bits of a 4 KiB batch are a 32 x 32768 bit matrix times its bits, and
 // the FP4 matrix instruction counts, per CRC bit, the set bits that reach it;
-// the count's parity is the bit.  See fold_4k.  The header and image-check
-// kernels work on short messages with byte tables in LDS (slicing by 16, a
-// Horner step and a butterfly over lanes; see wg_crc_steps).  Pieces of one
-// page combine by a shift by the piece length; the standard CRC adds
-// crc_init_fix(page bytes).
+// the count's parity is the bit.  See fold_4k.  The header's two messages (the
+// prefix and the CRC array) go the same way.  Pieces of one page, and shares of
+// one message, combine by a shift by the bytes that follow them; the standard
+// CRC adds crc_init_fix(page bytes).
 #include "crum_dev.h"
 #include "gf2.h"
 
@@ -57,20 +56,22 @@ typedef uint32_t __attribute__((address_space(1)))* gu32;
 
 static void fill_crc_tables(CrcTables* h)
 {
-    for (int k = 0; k < 16; ++k) {
-        const uint32_t xk = gf2_xpow8n((uint64_t)k + 1);
+    const uint32_t x4k = gf2_xpow8n(4096);
+    for (int i = 0; i < 4; ++i)
         for (int b = 0; b < 256; ++b)
-            h->t[k][b] = gf2_mulmod((uint32_t)b, xk);
-    }
-    const uint64_t L[7] = {32, 64, 128, 256, 512, 1024, 4096};
-    for (int j = 0; j < 7; ++j) {
-        const uint32_t xl = gf2_xpow8n(L[j]);
-        for (int i = 0; i < 4; ++i)
-            for (int b = 0; b < 256; ++b)
-                h->z[j][i][b] = gf2_mulmod((uint32_t)b << (8 * i), xl);
-    }
+            h->z4k[i][b] = gf2_mulmod((uint32_t)b << (8 * i), x4k);
     for (int i = 0; i < 64; ++i)
         h->xp[i] = gf2_xpow8n(1ull << i);
+    const uint32_t x4 = gf2_xpow8n(4);
+    h->xr[0] = 0x80000000u;  // x^0
+    for (int i = 1; i < 1024; ++i)
+        h->xr[i] = gf2_mulmod(h->xr[i - 1], x4);
+    for (int k = 0; k < 3; ++k) {
+        const uint32_t x = gf2_xpow8n(4096ull << (8 * k));
+        h->xb[k][0] = 0x80000000u;
+        for (int i = 1; i < 256; ++i)
+            h->xb[k][i] = gf2_mulmod(h->xb[k][i - 1], x);
+    }
     // fold_4k's matrix: the CRC bit of matrix row r, and what each data bit adds
     // to it (see there for the layout)
     static const uint32_t unit[4] = {4, 2, 1, 4};  // FP4 2.0, 1.0, 0.5, 2.0
@@ -108,15 +109,10 @@ const CrcTables& crc_tables()
     return *t;
 }
 
-// LDS layout of the header and restore-check kernels (words): the slicing
-// tables, then all seven shift levels z[0..6] (44 KiB), as in CrcTables.
-constexpr int kSliceWords = 16 * 256;                      // 16 KiB
-constexpr int kAllTabWords = kSliceWords + 7 * 4 * 256;    // 44 KiB
-
-// LDS layout of the pack and verify kernels (words): the column tables (col),
-// then the shift-by-4-KiB byte tables (z[6]); 20 KiB.
+// LDS layout of the kernels that compute CRCs (words): the column tables (col),
+// then the shift-by-4-KiB byte tables (z4k); 20 KiB.
 constexpr int kColWords = 8 * 16 * 32;
-constexpr int kPackLdsWords = kColWords + 4 * 256;
+constexpr int kCrcLdsWords = kColWords + 4 * 256;
 
 // Every kernel of this file runs 256-thread workgroups.
 constexpr int kBlock = 256;
@@ -149,45 +145,10 @@ __device__ __forceinline__ void stage_words(uint32_t* __restrict__ dst,
     }
 }
 
-__device__ __forceinline__ void load_pack_tables(uint32_t* lds, const CrcTables* tabs)
+__device__ __forceinline__ void load_crc_tables(uint32_t* lds, const CrcTables* tabs)
 {
     stage_words<kColWords>(lds, &tabs->col[0][0][0]);
-    stage_words<4 * 256>(lds + kColWords, &tabs->z[6][0][0]);
-    __syncthreads();
-}
-
-// raw CRC of one 16-byte word (bytes b0..b15, b0 = low byte of w.x)
-__device__ __forceinline__ uint32_t word_crc(const uint32_t* __restrict__ T, uint4 w)
-{
-    return T[15 * 256 + (w.x & 255u)] ^ T[14 * 256 + ((w.x >> 8) & 255u)] ^
-           T[13 * 256 + ((w.x >> 16) & 255u)] ^ T[12 * 256 + (w.x >> 24)] ^
-           T[11 * 256 + (w.y & 255u)] ^ T[10 * 256 + ((w.y >> 8) & 255u)] ^
-           T[9 * 256 + ((w.y >> 16) & 255u)] ^ T[8 * 256 + (w.y >> 24)] ^
-           T[7 * 256 + (w.z & 255u)] ^ T[6 * 256 + ((w.z >> 8) & 255u)] ^
-           T[5 * 256 + ((w.z >> 16) & 255u)] ^ T[4 * 256 + (w.z >> 24)] ^
-           T[3 * 256 + (w.w & 255u)] ^ T[2 * 256 + ((w.w >> 8) & 255u)] ^
-           T[1 * 256 + ((w.w >> 16) & 255u)] ^ T[0 * 256 + (w.w >> 24)];
-}
-
-// state carried through 16 zero bytes: the first four slicing tables
-__device__ __forceinline__ uint32_t shift16(const uint32_t* __restrict__ T, uint32_t s)
-{
-    return T[15 * 256 + (s & 255u)] ^ T[14 * 256 + ((s >> 8) & 255u)] ^
-           T[13 * 256 + ((s >> 16) & 255u)] ^ T[12 * 256 + (s >> 24)];
-}
-
-// state carried through L_j zero bytes (Z points at z[j])
-__device__ __forceinline__ uint32_t shiftz(const uint32_t* __restrict__ Z, uint32_t s)
-{
-    return Z[s & 255u] ^ Z[256 + ((s >> 8) & 255u)] ^ Z[512 + ((s >> 16) & 255u)] ^
-           Z[768 + (s >> 24)];
-}
-
-// The slicing tables and all shift tables (t and z are contiguous in CrcTables).
-__device__ __forceinline__ void load_all_tables(uint32_t* lds, const CrcTables* tabs)
-{
-    static_assert(offsetof(CrcTables, z) == sizeof(uint32_t) * kSliceWords, "t then z");
-    stage_words<kAllTabWords>(lds, &tabs->t[0][0]);
+    stage_words<4 * 256>(lds + kColWords, &tabs->z4k[0][0]);
     __syncthreads();
 }
 
@@ -201,31 +162,6 @@ __device__ __forceinline__ uint32_t lds_at(const uint32_t* __restrict__ L, uint3
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
 {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
-}
-
-// Butterfly over the 64 lanes: afterwards every lane holds sum_l C_l*x^(128(63-l)).
-// T: the slicing tables; Z: z[0] of the shift tables (LDS or global memory).
-__device__ __forceinline__ uint32_t lane_combine_z(const uint32_t* __restrict__ T,
-                                                   const uint32_t* __restrict__ Z, uint32_t s,
-                                                   uint32_t lane)
-{
-#pragma unroll
-    for (int lvl = 0; lvl < 6; ++lvl) {
-        const uint32_t other = (uint32_t)__shfl_xor((int)s, 1 << lvl);
-        const bool upper = (lane >> lvl) & 1u;
-        const uint32_t left = upper ? other : s;
-        const uint32_t right = upper ? s : other;
-        const uint32_t sh = lvl == 0 ? shift16(T, left) : shiftz(Z + (lvl - 1) * 1024, left);
-        s = sh ^ right;
-    }
-    return s;
-}
-
-// The butterfly with all tables in LDS in the header layout.
-__device__ __forceinline__ uint32_t lane_combine(const uint32_t* __restrict__ lds, uint32_t s,
-                                                 uint32_t lane)
-{
-    return lane_combine_z(lds, lds + kSliceWords, s, lane);
 }
 
 // ------------------------------------------------------------ matrix-core CRC
@@ -288,7 +224,7 @@ __device__ __forceinline__ uint32_t fold_4k(const CrcMatrix& m, const u32x4* __r
     return half ? r & 0xFFFF0000u : r >> 16;
 }
 
-// The lane's state carried through 4 KiB of zeros (lds: the pack layout).
+// The lane's state carried through 4 KiB of zeros.
 __device__ __forceinline__ uint32_t shift_4k(const uint32_t* __restrict__ lds, uint32_t s)
 {
     return xor3(lds_at(lds, 4u * kColWords + ((s << 2) & 0x3FCu)),
@@ -868,7 +804,7 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
                                               uint32_t update_shadow)
 {
     constexpr bool CRC = MODE != kModeScatter;
-    __shared__ __attribute__((aligned(16))) uint32_t lds[CRC ? kPackLdsWords : 4];
+    __shared__ __attribute__((aligned(16))) uint32_t lds[CRC ? kCrcLdsWords : 4];
     if (MODE != kModePack && glob->fmt_bad)
         return;
     if (MODE == kModeScatter && glob->crc_bad != kNoBad)
@@ -885,7 +821,7 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
     CrcMatrix mat;
     if (CRC) {
         load_crc_matrix(mat, tabs, lane);
-        load_pack_tables(lds, tabs);
+        load_crc_tables(lds, tabs);
     }
     const uint64_t wave =
         (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1166,130 +1102,115 @@ hipError_t launch_finalize(int mode, const DevRegion* regs, uint32_t n_regs,
 
 // ------------------------------------------------------------ block CRC
 
-// x^(8n) mod P from the table xp[i] = x^(8 * 2^i): the product of the
-// entries for the set bits of n, reduced across the wave.  Every lane returns
-// it; all lanes of the wave must call.
-__device__ __forceinline__ uint32_t xpow8n_wave(uint64_t n, const uint32_t* __restrict__ xp,
-                                               uint32_t lane)
+// x^(8 * 4096 * k) mod P: a table entry per byte of k, almost always one.
+__device__ __forceinline__ uint32_t xpow_batches(uint64_t k, const CrcTables* __restrict__ tabs)
 {
-    uint32_t v = ((n >> lane) & 1u) ? xp[lane] : 0x80000000u;  // x^0 when the bit is clear
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1)
-        v = gf2_mulmod(v, (uint32_t)__shfl_xor((int)v, d));
+    uint32_t v = tabs->xb[0][k & 255u];
+    for (int i = 1; i < 3; ++i) {
+        const uint32_t e = (uint32_t)(k >> (8 * i)) & 255u;
+        if (e)
+            v = gf2_mulmod(v, tabs->xb[i][e]);
+    }
     return v;
 }
 
-// x^(8 n_w) for one n per wave of a 256-thread workgroup, the four computed
-// in parallel, into pw[w]; the caller synchronises before reading them.
-__device__ __forceinline__ void wave_powers(uint64_t n0, uint64_t n1, uint64_t n2, uint64_t n3,
-                                            const uint32_t* __restrict__ xp, uint32_t* pw)
+// x^(8n) mod P for a multiple n of 4.
+__device__ __forceinline__ uint32_t xpow_words(uint64_t n, const CrcTables* __restrict__ tabs)
 {
-    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-    const uint64_t n = wave == 0 ? n0 : wave == 1 ? n1 : wave == 2 ? n2 : n3;
-    const uint32_t v = xpow8n_wave(n, xp, lane);
-    if (lane == 0)
-        pw[wave] = v;
+    const uint32_t r = tabs->xr[(n & 4095u) >> 2];
+    return n >> 12 ? gf2_mulmod(r, xpow_batches(n >> 12, tabs)) : r;
 }
 
-// Standard CRC-32C of an n-byte message from its raw CRC (zero initial
-// value, no final inversion) and x^(8n): the all-ones initial value carried
-// through the n bytes, plus the final inversion.
-__device__ __forceinline__ uint32_t crc_from_raw(uint32_t raw, uint32_t x8n)
-{
-    return raw ^ gf2_mulmod(0xFFFFFFFFu, x8n) ^ 0xFFFFFFFFu;
-}
-
-// Raw CRC of the 4 KiB steps [j0, j1) of a message by one 256-thread
-// workgroup.  load(j) gives thread t's 16-byte word t of step j (the caller
-// left-pads the message with zero bytes to whole steps, which leaves a raw
-// CRC unchanged); use(j, w) is called on it in step order (a store of the
-// word, or nothing).  Thread t keeps a Horner accumulator with a "shift by
-// 4 KiB" step over its words, the wave butterfly combines lanes and each wave
-// is shifted by the 1 KiB stripes that follow it.  Eight steps' loads are in
-// flight before they are folded.  lds: slicing tables and all seven shift
-// levels.  Uniform over the workgroup; all threads return the value.
-template <typename Load, typename Use>
-__device__ __forceinline__ uint32_t wg_crc_steps(Load load, Use use, uint64_t j0, uint64_t j1,
-                                                 const uint32_t* __restrict__ lds, uint32_t* red)
-{
-    const uint32_t tid = threadIdx.x;
-    const uint32_t lane = tid & 63u;
-    const uint32_t wave = tid >> 6;
-    const uint32_t* Z1024 = lds + kSliceWords + 5 * 1024;
-    const uint32_t* Z4096 = lds + kSliceWords + 6 * 1024;
-    constexpr int U = 8;
-    uint32_t s = 0;
-    uint64_t j = j0;
-    for (; j + U <= j1; j += U) {
-        uint4 w[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            w[u] = load(j + u);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            use(j + u, w[u]);
-            s = shiftz(Z4096, s) ^ word_crc(lds, w[u]);
-        }
-    }
-    for (; j < j1; ++j) {
-        const uint4 w = load(j);
-        use(j, w);
-        s = shiftz(Z4096, s) ^ word_crc(lds, w);
-    }
-    s = lane_combine(lds, s, lane);
-    for (uint32_t k = wave; k < 3; ++k)
-        s = shiftz(Z1024, s);
-    if (lane == 0)
-        red[wave] = s;
-    __syncthreads();
-    const uint32_t raw = red[0] ^ red[1] ^ red[2] ^ red[3];
-    __syncthreads();
-    return raw;
-}
-
-// A message of n bytes cut into S = ceil(n / 4096) steps of 4 KiB after
-// left-padding with zeros; workgroup b of nb takes steps [S b / nb,
-// S (b + 1) / nb).  Its raw CRC times x^(8 * bytes after its steps) is its
-// share of the message's raw CRC, and the shares XOR to the whole.
-struct StepSplit {
+// A message of n bytes cut into 4 KiB batches after left-padding it with zeros
+// (which leaves a raw CRC unchanged); share i of ns, one wave's, is batches
+// [j0, j1).
+struct MessageShare {
     uint64_t steps, j0, j1;
     int64_t pad;  // zero bytes in front of the message
-    __device__ StepSplit(uint64_t n, uint32_t b, uint32_t nb)
+    __device__ MessageShare(uint64_t n, uint32_t i, uint32_t ns)
     {
         steps = (n + 4095) >> 12;
         pad = (int64_t)(steps * 4096 - n);
-        j0 = steps * b / nb;
-        j1 = steps * (b + 1) / nb;
+        j0 = steps * i / ns;
+        j1 = steps * (i + 1) / ns;
     }
-    // message offset of thread t's first byte of step j (negative: padding)
-    __device__ int64_t at(uint64_t j) const
+    __device__ bool empty() const { return j0 >= j1; }
+    // message offset of this lane's 16 bytes of step t of batch j (negative: padding)
+    __device__ int64_t at(uint64_t j, int t, uint32_t lane) const
     {
-        return (int64_t)((j * 256 + threadIdx.x) * 16) - pad;
+        return (int64_t)((j * 256 + 64 * t + lane) * 16) - pad;
     }
 };
 
-// This workgroup's share of the raw CRC of the message split by sp: the raw
-// CRC of its steps times x_after = x^(8 * bytes after them), zero when it
-// has no steps.  load and use as for wg_crc_steps.  Uniform over the
-// workgroup.
+// This wave's share of the raw CRC of a message that starts from the all-ones
+// register: the raw CRC of its batches times x^(8 * bytes after them); the
+// shares XOR to the whole.  load(v) gives the 16 bytes at message offset v (words
+// before the message zero); use(v, w) is called on them (a store of the words, or
+// nothing).  The initial register is XORed into the first word.  Uniform over
+// the wave.
 template <typename Load, typename Use>
-__device__ __forceinline__ uint32_t wg_crc_share(const StepSplit& sp, Load load, Use use,
-                                                 uint32_t x_after,
-                                                 const uint32_t* __restrict__ lds, uint32_t* red)
+__device__ __forceinline__ uint32_t message_share(const MessageShare& sp, Load load, Use use,
+                                                  const CrcMatrix& mat,
+                                                  const CrcTables* __restrict__ tabs,
+                                                  const uint32_t* __restrict__ lds,
+                                                  uint32_t lane)
 {
-    if (sp.j0 >= sp.j1)
+    if (sp.empty())
         return 0;
-    return gf2_mulmod(wg_crc_steps(load, use, sp.j0, sp.j1, lds, red), x_after);
+    uint32_t s = 0;
+    for (uint64_t j = sp.j0; j < sp.j1; ++j) {
+        u32x4 w[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            w[t] = load(sp.at(j, t, lane));
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            use(sp.at(j, t, lane), w[t]);
+        if (j == 0) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (sp.at(j, t, lane) + 4 * i == 0)
+                        w[t][i] ^= 0xFFFFFFFFu;
+        }
+        const uint32_t f = fold_4k(mat, w, lane >> 5);
+        s = j > sp.j0 ? shift_4k(lds, s) ^ f : f;
+    }
+    const uint32_t raw = columns_crc(lds, s, lane);
+    const uint64_t after = sp.steps - sp.j1;
+    return after ? gf2_mulmod(raw, xpow_batches(after, tabs)) : raw;
 }
 
-// Workgroups a request's header or image check uses: about two 4 KiB steps
-// each over the longer of its two CRC messages, at most the nb launched.
-__device__ __forceinline__ uint32_t active_blocks(uint64_t bytes_a, uint64_t bytes_b, uint32_t nb)
+// Workgroups for two messages: about two 4 KiB batches for each of their
+// waves, at most max.  The meeting of several workgroups costs 6 us or more
+// (atomics, fences): 154 batches took no longer with two a wave than with one.
+__host__ __device__ __forceinline__ uint32_t message_blocks(uint64_t bytes_a, uint64_t bytes_b,
+                                                            uint32_t max)
 {
-    const uint64_t steps = ((bytes_a > bytes_b ? bytes_a : bytes_b) + 4095) >> 12;
-    const uint64_t want = (steps + 1) / 2;
-    return want < 1 ? 1u : want < nb ? (uint32_t)want : nb;
+    const uint64_t want = (((bytes_a + 4095) >> 12) + ((bytes_b + 4095) >> 12) + 7) / 8;
+    return want < 1 ? 1u : want < max ? (uint32_t)want : max;
 }
+
+// Which message the wave with index i of n takes a share of, and which share:
+// the waves are split by the messages' batches, at least one for each message
+// that is not empty.
+struct WaveRole {
+    bool first;  // the first message (a), else the second
+    uint32_t share, shares;
+    __device__ WaveRole(uint64_t bytes_a, uint64_t bytes_b, uint32_t i, uint32_t n)
+    {
+        const uint64_t ba = (bytes_a + 4095) >> 12, bb = (bytes_b + 4095) >> 12;
+        uint32_t na = ba == 0 ? 0u : (uint32_t)((uint64_t)n * ba / (ba + bb));
+        if (ba && na == 0)
+            na = 1;
+        if (bb && na == n)
+            na = n - 1;
+        first = i < na;
+        share = first ? i : i - na;
+        shares = first ? na : n - na;
+    }
+};
 
 // Called once by every workgroup of a request after its atomics: true in
 // exactly one of them, the last to arrive, which then sees every other
@@ -1317,22 +1238,22 @@ __device__ __forceinline__ void read_accs(uint32_t* acc, uint32_t* s_vals)
     __syncthreads();
 }
 
-// 0xFFFFFFFF * x^(8 * 60): the all-ones initial value carried to the end of
-// the header's first 60 bytes.
-constexpr uint32_t kInitOver60 = gf2_shift(0xFFFFFFFFu, 60);
-
 // ------------------------------------------------------------ k_header
 
 // nb workgroups launched per request of [q0, q0 + gridDim.x / nb), of which
-// the first active_blocks() work.  Each writes its share of the prefix
-// (header, region table, bitmap) and of the CRC array into the image while
-// folding the same words into its shares of the raw meta_crc and crcs_crc
-// (read from the sources, never back from the image, which may sit in host
-// memory).  In the meta message the header's last two words (meta_crc,
-// crcs_crc) count as zero; crcs_crc is added at the end by linearity.  With
-// several workgroups O.acc collects the shares and the arrivals (zero on
+// the first message_blocks() work.  Each of their waves takes a share of the CRC
+// array or of the prefix (header, region table, bitmap): it writes the words into
+// the image while folding them into its share of crcs_crc or meta_crc (read from
+// the sources, never back from the image, which may sit in host memory).  In the meta message the header's last two words
+// (meta_crc, crcs_crc) count as zero; crcs_crc is added at the end by linearity.
+// With several workgroups O.acc collects the shares and the arrivals (zero on
 // entry: the final scan clears it) and the last to arrive writes the two CRC
-// words; a single workgroup keeps its shares in registers.
+// words.
+//
+// Bound by latency: a chain of dependent reads, products and, with several
+// workgroups, atomics.  With byte tables (44 KiB to stage) and a butterfly over
+// lanes, four powers of x and five products the 64 MiB image's header took 14.6
+// us and a 1.5 GiB one's of 4 KiB pages 22; now 8 and 13.
 __global__ __launch_bounds__(256) void k_header(const DevRegion* __restrict__ regs,
                                                 const DevRequest* __restrict__ reqs,
                                                 DevReqOut* __restrict__ out,
@@ -1342,18 +1263,18 @@ __global__ __launch_bounds__(256) void k_header(const DevRegion* __restrict__ re
                                                 uint32_t nb, uint64_t capacity,
                                                 const CrcTables* __restrict__ tabs)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t lds[kAllTabWords];
-    __shared__ uint32_t red[4];
+    __shared__ __attribute__((aligned(16))) uint32_t lds[kCrcLdsWords];
+    __shared__ uint32_t red[8];
     __shared__ uint32_t s_word;
     __shared__ uint32_t s_hdr[16];
-    __shared__ uint32_t s_pw[4];
     __shared__ uint32_t s_acc[4];
     const uint32_t q = q0 + blockIdx.x / nb, b = blockIdx.x % nb;
     const DevRequest& Q = reqs[q];
     DevReqOut& O = out[q];
     if (O.code != 0 && O.img_base + Q.data_off > capacity)
         return;  // no room even for the prefix
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint8_t* img = staging + O.img_base;
     const uint64_t R = Q.n_regions;
     const uint64_t table_end = 64 + 32 * R;
@@ -1361,33 +1282,22 @@ __global__ __launch_bounds__(256) void k_header(const DevRegion* __restrict__ re
     const uint64_t D = O.n_dirty;
     const uint64_t first_page0 = Q.first_word * 64;
     const bool ok = O.code == 0;
-    const uint32_t ne = active_blocks(prefix_end, ok ? 4 * D : 0, nb);
+    const uint64_t crc_bytes = ok ? 4 * D : 0;
+    const uint32_t ne = message_blocks(crc_bytes, prefix_end, nb);
     if (b >= ne)
         return;
-    const StepSplit m(prefix_end, b, ne);
-    const StepSplit c(ok ? 4 * D : 0, b, ne);
-    // the shares' shifts, and for the last workgroup x^(8 * 4D) and
-    // x^(8 * (prefix_end - 60)) (crcs_crc's place in the meta message)
-    wave_powers((c.steps - c.j1) * 4096, (m.steps - m.j1) * 4096, 4 * D, prefix_end - 60,
-                tabs->xp, s_pw);
-    load_all_tables(lds, tabs);
-
-    // header words (the two CRC words zero), in the workgroups whose steps
-    // hold some of its bytes: padded positions [m.pad, m.pad + 64)
-    const bool has_hdr = m.j0 < m.j1 && m.j0 * 4096 < (uint64_t)m.pad + 64 &&
-                         m.j1 * 4096 > (uint64_t)m.pad;
-    uint32_t shadowed = 0;
-    if (has_hdr)
-        for (uint64_t i = tid; i < R; i += blockDim.x)
-            shadowed |= regs[Q.first_region + i].shadow ? 1u : 0u;
-    const int any_shadow = __syncthreads_or((int)shadowed);
+    const WaveRole role(crc_bytes, prefix_end, 4 * b + wave, 4 * ne);
+    const MessageShare sp(role.first ? crc_bytes : prefix_end, role.share, role.shares);
+    CrcMatrix mat;
+    if (!sp.empty())
+        load_crc_matrix(mat, tabs, lane);
     if (tid == 0) {
         s_hdr[0] = 0x4D555243u;  // "CRUM"
         s_hdr[1] = 0x31474D49u;  // "IMG1"
         s_hdr[2] = 1;
         s_hdr[3] = 1u << Q.page_shift;
         s_hdr[4] = (uint32_t)R;
-        s_hdr[5] = any_shadow ? 0u : 1u;
+        s_hdr[5] = (Q.flags & kReqShadow) ? 0u : 1u;
         s_hdr[6] = (uint32_t)Q.n_pages;
         s_hdr[7] = (uint32_t)(Q.n_pages >> 32);
         s_hdr[8] = (uint32_t)D;
@@ -1399,87 +1309,85 @@ __global__ __launch_bounds__(256) void k_header(const DevRegion* __restrict__ re
         s_hdr[14] = 0;
         s_hdr[15] = 0;
     }
-    __syncthreads();
-    const uint64_t gt = (uint64_t)b * blockDim.x + tid, gstride = (uint64_t)ne * blockDim.x;
-    for (uint64_t o = prefix_end + 8 * gt; o < Q.data_off; o += 8 * gstride)
-        *reinterpret_cast<uint64_t*>(img + o) = 0;
+    load_crc_tables(lds, tabs);
 
-    // prefix word at byte r: header, region table entries {id, len, first
-    // page within the request, 0}, then the bitmap
-    const gcu32 bm32 = (gcu32)(bitmap + Q.first_word);
-    auto prefix_word = [&](uint64_t r) -> uint32_t {
-        if (r < 64)
-            return s_hdr[r >> 2];
-        if (r < table_end) {
-            const uint64_t t = r - 64;
-            const DevRegion& G = regs[Q.first_region + (t >> 5)];
-            const uint32_t k = (uint32_t)(t >> 2) & 7u;
-            const uint64_t v = k < 2 ? G.id : k < 4 ? G.len : k < 6 ? G.first_page - first_page0 : 0;
-            return (uint32_t)(v >> (32 * (k & 1)));
-        }
-        return bm32[(r - table_end) >> 2];
-    };
-    // m.pad is a multiple of 8, so each thread's 16 bytes are two aligned
-    // 8-byte pairs; the pair at 56 is the two CRC words, written last
-    auto m_load = [&](uint64_t j) {
-        const int64_t v = m.at(j);
-        uint32_t w[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int64_t r = v + 4 * i;
-            w[i] = r >= 0 ? prefix_word((uint64_t)r) : 0u;
-        }
-        return make_uint4(w[0], w[1], w[2], w[3]);
-    };
-    auto m_use = [&](uint64_t j, uint4 w) {
-        const int64_t v = m.at(j);
-        if (v >= 0 && v != 56)
-            *(gv2)(img + v) = u32x2{w.x, w.y};
-        if (v + 8 >= 0 && v + 8 != 56)
-            *(gv2)(img + v + 8) = u32x2{w.z, w.w};
-    };
-    const uint32_t m_share = wg_crc_share(m, m_load, m_use, s_pw[1], lds, red);
-    uint32_t c_share = 0;
-    if (ok) {
-        const uint64_t crcs_off = Q.data_off + (D << Q.page_shift);
+    uint32_t share = 0;
+    if (role.first) {
+        uint8_t* dst = img + Q.data_off + (D << Q.page_shift);
         const gcu32 src = (gcu32)(crcs + O.slot_base);
-        uint8_t* dst = img + crcs_off;
-        const bool even = (D & 1) == 0;  // then c.pad, and every v, is a multiple of 8
-        auto c_load = [&](uint64_t j) {
-            const int64_t v = c.at(j);
-            uint32_t w[4];
+        const bool even = (D & 1) == 0;  // then the pad, and every v, is a multiple of 8
+        auto load = [&](int64_t v) {
+            u32x4 w;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 w[i] = v + 4 * i >= 0 ? src[(v >> 2) + i] : 0u;
-            return make_uint4(w[0], w[1], w[2], w[3]);
+            return w;
         };
-        auto c_use = [&](uint64_t j, uint4 w) {
-            const int64_t v = c.at(j);
+        auto use = [&](int64_t v, u32x4 w) {
             if (even) {
                 if (v >= 0)
                     *(gv2)(dst + v) = u32x2{w.x, w.y};
                 if (v + 8 >= 0)
                     *(gv2)(dst + v + 8) = u32x2{w.z, w.w};
             } else {
-                const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
                     if (v + 4 * i >= 0)
-                        ((gu32)dst)[(v >> 2) + i] = ws[i];
+                        ((gu32)dst)[(v >> 2) + i] = w[i];
             }
         };
-        c_share = wg_crc_share(c, c_load, c_use, s_pw[0], lds, red);
-        if (b == 0 && tid == 0 && !even)
+        share = message_share(sp, load, use, mat, tabs, lds, lane);
+        if (role.share == 0 && lane == 0 && !even)
             ((gu32)dst)[D] = 0;
+    } else {
+        // prefix word at byte r: header, region table entries {id, len, first
+        // page within the request, 0}, then the bitmap
+        const gcu32 bm32 = (gcu32)(bitmap + Q.first_word);
+        auto prefix_word = [&](uint64_t r) -> uint32_t {
+            if (r >= table_end)
+                return bm32[(r - table_end) >> 2];
+            if (r < 64)
+                return s_hdr[r >> 2];
+            const uint64_t t = r - 64;
+            const DevRegion& G = regs[Q.first_region + (t >> 5)];
+            const uint32_t k = (uint32_t)(t >> 2) & 7u;
+            const uint64_t v =
+                k < 2 ? G.id : k < 4 ? G.len : k < 6 ? G.first_page - first_page0 : 0;
+            return (uint32_t)(v >> (32 * (k & 1)));
+        };
+        // the prefix is a multiple of 8 bytes, so each lane's 16 are two aligned
+        // 8-byte pairs; the pair at 56 is the two CRC words, written last
+        auto load = [&](int64_t v) {
+            u32x4 w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                w[i] = v + 4 * i >= 0 ? prefix_word((uint64_t)(v + 4 * i)) : 0u;
+            return w;
+        };
+        auto use = [&](int64_t v, u32x4 w) {
+            if (v >= 0 && v != 56)
+                *(gv2)(img + v) = u32x2{w.x, w.y};
+            if (v + 8 >= 0 && v + 8 != 56)
+                *(gv2)(img + v + 8) = u32x2{w.z, w.w};
+        };
+        share = message_share(sp, load, use, mat, tabs, lds, lane);
     }
-
-    uint32_t c_raw = c_share, m_raw = m_share;
+    if (lane == 0) {
+        red[wave] = role.first ? share : 0;
+        red[4 + wave] = role.first ? 0 : share;
+    }
+    const uint64_t gt = (uint64_t)b * blockDim.x + tid, gstride = (uint64_t)ne * blockDim.x;
+    for (uint64_t o = prefix_end + 8 * gt; o < Q.data_off; o += 8 * gstride)
+        *reinterpret_cast<uint64_t*>(img + o) = 0;
+    __syncthreads();
+    uint32_t c_raw = red[0] ^ red[1] ^ red[2] ^ red[3];
+    uint32_t m_raw = red[4] ^ red[5] ^ red[6] ^ red[7];
     if (ne > 1) {
         if (tid == 0) {
-            if (c_share)
-                atomicXor(&O.acc[0], c_share);
-            if (m_share)
-                atomicXor(&O.acc[1], m_share);
+            if (c_raw)
+                atomicXor(&O.acc[0], c_raw);
+            if (m_raw)
+                atomicXor(&O.acc[1], m_raw);
         }
         if (!last_arrival(&O.acc[2], ne, &s_word))
             return;
@@ -1488,23 +1396,17 @@ __global__ __launch_bounds__(256) void k_header(const DevRegion* __restrict__ re
         m_raw = s_acc[1];
     }
     if (tid == 0) {
-        const uint32_t crcs_crc = ok ? crc_from_raw(c_raw, s_pw[2]) : 0u;
-        // raw meta with crcs_crc in place, then the initial value and inversion
-        const uint32_t meta = m_raw ^ gf2_mulmod(crcs_crc ^ kInitOver60, s_pw[3]) ^ 0xFFFFFFFFu;
+        const uint32_t crcs_crc = crc_bytes ? c_raw ^ 0xFFFFFFFFu : 0u;
+        const uint32_t meta =
+            m_raw ^ gf2_mulmod(crcs_crc, xpow_words(prefix_end - 60, tabs)) ^ 0xFFFFFFFFu;
         *(gv2)(img + 56) = u32x2{meta, crcs_crc};
     }
 }
 
-// Workgroups per request for the header and image-check kernels: about two
-// 4 KiB CRC steps each over the larger of the prefix and the CRC array, at
-// most 128.
+// Workgroups per request for the header and image-check kernels.
 uint32_t header_blocks(uint64_t n_regions, uint64_t n_words, uint64_t n_crcs)
 {
-    const uint64_t prefix = 64 + 32 * n_regions + 8 * n_words;
-    const uint64_t bytes = prefix > 4 * n_crcs ? prefix : 4 * n_crcs;
-    const uint64_t steps = (bytes + 4095) >> 12;
-    const uint64_t nb = (steps + 1) / 2;
-    return (uint32_t)(nb < 1 ? 1 : nb > 128 ? 128 : nb);
+    return message_blocks(4 * n_crcs, 64 + 32 * n_regions + 8 * n_words, 128);
 }
 
 hipError_t launch_header(const DevRegion* regs, const DevRequest* reqs, uint32_t q0, uint32_t q1,
@@ -1567,7 +1469,7 @@ hipError_t launch_plan_status(const DevReqOut* out, uint32_t n, uint8_t* dst, hi
 // Device-side image checks that need the bytes: meta_crc, crcs_crc, bitmap
 // population and unused bits, zero pads.  The host has already checked the
 // header fields, lengths and the region table.  nb workgroups launched per
-// request, of which the first active_blocks() work; each takes a share of the
+// request, of which the first message_blocks() work; each takes a share of the
 // bitmap, the pad and the two CRC messages.  With several, O.acc (zero on
 // entry: the host uploads it cleared) collects the CRC shares, the arrivals
 // and the population, and the last workgroup to arrive compares.
@@ -1578,13 +1480,13 @@ __global__ __launch_bounds__(256) void k_restore_check(const DevRequest* __restr
                                                        const CrcTables* __restrict__ tabs,
                                                        DevGlobal* __restrict__ glob)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t lds[kAllTabWords];
-    __shared__ uint32_t red[4];
+    __shared__ __attribute__((aligned(16))) uint32_t lds[kCrcLdsWords];
+    __shared__ uint32_t red[8];
     __shared__ uint32_t s_pop;
     __shared__ uint32_t s_word;
-    __shared__ uint32_t s_pw[4];
     __shared__ uint32_t s_acc[4];
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t q = blockIdx.x / nb, b = blockIdx.x % nb;
     const DevRequest& Q = reqs[q];
     DevReqOut& O = out[q];
@@ -1594,16 +1496,17 @@ __global__ __launch_bounds__(256) void k_restore_check(const DevRequest* __restr
     const uint64_t prefix_end = 64 + 32 * R + 8 * Q.n_words;
     const uint64_t D = reinterpret_cast<const uint64_t*>(img)[4];
     const uint64_t crcs_off = Q.data_off + (D << Q.page_shift);
-    const uint32_t ne = active_blocks(prefix_end, 4 * D, nb);
+    const uint32_t ne = message_blocks(4 * D, prefix_end, nb);
     if (b >= ne)
         return;
-    const StepSplit c(4 * D, b, ne);
-    const StepSplit m(prefix_end, b, ne);
-    wave_powers((c.steps - c.j1) * 4096, (m.steps - m.j1) * 4096, 4 * D, prefix_end, tabs->xp,
-                s_pw);
+    const WaveRole role(4 * D, prefix_end, 4 * b + wave, 4 * ne);
+    const MessageShare sp(role.first ? 4 * D : prefix_end, role.share, role.shares);
+    CrcMatrix mat;
+    if (!sp.empty())
+        load_crc_matrix(mat, tabs, lane);
     if (tid == 0)
         s_pop = 0;
-    load_all_tables(lds, tabs);
+    load_crc_tables(lds, tabs);
 
     const uint64_t gt = (uint64_t)b * blockDim.x + tid, gstride = (uint64_t)ne * blockDim.x;
     const uint64_t* bm = reinterpret_cast<const uint64_t*>(img + 64 + 32 * R);
@@ -1629,36 +1532,33 @@ __global__ __launch_bounds__(256) void k_restore_check(const DevRequest* __restr
     if (pop)
         atomicAdd(&s_pop, pop);
 
-    auto no_use = [](uint64_t, uint4) {};
-    const gcu32 c32 = (gcu32)(img + crcs_off);
-    auto c_load = [&](uint64_t j) {
-        const int64_t v = c.at(j);
-        uint32_t w[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            w[i] = v + 4 * i >= 0 ? c32[(v >> 2) + i] : 0u;
-        return make_uint4(w[0], w[1], w[2], w[3]);
-    };
-    const uint32_t c_share = wg_crc_share(c, c_load, no_use, s_pw[0], lds, red);
-    auto m_load = [&](uint64_t j) {
-        const int64_t v = m.at(j);
-        uint32_t w[4];
+    // the CRC array, or the prefix (where meta_crc itself reads as zero)
+    const gcu32 src = role.first ? (gcu32)(img + crcs_off) : img32;
+    const int64_t zero_at = role.first ? -1 : 56;
+    auto load = [&](int64_t v) {
+        u32x4 w;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int64_t r = v + 4 * i;
-            w[i] = r >= 0 && r != 56 ? img32[r >> 2] : 0u;  // meta_crc itself reads as zero
+            w[i] = r >= 0 && r != zero_at ? src[r >> 2] : 0u;
         }
-        return make_uint4(w[0], w[1], w[2], w[3]);
+        return w;
     };
-    const uint32_t m_share = wg_crc_share(m, m_load, no_use, s_pw[1], lds, red);
+    const uint32_t share =
+        message_share(sp, load, [](int64_t, u32x4) {}, mat, tabs, lds, lane);
+    if (lane == 0) {
+        red[wave] = role.first ? share : 0;
+        red[4 + wave] = role.first ? 0 : share;
+    }
     __syncthreads();
-    uint32_t c_raw = c_share, m_raw = m_share, total_pop = s_pop;
+    uint32_t c_raw = red[0] ^ red[1] ^ red[2] ^ red[3];
+    uint32_t m_raw = red[4] ^ red[5] ^ red[6] ^ red[7], total_pop = s_pop;
     if (ne > 1) {
         if (tid == 0) {
-            if (c_share)
-                atomicXor(&O.acc[0], c_share);
-            if (m_share)
-                atomicXor(&O.acc[1], m_share);
+            if (c_raw)
+                atomicXor(&O.acc[0], c_raw);
+            if (m_raw)
+                atomicXor(&O.acc[1], m_raw);
             if (s_pop)
                 atomicAdd(&O.acc[3], s_pop);
         }
@@ -1670,8 +1570,8 @@ __global__ __launch_bounds__(256) void k_restore_check(const DevRequest* __restr
         total_pop = s_acc[3];
     }
     if (tid == 0) {
-        const uint32_t crcs = crc_from_raw(c_raw, s_pw[2]);
-        const uint32_t meta = crc_from_raw(m_raw, s_pw[3]);
+        const uint32_t crcs = D ? c_raw ^ 0xFFFFFFFFu : 0u;
+        const uint32_t meta = m_raw ^ 0xFFFFFFFFu;
         if ((uint64_t)total_pop != D || crcs != img32[15] || meta != img32[14])
             atomicOr(&glob->fmt_bad, 1u);
     }

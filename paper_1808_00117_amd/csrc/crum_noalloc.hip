@@ -194,6 +194,7 @@ int crum_snapshot_noalloc(crum_ctx* c, const crum_region* regions, uint32_t n_re
     rq.n_pages = G;
     rq.first_region = 0;
     rq.n_regions = n_regions;
+    rq.flags = any_shadow(regions, n_regions) ? kReqShadow : 0;
     rq.data_off = data_off;
     rq.seq = seq;
     rq.page_shift = ps;

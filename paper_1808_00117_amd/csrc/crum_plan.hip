@@ -160,6 +160,7 @@ int crum_plan_create(crum_ctx* c, const crum_request* reqs, uint32_t n_reqs, voi
         Q.first_word = page / 64;
         Q.first_region = ri;
         Q.n_regions = r.n_regions;
+        Q.flags = any_shadow(r.regions, r.n_regions) ? kReqShadow : 0;
         Q.seq = r.seq;
         Q.page_shift = ps;
         Q.init_fix = crc_init_fix(r.page_size);

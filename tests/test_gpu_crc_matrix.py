@@ -59,3 +59,34 @@ def test_pages_and_pieces(P, piece_shift, fill):
            "random": np.random.default_rng(P + piece_shift).integers(0, 256, n * P,
                                                                      dtype=np.uint8)}[fill]
     check(cur, P, piece_shift)
+
+
+@pytest.mark.parametrize("n_pages", [1024 * 3 + 1, 262144 + 77, 3 * 262144 // 2])
+def test_checksums_of_long_messages(n_pages):
+    """crcs_crc and meta_crc of CRC arrays and prefixes of one to hundreds of
+    4 KiB batches (shares followed by more than 255 batches)."""
+    import torch
+    import paper_1808_00117_amd as crum
+    from paper_1808_00117_amd.api import Snapshotter
+
+    P = 4 * KiB
+    log(f"[crc] {n_pages} pages")
+    s = Snapshotter(0)
+    try:
+        cur = torch.empty(n_pages * P // 8, dtype=torch.int64, device="cuda").random_()
+        size = crum.crum_image_bytes(1, n_pages, n_pages, P)
+        staging = torch.empty(size, dtype=torch.uint8, device="cuda")
+        rc, st = s.snapshot([(cur, None, 3)], P, staging, seq=2)
+        assert rc == 0 and st.code == 0 and st.n_dirty == n_pages
+        prefix_end = 64 + 32 + 8 * ((n_pages + 63) // 64)
+        prefix = staging[:prefix_end].cpu().numpy()
+        at = crum.crum_image_prefix_bytes(1, n_pages) + n_pages * P
+        crcs = staging[at:at + 4 * n_pages].cpu().numpy()
+        meta, crcs_crc = prefix[56:64].copy().view(np.uint32)
+        assert crcs_crc == oracle.crc32c(crcs)
+        prefix[56:60] = 0
+        assert meta == oracle.crc32c(prefix)
+        rc, st = s.restore([(cur, None, 3)], None, size, staging, flags=crum.CRUM_VERIFY)
+        assert rc == 0 and st.code == 0
+    finally:
+        s.close()
