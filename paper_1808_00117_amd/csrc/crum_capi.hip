@@ -7,6 +7,7 @@
 #include "gf2.h"
 
 #include <algorithm>
+#include <chrono>
 #include <cstdlib>
 #include <cstring>
 #include <utility>
@@ -134,6 +135,13 @@ hipError_t ensure_pinned(crum_ctx* c, size_t bytes)
     return e;
 }
 
+// Before the pinned buffer is written again: the previous call's tables have
+// been read (also when it stopped part-way through its enqueue).
+hipError_t settle(crum_ctx* c)
+{
+    return c->partial_call ? hipDeviceSynchronize() : hipEventSynchronize(c->ev_upload);
+}
+
 hipError_t ensure_events(std::vector<hipEvent_t>& v, size_t n)
 {
     while (v.size() < n) {
@@ -169,6 +177,32 @@ static uint64_t rd64(const uint8_t* p)
     uint64_t v;
     std::memcpy(&v, p, 8);
     return v;
+}
+
+int wait_count(const uint64_t* count, hipEvent_t ev, hipStream_t s)
+{
+    // long enough for the largest chunk of device memory's diff
+    const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(1500);
+    for (uint32_t i = 0; __atomic_load_n(count, __ATOMIC_ACQUIRE) == kNoCount; ++i) {
+        __builtin_ia32_pause();
+        if ((i & 63u) == 63u && std::chrono::steady_clock::now() > until) {
+            if ((ev ? hipEventSynchronize(ev) : hipStreamSynchronize(s)) != hipSuccess ||
+                __atomic_load_n(count, __ATOMIC_ACQUIRE) == kNoCount)
+                return CRUM_EHIP;
+            break;
+        }
+    }
+    return CRUM_OK;
+}
+
+void* mapped_status(crum_status* h_status)
+{
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, h_status) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return a.type == hipMemoryTypeHost && a.devicePointer == h_status ? h_status : nullptr;
 }
 
 // Flatten one table into DevRegion entries (single request, request 0).
@@ -296,7 +330,6 @@ int crum_ctx_create(int device, const char* tuning_cache, crum_ctx** out)
                   hipSuccess &&
               hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) == hipSuccess &&
               hipEventCreateWithFlags(&c->ev_upload, hipEventDisableTiming) == hipSuccess &&
-              hipEventCreateWithFlags(&c->ev_count, hipEventDisableTiming) == hipSuccess &&
               hipEventCreateWithFlags(&c->ev_done, hipEventDisableTiming) == hipSuccess &&
               hipEventCreateWithFlags(&c->ev_hdr, hipEventDisableTiming) == hipSuccess &&
               hipHostMalloc(reinterpret_cast<void**>(&c->na_pin), kNoAllocPinnedBytes, 0) ==
@@ -322,7 +355,7 @@ void crum_ctx_destroy(crum_ctx* c)
         (void)hipEventDestroy(e);
     for (hipEvent_t e : c->ev_cnt)
         (void)hipEventDestroy(e);
-    for (hipEvent_t e : {c->ev_upload, c->ev_count, c->ev_done, c->ev_hdr})
+    for (hipEvent_t e : {c->ev_upload, c->ev_done, c->ev_hdr})
         if (e)
             (void)hipEventDestroy(e);
     if (c->side)
@@ -684,7 +717,7 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
     CRUM_TRY(ensure_pinned(c, rb_off + 128 + 8 * n_chunks));
     CRUM_TRY(ensure_events(c->ev_chunk, n_chunks));
     CRUM_TRY(ensure_events(c->ev_cnt, n_chunks));
-    CRUM_TRY(hipEventSynchronize(c->ev_upload));
+    CRUM_TRY(settle(c));
     uint8_t* P = c->h_pin;
     std::memset(P, 0, L.upload_end);
     std::memcpy(P + L.regs, dregs.data(), sizeof(DevRegion) * n_regions);
@@ -724,11 +757,19 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
     uint8_t* himg = static_cast<uint8_t*>(h_image);
     uint8_t* rb = P + rb_off;
 
+    uint64_t* h_counts = reinterpret_cast<uint64_t*>(rb + 128);
+    for (size_t ci = 0; ci < n_chunks; ++ci)
+        h_counts[ci] = kNoCount;
+    void* d_status = mapped_status(h_status);
+    const FlagSource flag_src{d_regs, n_regions, d_flags};
+
     // the previous call on this context may still be draining from scratch
     c->partial_call = true;  // cleared once ev_done is recorded
     CRUM_TRY(hipStreamWaitEvent(stream, c->ev_done, 0));
-    CRUM_TRY(hipMemcpyAsync(S, P, L.upload_end, hipMemcpyHostToDevice, stream));
-    CRUM_TRY(hipEventRecord(c->ev_upload, stream));
+    CRUM_TRY(launch_begin(P, S, L.upload_end, nullptr, stream));
+    // a call that waits for a count knows that its tables have been read
+    if (direct || (eager && !h_image))
+        CRUM_TRY(hipEventRecord(c->ev_upload, stream));
 
     if (direct) {
         // ---- direct order: diff, scan (with the capacity check), list, then
@@ -741,9 +782,8 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
         }
         {
             Span sp(c, kTScan, stream);
-            CRUM_TRY(launch_bitmap(d_regs, n_regions, 0, W, d_flags, d_bitmap, stream));
-            CRUM_TRY(launch_scan(d_bitmap, 0, W, W, d_prefix, d_bounds, 1, d_reqs, 0, 1, d_out,
-                                 d_glob, capacity, 0, d_list, stream));
+            CRUM_TRY(launch_scan(d_bitmap, 0, W, d_prefix, d_bounds, 1, d_reqs, 0, 1, d_out,
+                                 d_glob, capacity, 0, d_list, stream, flag_src));
         }
         {
             Span sp(c, kTPack, stream);
@@ -759,10 +799,11 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
         {
             Span sp(c, kTHeader, stream);
             CRUM_TRY(launch_header(d_regs, d_reqs, 0, 1, hdr_blocks, d_out, d_bitmap, d_crcs,
-                                   himg, capacity, c->d_tabs, stream));
+                                   himg, capacity, c->d_tabs, stream, d_status));
         }
-        CRUM_TRY(hipMemcpyAsync(h_status, d_out, sizeof(crum_status), hipMemcpyDeviceToHost,
-                                stream));
+        if (!d_status)
+            CRUM_TRY(hipMemcpyAsync(h_status, d_out, sizeof(crum_status), hipMemcpyDeviceToHost,
+                                    stream));
         CRUM_TRY(hipEventRecord(c->ev_done, stream));
         c->partial_call = false;
         return CRUM_OK;
@@ -783,14 +824,15 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
             }
             {
                 Span sp(c, kTScan, stream);
-                CRUM_TRY(launch_bitmap(d_regs, n_regions, w0, w1, d_flags, d_bitmap, stream));
-                CRUM_TRY(launch_scan(d_bitmap, w0, w1, W, d_prefix, d_bounds + ci,
+                HostNote note;
+                if (himg)
+                    note.count = h_counts + ci;
+                CRUM_TRY(launch_scan(d_bitmap, w0, w1, d_prefix, d_bounds + ci,
                                      ci + 1 == n_chunks, d_reqs, 0, 1, d_out, d_glob, capacity,
-                                     0, d_list, stream));
+                                     0, d_list, stream, flag_src, note));
             }
-            CRUM_TRY(hipMemcpyAsync(rb + 128 + 8 * ci, d_bounds + ci, 8, hipMemcpyDeviceToHost,
-                                    stream));
-            CRUM_TRY(hipEventRecord(c->ev_cnt[ci], stream));
+            if (himg && n_chunks > 1)
+                CRUM_TRY(hipEventRecord(c->ev_cnt[ci], stream));
             {
                 Span sp(c, kTPack, stream);
                 SlotRange sr{0, 0, d_bounds, (uint32_t)ci, g1 - g0};
@@ -802,33 +844,63 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
                                          np_shift, pc_shift, d_partials, d_crcs, staging, d_glob,
                                          c->d_tabs, stream));
             }
-            CRUM_TRY(hipEventRecord(c->ev_chunk[ci], stream));
+            if (himg && ci + 1 < n_chunks)
+                CRUM_TRY(hipEventRecord(c->ev_chunk[ci], stream));
         }
         // the header takes its sizes from the device, so it follows the last
         // pack without waiting for the host
         {
             Span sp(c, kTHeader, stream);
             CRUM_TRY(launch_header(d_regs, d_reqs, 0, 1, hdr_blocks, d_out, d_bitmap, d_crcs,
-                                   staging, capacity, c->d_tabs, stream));
+                                   staging, capacity, c->d_tabs, stream, d_status));
         }
-        // ---- drain each chunk as soon as its count is known (one chunk: the
-        // whole image in one copy behind the header, below)
-        uint64_t prev = 0;
-        for (size_t ci = 0; ci < n_chunks; ++ci) {
-            CRUM_TRY(hipEventSynchronize(c->ev_cnt[ci]));
-            uint64_t cnt;
-            std::memcpy(&cnt, rb + 128 + 8 * ci, 8);
-            if (himg && cnt > prev && n_chunks > 1) {
-                CRUM_TRY(hipStreamWaitEvent(c->side, c->ev_chunk[ci], 0));
-                const uint64_t off = data_off + (prev << ps);
-                Span sp(c, kTDrain, c->side);
-                CRUM_TRY(hipMemcpyAsync(himg + off, staging + off, (cnt - prev) << ps,
-                                        hipMemcpyDeviceToHost, c->side));
+        if (himg && n_chunks == 1) {
+            // one chunk has nothing to overlap: the whole image in one copy
+            // behind the header, on the same stream
+            if (wait_count(h_counts, nullptr, stream) != CRUM_OK)
+                return CRUM_EHIP;
+            D = h_counts[0];
+            image_bytes = data_off + (D << ps) + round_up(4 * D, 8);
+            Span sp(c, kTDrain, stream);
+            CRUM_TRY(hipMemcpyAsync(himg, staging, image_bytes, hipMemcpyDeviceToHost, stream));
+        } else if (himg) {
+            CRUM_TRY(hipEventRecord(c->ev_hdr, stream));
+            // ---- drain each chunk as soon as its count is known; the last one
+            // with the CRC array behind it, after the header
+            uint64_t prev = 0;
+            for (size_t ci = 0; ci < n_chunks; ++ci) {
+                const bool last = ci + 1 == n_chunks;
+                if (wait_count(h_counts + ci, c->ev_cnt[ci], stream) != CRUM_OK)
+                    return CRUM_EHIP;
+                const uint64_t cnt = h_counts[ci];
+                uint64_t bytes = (cnt - prev) << ps;
+                if (last) {
+                    CRUM_TRY(hipStreamWaitEvent(c->side, c->ev_hdr, 0));
+                    Span sp(c, kTDrain, c->side);
+                    CRUM_TRY(hipMemcpyAsync(himg, staging, data_off, hipMemcpyDeviceToHost,
+                                            c->side));
+                    bytes += round_up(4 * cnt, 8);
+                } else if (bytes) {
+                    CRUM_TRY(hipStreamWaitEvent(c->side, c->ev_chunk[ci], 0));
+                }
+                if (bytes) {
+                    const uint64_t off = data_off + (prev << ps);
+                    Span sp(c, kTDrain, c->side);
+                    CRUM_TRY(hipMemcpyAsync(himg + off, staging + off, bytes,
+                                            hipMemcpyDeviceToHost, c->side));
+                }
+                prev = cnt;
             }
-            prev = cnt;
         }
-        D = prev;
-        image_bytes = data_off + (D << ps) + round_up(4 * D, 8);
+        hipStream_t end = himg && n_chunks > 1 ? c->side : stream;
+        if (!d_status)
+            CRUM_TRY(hipMemcpyAsync(h_status, d_out, sizeof(crum_status), hipMemcpyDeviceToHost,
+                                    end));
+        CRUM_TRY(hipEventRecord(c->ev_done, end));
+        c->partial_call = false;
+        if (end != stream)
+            CRUM_TRY(hipStreamWaitEvent(stream, c->ev_done, 0));
+        return CRUM_OK;
     } else {
         // ---- checked order: whole diff, scan with the capacity check, readback
         if (need_diff) {
@@ -839,33 +911,31 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
         }
         {
             Span sp(c, kTScan, stream);
-            CRUM_TRY(launch_bitmap(d_regs, n_regions, 0, W, d_flags, d_bitmap, stream));
-            CRUM_TRY(launch_scan(d_bitmap, 0, W, W, d_prefix, d_bounds, 1, d_reqs, 0, 1, d_out,
-                                 d_glob, capacity, 0, nullptr, stream));
+            HostNote note;
+            note.out = reinterpret_cast<uint64_t*>(rb);
+            note.count = h_counts;
+            CRUM_TRY(launch_scan(d_bitmap, 0, W, d_prefix, d_bounds, 1, d_reqs, 0, 1, d_out,
+                                 d_glob, capacity, 0, d_list, stream, flag_src, note));
         }
-        CRUM_TRY(hipMemcpyAsync(rb, d_out, 128, hipMemcpyDeviceToHost, stream));
-        CRUM_TRY(hipEventRecord(c->ev_count, stream));
-        CRUM_TRY(hipEventSynchronize(c->ev_count));
-        DevReqOut o;
+        if (wait_count(h_counts, nullptr, stream) != CRUM_OK)
+            return CRUM_EHIP;
+        crum_status o;
         std::memcpy(&o, rb, sizeof(o));
         if (o.code != CRUM_OK) {
             // ENOSPC: header, table and bitmap only; nothing packed or drained
             Span sp(c, kTHeader, stream);
             CRUM_TRY(launch_header(d_regs, d_reqs, 0, 1, hdr_blocks, d_out, d_bitmap, d_crcs,
-                                   staging, capacity, c->d_tabs, stream));
+                                   staging, capacity, c->d_tabs, stream, d_status));
             sp.end();
-            CRUM_TRY(hipMemcpyAsync(h_status, d_out, sizeof(crum_status), hipMemcpyDeviceToHost,
-                                    stream));
+            if (!d_status)
+                CRUM_TRY(hipMemcpyAsync(h_status, d_out, sizeof(crum_status),
+                                        hipMemcpyDeviceToHost, stream));
             CRUM_TRY(hipEventRecord(c->ev_done, stream));
             c->partial_call = false;
             return CRUM_OK;
         }
         D = o.n_dirty;
         image_bytes = o.image_bytes;
-        if (D) {
-            Span sp(c, kTScan, stream);
-            CRUM_TRY(launch_list(d_bitmap, d_prefix, 0, W, d_list, stream));
-        }
         // pack in slot chunks with the drain of each behind it
         uint64_t k0 = 0;
         uint64_t chunk_bytes = c->drain_chunk_bytes;
@@ -900,38 +970,31 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
         }
     }
 
-    // ---- header (with the CRC array; already enqueued in the chunked order),
-    // then the prefix and tail of the drain
-    if (!eager) {
+    // ---- diff-first order: header (with the CRC array), then the prefix and
+    // tail of the drain
+    {
         Span sp(c, kTHeader, stream);
         CRUM_TRY(launch_header(d_regs, d_reqs, 0, 1, hdr_blocks, d_out, d_bitmap, d_crcs,
-                               staging, capacity, c->d_tabs, stream));
+                               staging, capacity, c->d_tabs, stream, d_status));
     }
+    hipStream_t end = himg ? c->side : stream;
     if (himg) {
         CRUM_TRY(hipEventRecord(c->ev_hdr, stream));
         CRUM_TRY(hipStreamWaitEvent(c->side, c->ev_hdr, 0));
         const uint64_t tail = data_off + (D << ps);
         Span sp(c, kTDrain, c->side);
-        if (eager && n_chunks == 1) {
-            CRUM_TRY(hipMemcpyAsync(himg, staging, image_bytes, hipMemcpyDeviceToHost, c->side));
-        } else {
-            CRUM_TRY(hipMemcpyAsync(himg, staging, data_off, hipMemcpyDeviceToHost, c->side));
-            if (image_bytes > tail)
-                CRUM_TRY(hipMemcpyAsync(himg + tail, staging + tail, image_bytes - tail,
-                                        hipMemcpyDeviceToHost, c->side));
-        }
-        sp.end();
-        CRUM_TRY(hipMemcpyAsync(h_status, d_out, sizeof(crum_status), hipMemcpyDeviceToHost,
-                                c->side));
-        CRUM_TRY(hipEventRecord(c->ev_done, c->side));
-        c->partial_call = false;
-        CRUM_TRY(hipStreamWaitEvent(stream, c->ev_done, 0));
-    } else {
-        CRUM_TRY(hipMemcpyAsync(h_status, d_out, sizeof(crum_status), hipMemcpyDeviceToHost,
-                                stream));
-        CRUM_TRY(hipEventRecord(c->ev_done, stream));
-        c->partial_call = false;
+        CRUM_TRY(hipMemcpyAsync(himg, staging, data_off, hipMemcpyDeviceToHost, c->side));
+        if (image_bytes > tail)
+            CRUM_TRY(hipMemcpyAsync(himg + tail, staging + tail, image_bytes - tail,
+                                    hipMemcpyDeviceToHost, c->side));
     }
+    if (!d_status)
+        CRUM_TRY(hipMemcpyAsync(h_status, d_out, sizeof(crum_status), hipMemcpyDeviceToHost,
+                                end));
+    CRUM_TRY(hipEventRecord(c->ev_done, end));
+    c->partial_call = false;
+    if (end != stream)
+        CRUM_TRY(hipStreamWaitEvent(stream, c->ev_done, 0));
     return CRUM_OK;
 }
 
@@ -981,20 +1044,37 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
     DeviceGuard g(c->device);
 
     // ---- host-side header and table checks
-    std::vector<uint8_t> hdr_copy;
     const uint8_t* h = static_cast<const uint8_t*>(h_image);
+    uint64_t avail = image_bytes;
     if (image_bytes < 64)
         return restore_fail(h_status, CRUM_EFORMAT, 0, 0, image_bytes);
+    CRUM_TRY(settle(c));
+    std::vector<uint8_t> hdr_copy;
     if (!h) {
-        const uint64_t want = std::min<uint64_t>(image_bytes, 64 + 32ull * n_regions);
-        hdr_copy.resize(want);
-        CRUM_TRY(hipStreamSynchronize(stream));
-        CRUM_TRY(hipMemcpy(hdr_copy.data(), d_staging, want, hipMemcpyDeviceToHost));
-        h = hdr_copy.data();
+        avail = std::min<uint64_t>(image_bytes, 64 + 32ull * n_regions);
+        const uint64_t fetch = round_up(avail, 16);
+        if (fetch <= staging_bytes) {
+            // header and table into the pinned buffer, with a word behind them
+            // that the host watches
+            CRUM_TRY(ensure_pinned(c, fetch + 16));
+            uint64_t* done = reinterpret_cast<uint64_t*>(c->h_pin + fetch);
+            *done = kNoCount;
+            c->partial_call = true;
+            CRUM_TRY(hipStreamWaitEvent(stream, c->ev_done, 0));
+            CRUM_TRY(launch_begin(d_staging, c->h_pin, fetch, done, stream));
+            if (wait_count(done, nullptr, stream) != CRUM_OK)
+                return CRUM_EHIP;
+            c->partial_call = false;
+            h = c->h_pin;
+        } else {
+            hdr_copy.resize(avail);
+            CRUM_TRY(hipStreamSynchronize(stream));
+            CRUM_TRY(hipMemcpy(hdr_copy.data(), d_staging, avail, hipMemcpyDeviceToHost));
+            h = hdr_copy.data();
+        }
     }
     ImageInfo info;
-    const int rc = parse_image_prefix(h, hdr_copy.size() ? hdr_copy.size() : image_bytes,
-                                      image_bytes, regions, n_regions, &info);
+    const int rc = parse_image_prefix(h, avail, image_bytes, regions, n_regions, &info);
     const uint64_t G = info.G, D = info.D;
     if (rc != CRUM_OK)
         return restore_fail(h_status, rc, D, G, image_bytes);
@@ -1014,7 +1094,6 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
     const Layout L = make_layout(n_regions, 1, 0, W, W * 64, np_shift ? D << np_shift : 0, 1);
     CRUM_TRY(ensure_scratch(c, L.total));
     CRUM_TRY(ensure_pinned(c, L.upload_end));
-    CRUM_TRY(hipEventSynchronize(c->ev_upload));
     uint8_t* P = c->h_pin;
     std::memset(P, 0, L.upload_end);
     std::memcpy(P + L.regs, dregs.data(), sizeof(DevRegion) * n_regions);
@@ -1047,11 +1126,11 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
     uint32_t* d_partials = reinterpret_cast<uint32_t*>(S + L.partials);
     uint32_t* d_crcs = reinterpret_cast<uint32_t*>(S + L.crcs);
     uint8_t* staging = static_cast<uint8_t*>(d_staging);
-    const uint64_t* img_bitmap = reinterpret_cast<const uint64_t*>(staging + 64 + 32 * R);
+    uint64_t* img_bitmap = reinterpret_cast<uint64_t*>(staging + 64 + 32 * R);
 
     c->partial_call = true;
     CRUM_TRY(hipStreamWaitEvent(stream, c->ev_done, 0));
-    CRUM_TRY(hipMemcpyAsync(S, P, L.upload_end, hipMemcpyHostToDevice, stream));
+    CRUM_TRY(launch_begin(P, S, L.upload_end, nullptr, stream));
     CRUM_TRY(hipEventRecord(c->ev_upload, stream));
     if (h_image)
         CRUM_TRY(hipMemcpyAsync(staging, h_image, image_bytes, hipMemcpyHostToDevice, stream));
@@ -1059,8 +1138,8 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
         Span sp(c, kTScan, stream);
         CRUM_TRY(launch_restore_check(d_reqs, 1, header_blocks(n_regions, W, D), d_out, staging,
                                       c->d_tabs, d_glob, stream));
-        CRUM_TRY(launch_scan(img_bitmap, 0, W, W, d_prefix, nullptr, 1, d_reqs, 0, 1, d_out,
-                             d_glob, 0, 1, d_list, stream));
+        CRUM_TRY(launch_scan(img_bitmap, 0, W, d_prefix, nullptr, 1, d_reqs, 0, 1, d_out,
+                             d_glob, 0, 1, d_list, stream, FlagSource{}));
     }
     if (flags & CRUM_VERIFY) {
         Span sp(c, kTVerify, stream);
@@ -1082,8 +1161,11 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
                              ctx_pack_flags(c, (D << ps) * (flags & CRUM_UPDATE_SHADOW ? 2 : 1)),
                              (flags & CRUM_UPDATE_SHADOW) ? 1 : 0));
     }
-    CRUM_TRY(launch_restore_finish(d_out, 1, d_glob, stream));
-    CRUM_TRY(hipMemcpyAsync(h_status, d_out, sizeof(crum_status), hipMemcpyDeviceToHost, stream));
+    void* d_status = mapped_status(h_status);
+    CRUM_TRY(launch_restore_finish(d_out, 1, d_glob, stream, d_status));
+    if (!d_status)
+        CRUM_TRY(hipMemcpyAsync(h_status, d_out, sizeof(crum_status), hipMemcpyDeviceToHost,
+                                stream));
     CRUM_TRY(hipEventRecord(c->ev_done, stream));
     c->partial_call = false;
     return CRUM_OK;

@@ -119,7 +119,29 @@ struct SlotRange {
     uint64_t max_slots;  // upper bound on hi - lo (grid sizing)
 };
 
+// Pinned host words that a scan writes itself (each may be null), so that the
+// host need not wait for a copy or an event: used = the staging bytes the images
+// occupy; out = the first 32 bytes of request q0's results (final scans); count,
+// written last and with release order, = the running total of dirty pages.
+struct HostNote {
+    uint64_t* used = nullptr;
+    uint64_t* out = nullptr;
+    uint64_t* count = nullptr;
+};
+
+// Where a snapshot's bitmap words come from: the region table and the diff's
+// unit flags (regs null: the bitmap is there already).
+struct FlagSource {
+    const DevRegion* regs = nullptr;
+    uint32_t n_regs = 0;
+    const uint8_t* unit_flags = nullptr;
+};
+
 // Kernel launchers (crum_kernels.hip).  All enqueue on `s`.
+// Copies `bytes` (rounded up to 16; both ends 16-byte aligned) from or to pinned
+// host memory; with done (pinned), one workgroup copies and then stores 1 there.
+hipError_t launch_begin(const void* src, void* dst, uint64_t bytes, uint64_t* done,
+                        hipStream_t s);
 const CrcTables& crc_tables();  // the constants, in host memory
 // cand (may be null): bitmap over global pages; pages whose bit is clear are
 // flagged clean without being read (they are known to equal their shadow).
@@ -133,19 +155,20 @@ hipError_t launch_diff(const DevRegion* regs, uint32_t n_regs, uint64_t u0, uint
                        uint8_t* unit_flags, int blocks, int nontemporal, int prio,
                        hipStream_t s, const uint64_t* cand = nullptr,
                        uint64_t* stamp = nullptr, int group = 1);
-hipError_t launch_bitmap(const DevRegion* regs, uint32_t n_regs, uint64_t w0, uint64_t w1,
-                         const uint8_t* unit_flags, uint64_t* bitmap, hipStream_t s);
-// Scans words [w0, w1) continuing glob->running; writes the new running total
-// to *bounds_out when non-null.  With `final`, also fills the results of
+// Scans bitmap words [w0, w1) continuing glob->running; writes the new running
+// total to *bounds_out when non-null.  With fs, the words are first formed from
+// the diff's unit flags: inside the scan kernel when the range is short, else by a
+// k_bitmap launch.  With `final`, also fills the results of
 // requests [q0, q1) (whose words must all have been scanned), lays their
 // images out from glob->img_next and applies the capacity check: a group that
 // does not fit, and every later group, gets CRUM_ENOSPC.  With `list`, also
 // writes the slot list of the words (as launch_list): inside the scan kernel
 // when the range takes one pass, else by a launch_list behind it.
-hipError_t launch_scan(const uint64_t* bitmap, uint64_t w0, uint64_t w1, uint64_t n_words_total,
-                       uint32_t* prefix, uint64_t* bounds_out, int final, const DevRequest* reqs,
-                       uint32_t q0, uint32_t q1, DevReqOut* out, DevGlobal* glob,
-                       uint64_t capacity, int restore_mode, uint32_t* list, hipStream_t s);
+hipError_t launch_scan(uint64_t* bitmap, uint64_t w0, uint64_t w1, uint32_t* prefix,
+                       uint64_t* bounds_out, int final, const DevRequest* reqs, uint32_t q0,
+                       uint32_t q1, DevReqOut* out, DevGlobal* glob, uint64_t capacity,
+                       int restore_mode, uint32_t* list, hipStream_t s, const FlagSource& fs,
+                       const HostNote& note = HostNote{});
 hipError_t launch_list(const uint64_t* bitmap, const uint32_t* prefix, uint64_t w0, uint64_t w1,
                        uint32_t* list, hipStream_t s);
 // Pack, verify and scatter work on (slot, piece) items: a page of 2^ps bytes
@@ -172,11 +195,12 @@ hipError_t launch_finalize(int mode, const DevRegion* regs, uint32_t n_regs,
 uint32_t header_blocks(uint64_t n_regions, uint64_t n_words, uint64_t n_crcs);
 // `blocks` workgroups per request of [q0, q1).  Requests with ENOSPC get only
 // their prefix (header, table, bitmap), and only when it fits within
-// `capacity`.
+// `capacity`.  h_status (device-mapped pinned memory, may be null): gets the
+// first request's crum_status.
 hipError_t launch_header(const DevRegion* regs, const DevRequest* reqs, uint32_t q0, uint32_t q1,
                          uint32_t blocks, DevReqOut* out, const uint64_t* bitmap,
                          const uint32_t* crcs, uint8_t* staging, uint64_t capacity,
-                         const CrcTables* tabs, hipStream_t s);
+                         const CrcTables* tabs, hipStream_t s, void* h_status = nullptr);
 // Resets the launch-wide counters (graph-safe: a kernel, not a memset).
 hipError_t launch_plan_init(DevGlobal* glob, hipStream_t s);
 // Compact per-request results: {code, first_bad, n_dirty, total_pages,
@@ -189,6 +213,6 @@ hipError_t launch_restore_check(const DevRequest* reqs, uint32_t n_reqs, uint32_
                                 DevReqOut* out, const uint8_t* staging, const CrcTables* tabs,
                                 DevGlobal* glob, hipStream_t s);
 hipError_t launch_restore_finish(DevReqOut* out, uint32_t n_reqs, DevGlobal* glob,
-                                 hipStream_t s);
+                                 hipStream_t s, void* h_status = nullptr);
 
 }  // namespace crum

@@ -136,7 +136,7 @@ struct crum_ctx {
     size_t scratch_cap = 0;
     uint8_t* h_pin = nullptr;  // uploads, then readback area
     size_t pin_cap = 0;
-    hipEvent_t ev_upload = nullptr, ev_count = nullptr, ev_done = nullptr, ev_hdr = nullptr;
+    hipEvent_t ev_upload = nullptr, ev_done = nullptr, ev_hdr = nullptr;
     std::vector<hipEvent_t> ev_chunk;  // pack of chunk i done
     std::vector<hipEvent_t> ev_cnt;    // dirty count of chunk i read back
     LaunchShape shape{};
@@ -208,6 +208,16 @@ inline void ctx_add_timing(crum_ctx* c, int cls, double ms)
 }
 inline uint32_t ctx_chunk_growth(const crum_ctx* c) { return c->chunk_growth; }
 inline int ctx_pack_nt(const crum_ctx* c) { return c->pack_nt ? 1 : 0; }
+// What a pinned count holds until the scan has written it.
+constexpr uint64_t kNoCount = ~0ull;
+// Waits until *count, set to kNoCount before the scan's launch, holds its
+// total: a short spin (the host reads the word as soon as the scan has stored it),
+// then a wait for `ev`, recorded behind the scan, or for `s` when ev is null.
+int wait_count(const uint64_t* count, hipEvent_t ev, hipStream_t s);
+// The address at which kernels may write 32 bytes at h_status, or null when it
+// is not pinned memory that the device maps at the same address.
+void* mapped_status(crum_status* h_status);
+
 // Grid limit of a diff launch (0: none).  By default every wave of a launch
 // takes one unit (or group) and the dispatcher balances them: 8 GiB in 64 KiB
 // pages 2505 us persistent (8 workgroups per compute unit), 2440 this way, 1.5

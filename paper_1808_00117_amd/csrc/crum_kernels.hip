@@ -1,12 +1,13 @@
 // HIP kernels of the incremental snapshot (gfx950, wave64).
 //
-// Snapshot pipeline (one launch of each per chunk of the page space, or per
-// group of requests of a plan):
+// Snapshot pipeline (k_begin once a call, then one launch of each per chunk of
+// the page space, or per group of requests of a plan):
+//   k_begin   tables from pinned memory into scratch.
 //   k_diff    per diff unit (min(page, 4-16 KiB)): OR over 16-byte words of
 //             (cur ^ shadow) != 0, read with coalesced 128-bit loads and
 //             reduced across the wave by ballot; one flag byte per unit.
 //   k_bitmap  per 64 pages: OR of each page's unit flags, then one ballot
-//             gives the u64 bitmap word.
+//             gives the u64 bitmap word (short ranges: inside k_scan).
 //   k_scan    one workgroup: exclusive prefix sum of popcount(word) -> slot of
 //             each word's first dirty page, continuing a running total so the
 //             page space can be processed in chunks; at the end, per-request
@@ -257,6 +258,35 @@ __device__ __forceinline__ uint32_t columns_crc(const uint32_t* __restrict__ lds
            (uint32_t)__builtin_amdgcn_readlane((int)r, 16) ^
            (uint32_t)__builtin_amdgcn_readlane((int)r, 32) ^
            (uint32_t)__builtin_amdgcn_readlane((int)r, 48);
+}
+
+// ------------------------------------------------------------ k_begin
+
+// Copies n16 16-byte words between pinned host memory and the device: a call's
+// region and request tables and counters, or an image's header.  With `done`
+// (pinned), stores 1 there once its one workgroup's copy is visible to the host.
+__global__ __launch_bounds__(256) void k_begin(const u32x4* __restrict__ src,
+                                               u32x4* __restrict__ dst, uint64_t n16,
+                                               uint64_t* __restrict__ done)
+{
+    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n16;
+         i += (uint64_t)gridDim.x * 256)
+        dst[i] = src[i];
+    if (done) {
+        __threadfence_system();
+        __syncthreads();
+        if (threadIdx.x == 0)
+            __hip_atomic_store(done, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+hipError_t launch_begin(const void* src, void* dst, uint64_t bytes, uint64_t* done, hipStream_t s)
+{
+    const uint64_t n16 = (bytes + 15) / 16, need = (n16 + 255) / 256;
+    const unsigned nb = done ? 1u : (unsigned)(need < 1 ? 1 : need < 256 ? need : 256);
+    hipLaunchKernelGGL(k_begin, dim3(nb), dim3(256), 0, s, static_cast<const u32x4*>(src),
+                       static_cast<u32x4*>(dst), n16, done);
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------------ region lookup
@@ -510,10 +540,22 @@ __device__ __forceinline__ bool any_flag(const uint8_t* __restrict__ f, uint32_t
     return acc != 0;
 }
 
-// One wave per bitmap word in [w0, w1): lane l owns global page 64w + l, ORs
-// its unit flags (none are needed without a shadow: every page is dirty), and
-// a ballot forms the word.  Bound by latency; 2 MiB pages (128 flags each) took
-// 14-18 us a byte at a time and take 5.
+// Whether global page g exists in region R and is dirty: without a shadow every
+// page is (and no flag is looked at).
+__device__ __forceinline__ bool page_dirty(const DevRegion& R, uint64_t g,
+                                           const uint8_t* __restrict__ unit_flags)
+{
+    if (g < R.first_page || g - R.first_page >= (R.len >> R.page_shift))
+        return false;
+    const uint32_t upp_shift = R.page_shift - R.unit_shift;
+    return R.shadow == nullptr ||
+           any_flag(unit_flags + R.first_unit + ((g - R.first_page) << upp_shift), upp_shift);
+}
+
+// One wave per bitmap word in [w0, w1): lane l owns global page 64w + l, and a
+// ballot forms the word.  Bound by latency; 2 MiB pages (128 flags each) took
+// 14-18 us a byte at a time and take 5.  (Bits set by the diff itself with atomics
+// cost about 3 ns each: 75 us on 2.4 ms for 8 GiB with 5 % of the units dirty.)
 __global__ __launch_bounds__(256) void k_bitmap(const DevRegion* __restrict__ regs,
                                                 uint32_t n_regs, uint64_t w0, uint64_t w1,
                                                 const uint8_t* __restrict__ unit_flags,
@@ -525,29 +567,10 @@ __global__ __launch_bounds__(256) void k_bitmap(const DevRegion* __restrict__ re
     if (w >= w1)
         return;
     const uint64_t g = w * 64 + lane;
-    const uint32_t r = find_region<3>(regs, n_regs, g);
-    const DevRegion& R = regs[r];
-    bool dirty = false;
-    const uint64_t np = R.len >> R.page_shift;
-    if (g >= R.first_page && g - R.first_page < np) {
-        const uint64_t pi = g - R.first_page;
-        const uint32_t upp_shift = R.page_shift - R.unit_shift;
-        dirty = R.shadow == nullptr ||
-                any_flag(unit_flags + R.first_unit + (pi << upp_shift), upp_shift);
-    }
-    const uint64_t m = __ballot(dirty);
+    const uint64_t m =
+        __ballot(page_dirty(regs[find_region<3>(regs, n_regs, g)], g, unit_flags));
     if (lane == 0)
         bitmap[w] = m;
-}
-
-hipError_t launch_bitmap(const DevRegion* regs, uint32_t n_regs, uint64_t w0, uint64_t w1,
-                         const uint8_t* unit_flags, uint64_t* bitmap, hipStream_t s)
-{
-    if (w1 <= w0)
-        return hipSuccess;
-    hipLaunchKernelGGL(k_bitmap, dim3((unsigned)((w1 - w0 + 3) / 4)), dim3(256), 0, s, regs,
-                       n_regs, w0, w1, unit_flags, bitmap);
-    return hipGetLastError();
 }
 
 // ------------------------------------------------------------ k_scan
@@ -558,21 +581,59 @@ hipError_t launch_bitmap(const DevRegion* regs, uint32_t n_regs, uint64_t w0, ui
 // 5 us plus a launch gap) is faster.
 constexpr uint64_t kScanListWords = 512;
 
-__global__ __launch_bounds__(1024) void k_scan(const uint64_t* __restrict__ bitmap, uint64_t w0,
-                                               uint64_t w1, uint64_t n_words_total,
+// A range of at most this many words gets its bitmap from the unit flags in
+// k_scan itself: 16 waves with 8 words each in flight, one round, about 2 us against
+// 4.6 for a k_bitmap launch.  A second round would cost as much as the launch.
+constexpr uint64_t kScanFlagWords = 128;
+constexpr uint32_t kScanFlagRegions = 256;  // region starts held in LDS
+
+__global__ __launch_bounds__(1024) void k_scan(uint64_t* __restrict__ bitmap, uint64_t w0,
+                                               uint64_t w1,
                                                uint32_t* __restrict__ prefix,
                                                uint64_t* __restrict__ bounds_out, int final,
                                                const DevRequest* __restrict__ reqs, uint32_t q0,
                                                uint32_t q1, DevReqOut* __restrict__ out,
                                                DevGlobal* __restrict__ glob, uint64_t capacity,
-                                               int restore_mode, uint32_t* __restrict__ list)
+                                               int restore_mode, uint32_t* __restrict__ list,
+                                               HostNote note, FlagSource fs)
 {
     constexpr int V = 4;  // words per thread per pass
     static_assert(kScanListWords <= 1024 * V, "a fused list range takes one pass");
     __shared__ uint32_t wave_tot[16];
     __shared__ uint64_t s_words[kScanListWords];  // with `list`: the words and their
     __shared__ uint32_t s_pre[kScanListWords];    // prefixes, for the list below
+    __shared__ uint64_t s_tot[16];
+    __shared__ uint64_t s_used;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
+    if (fs.regs) {
+        __shared__ uint64_t s_first[kScanFlagRegions];
+        for (uint32_t i = tid; i < fs.n_regs; i += 1024)
+            s_first[i] = fs.regs[i].first_page;
+        __syncthreads();
+        bool dirty[kScanFlagWords / 16];
+#pragma unroll
+        for (uint32_t i = 0; i < kScanFlagWords / 16; ++i) {
+            const uint64_t g = (w0 + wv + 16 * i) * 64 + lane;
+            uint32_t lo = 0, hi = fs.n_regs;
+            while (hi - lo > 1) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (s_first[mid] <= g)
+                    lo = mid;
+                else
+                    hi = mid;
+            }
+            dirty[i] = w0 + wv + 16 * i < w1 && page_dirty(fs.regs[lo], g, fs.unit_flags);
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < kScanFlagWords / 16; ++i) {
+            const uint64_t m = __ballot(dirty[i]);
+            if (lane == 0 && w0 + wv + 16 * i < w1) {
+                bitmap[w0 + wv + 16 * i] = m;
+                s_words[wv + 16 * i] = m;
+            }
+        }
+        __syncthreads();
+    }
     uint32_t carry = (uint32_t)glob->running;
     for (uint64_t base = w0; base < w1; base += 1024 * V) {
         uint32_t c[V];
@@ -580,7 +641,7 @@ __global__ __launch_bounds__(1024) void k_scan(const uint64_t* __restrict__ bitm
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             const uint64_t w = base + (uint64_t)tid * V + v;
-            const uint64_t word = w < w1 ? bitmap[w] : 0ull;
+            const uint64_t word = w >= w1 ? 0ull : fs.regs ? s_words[w - w0] : bitmap[w];
             if (list && w < w1)
                 s_words[w - w0] = word;
             c[v] = (uint32_t)__popcll(word);
@@ -640,62 +701,117 @@ __global__ __launch_bounds__(1024) void k_scan(const uint64_t* __restrict__ bitm
     }
     __threadfence_block();
     __syncthreads();
+    if (final) {
+        // results of requests [q0, q1), a thread each; their images follow
+        // glob->img_next, 4 KiB aligned, so an image starts at the sum of the
+        // rounded sizes before it
+        uint64_t img0 = glob->img_next;
+        const bool full = glob->code != 0;
+        if (tid == 0)
+            s_used = glob->staging_used;
+        for (uint32_t base = q0; base < q1; base += 1024) {
+            const uint32_t q = base + tid;
+            uint64_t D = 0, p0 = 0, ib = 0, pages = 0;
+            if (q < q1) {
+                const DevRequest& Q = reqs[q];
+                // every word of these requests lies in [.., w1): a prefix at or past
+                // w1 is the running total, not a (not yet scanned) later word
+                const uint64_t a = Q.first_word, b = Q.first_word + Q.n_words;
+                p0 = a < w1 ? prefix[a] : carry;
+                D = (b < w1 ? prefix[b] : carry) - p0;
+                pages = Q.n_pages;
+                ib = Q.data_off + (D << Q.page_shift) + ((4 * D + 7) & ~7ull);
+            }
+            const uint64_t room = (ib + 4095) & ~4095ull;
+            uint64_t incl = room;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint64_t y = (uint64_t)__shfl_up((unsigned long long)incl, d);
+                if (lane >= (uint32_t)d)
+                    incl += y;
+            }
+            __syncthreads();
+            if (lane == 63)
+                s_tot[wv] = incl;
+            __syncthreads();
+            uint64_t img = img0 + incl - room;
+            for (uint32_t i = 0; i < 16; ++i) {
+                if (i < wv)
+                    img += s_tot[i];
+                img0 += s_tot[i];
+            }
+            if (q < q1) {
+                DevReqOut& O = out[q];
+                O.n_dirty = D;
+                O.total_pages = pages;
+                O.slot_base = p0;
+                O.acc[0] = O.acc[1] = O.acc[2] = O.acc[3] = 0;
+                if (!restore_mode) {
+                    O.code = 0;
+                    O.first_bad = 0;
+                    O.image_bytes = ib;
+                    O.img_base = img;
+                    if (q + 1 == q1)
+                        s_used = img + ib;
+                }
+            }
+        }
+        __syncthreads();
+        if (!restore_mode) {
+            const uint64_t used = s_used;
+            if (full || used > capacity) {
+                // the group does not fit: no request of it (or of a later group) is packed
+                for (uint32_t q = q0 + tid; q < q1; q += 1024)
+                    out[q].code = -2;  // CRUM_ENOSPC
+                if (tid == 0)
+                    glob->code = -2;
+            } else if (tid == 0) {
+                glob->staging_used = used;
+                glob->img_next = img0;
+            }
+        }
+        __threadfence_block();
+        __syncthreads();
+    }
     if (tid != 0)
         return;
     glob->running = carry;
+    if (final)
+        glob->total_dirty = carry;
     if (bounds_out)
         *bounds_out = carry;
-    if (!final)
-        return;
-    // results of requests [q0, q1); their images follow glob->img_next (4 KiB aligned)
-    uint64_t img = glob->img_next, used = glob->staging_used;
-    const bool full = glob->code != 0;
-    for (uint32_t q = q0; q < q1; ++q) {
-        const DevRequest& Q = reqs[q];
-        // every word of these requests lies in [.., w1): a prefix at or past
-        // w1 is the running total, not a (not yet scanned) later word
-        const uint64_t a = Q.first_word, b = Q.first_word + Q.n_words;
-        const uint64_t p0 = a < w1 ? prefix[a] : carry;
-        const uint64_t p1 = b < w1 ? prefix[b] : carry;
-        const uint64_t D = p1 - p0;
-        DevReqOut& O = out[q];
-        O.n_dirty = D;
-        O.total_pages = Q.n_pages;
-        O.slot_base = p0;
-        O.acc[0] = O.acc[1] = O.acc[2] = O.acc[3] = 0;
-        if (!restore_mode) {
-            const uint64_t ib = Q.data_off + (D << Q.page_shift) + ((4 * D + 7) & ~7ull);
-            O.code = 0;
-            O.first_bad = 0;
-            O.image_bytes = ib;
-            O.img_base = img;
-            used = img + ib;
-            img = (used + 4095) & ~4095ull;
-        }
+    if (note.used)
+        __hip_atomic_store(note.used, glob->staging_used, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    if (note.out && final) {
+        const uint64_t* o = reinterpret_cast<const uint64_t*>(&out[q0]);
+        for (int i = 0; i < 4; ++i)
+            __hip_atomic_store(note.out + i, o[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
-    glob->total_dirty = carry;
-    if (!restore_mode) {
-        if (full || used > capacity) {
-            // the group does not fit: no request of it (or of a later group) is packed
-            glob->code = -2;  // CRUM_ENOSPC
-            for (uint32_t q = q0; q < q1; ++q)
-                out[q].code = -2;
-        } else {
-            glob->staging_used = used;
-            glob->img_next = img;
-        }
-    }
+    if (note.count)
+        __hip_atomic_store(note.count, (uint64_t)carry, __ATOMIC_RELEASE,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-hipError_t launch_scan(const uint64_t* bitmap, uint64_t w0, uint64_t w1, uint64_t n_words_total,
-                       uint32_t* prefix, uint64_t* bounds_out, int final, const DevRequest* reqs,
-                       uint32_t q0, uint32_t q1, DevReqOut* out, DevGlobal* glob,
-                       uint64_t capacity, int restore_mode, uint32_t* list, hipStream_t s)
+hipError_t launch_scan(uint64_t* bitmap, uint64_t w0, uint64_t w1, uint32_t* prefix,
+                       uint64_t* bounds_out, int final, const DevRequest* reqs, uint32_t q0,
+                       uint32_t q1, DevReqOut* out, DevGlobal* glob, uint64_t capacity,
+                       int restore_mode, uint32_t* list, hipStream_t s, const FlagSource& fs,
+                       const HostNote& note)
 {
+    FlagSource in = fs;
+    if (fs.regs && w1 > w0 && (w1 - w0 > kScanFlagWords || fs.n_regs > kScanFlagRegions)) {
+        hipLaunchKernelGGL(k_bitmap, dim3((unsigned)((w1 - w0 + 3) / 4)), dim3(256), 0, s,
+                           fs.regs, fs.n_regs, w0, w1, fs.unit_flags, bitmap);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+        in.regs = nullptr;
+    }
     const bool fused = list && w1 - w0 <= kScanListWords;
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, bitmap, w0, w1, n_words_total, prefix,
-                       bounds_out, final, reqs, q0, q1, out, glob, capacity, restore_mode,
-                       fused ? list : nullptr);
+    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, bitmap, w0, w1, prefix, bounds_out,
+                       final, reqs, q0, q1, out, glob, capacity, restore_mode,
+                       fused ? list : nullptr, note, in);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && list && !fused)
         e = launch_list(bitmap, prefix, w0, w1, list, s);
@@ -1261,7 +1377,8 @@ __global__ __launch_bounds__(256) void k_header(const DevRegion* __restrict__ re
                                                 const uint32_t* __restrict__ crcs,
                                                 uint8_t* __restrict__ staging, uint32_t q0,
                                                 uint32_t nb, uint64_t capacity,
-                                                const CrcTables* __restrict__ tabs)
+                                                const CrcTables* __restrict__ tabs,
+                                                uint64_t* __restrict__ h_status)
 {
     __shared__ __attribute__((aligned(16))) uint32_t lds[kCrcLdsWords];
     __shared__ uint32_t red[8];
@@ -1271,6 +1388,8 @@ __global__ __launch_bounds__(256) void k_header(const DevRegion* __restrict__ re
     const uint32_t q = q0 + blockIdx.x / nb, b = blockIdx.x % nb;
     const DevRequest& Q = reqs[q];
     DevReqOut& O = out[q];
+    if (h_status && blockIdx.x == 0 && threadIdx.x < 4)
+        h_status[threadIdx.x] = reinterpret_cast<const uint64_t*>(&O)[threadIdx.x];
     if (O.code != 0 && O.img_base + Q.data_off > capacity)
         return;  // no room even for the prefix
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
@@ -1412,14 +1531,15 @@ uint32_t header_blocks(uint64_t n_regions, uint64_t n_words, uint64_t n_crcs)
 hipError_t launch_header(const DevRegion* regs, const DevRequest* reqs, uint32_t q0, uint32_t q1,
                          uint32_t blocks, DevReqOut* out, const uint64_t* bitmap,
                          const uint32_t* crcs, uint8_t* staging, uint64_t capacity,
-                         const CrcTables* tabs, hipStream_t s)
+                         const CrcTables* tabs, hipStream_t s, void* h_status)
 {
     if (q1 <= q0)
         return hipSuccess;
     if (blocks == 0 || (uint64_t)(q1 - q0) * blocks > 0x7FFFFFFFull)
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_header, dim3((q1 - q0) * blocks), dim3(256), 0, s, regs, reqs, out,
-                       bitmap, crcs, staging, q0, blocks, capacity, tabs);
+                       bitmap, crcs, staging, q0, blocks, capacity, tabs,
+                       static_cast<uint64_t*>(h_status));
     return hipGetLastError();
 }
 
@@ -1590,24 +1710,34 @@ hipError_t launch_restore_check(const DevRequest* reqs, uint32_t n_reqs, uint32_
     return hipGetLastError();
 }
 
-__global__ void k_restore_finish(DevReqOut* __restrict__ out, DevGlobal* __restrict__ glob)
+// Final code of a restore; with h_status, the status goes there too.
+__global__ void k_restore_finish(DevReqOut* __restrict__ out, DevGlobal* __restrict__ glob,
+                                 uint64_t* __restrict__ h_status)
 {
     DevReqOut& O = out[0];
+    int32_t code = 0;
+    uint32_t bad = 0;
     if (glob->fmt_bad) {
-        O.code = -4;  // CRUM_EFORMAT
-        O.first_bad = 0;
+        code = -4;  // CRUM_EFORMAT
     } else if (glob->crc_bad != kNoBad) {
-        O.code = -3;  // CRUM_ECRC
-        O.first_bad = glob->crc_bad;
-    } else {
-        O.code = 0;
-        O.first_bad = 0;
+        code = -3;  // CRUM_ECRC
+        bad = glob->crc_bad;
+    }
+    O.code = code;
+    O.first_bad = bad;
+    if (h_status) {
+        h_status[0] = (uint32_t)code | (uint64_t)bad << 32;
+        h_status[1] = O.n_dirty;
+        h_status[2] = O.total_pages;
+        h_status[3] = O.image_bytes;
     }
 }
 
-hipError_t launch_restore_finish(DevReqOut* out, uint32_t, DevGlobal* glob, hipStream_t s)
+hipError_t launch_restore_finish(DevReqOut* out, uint32_t, DevGlobal* glob, hipStream_t s,
+                                 void* h_status)
 {
-    hipLaunchKernelGGL(k_restore_finish, dim3(1), dim3(1), 0, s, out, glob);
+    hipLaunchKernelGGL(k_restore_finish, dim3(1), dim3(1), 0, s, out, glob,
+                       static_cast<uint64_t*>(h_status));
     return hipGetLastError();
 }
 

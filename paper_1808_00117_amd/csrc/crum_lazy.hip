@@ -423,8 +423,8 @@ int crum_lazy_open(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
     DevGlobal* d_glob = reinterpret_cast<DevGlobal*>(M + z->o_glob);
     uint32_t* d_prefix = reinterpret_cast<uint32_t*>(M + z->o_prefix);
     uint32_t* d_list = reinterpret_cast<uint32_t*>(M + z->o_list);
-    const uint64_t* img_bitmap =
-        reinterpret_cast<const uint64_t*>(z->staging + 64 + 32 * I.R);
+    uint64_t* img_bitmap =
+        reinterpret_cast<uint64_t*>(z->staging + 64 + 32 * I.R);
     const uint64_t pages_end = I.data_off + (D << I.ps);
     auto fail = [&]() {
         (void)hipStreamSynchronize(stream);
@@ -438,8 +438,8 @@ int crum_lazy_open(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
         launch_restore_check(d_req, 1, header_blocks(n_regions, W, D), d_out, z->staging,
                              ctx_tables(c), d_glob, stream) !=
             hipSuccess ||
-        launch_scan(img_bitmap, 0, W, W, d_prefix, nullptr, 1, d_req, 0, 1, d_out, d_glob, 0, 1,
-                    d_list, stream) != hipSuccess ||
+        launch_scan(img_bitmap, 0, W, d_prefix, nullptr, 1, d_req, 0, 1, d_out, d_glob, 0, 1,
+                    d_list, stream, FlagSource{}) != hipSuccess ||
         enqueue_status(z, h_status, stream) != hipSuccess ||
         record_done(z, stream) != hipSuccess ||
         // page copies start after everything the caller enqueued before

@@ -181,7 +181,7 @@ int crum_snapshot_noalloc(crum_ctx* c, const crum_region* regions, uint32_t n_re
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     DeviceGuard g(c->device);
     // the previous upload from the pinned buffer must have left it
-    CRUM_TRY_C(hipEventSynchronize(c->ev_upload));
+    CRUM_TRY_C(c->partial_call ? hipDeviceSynchronize() : hipEventSynchronize(c->ev_upload));
     uint8_t* P = c->na_pin;
     std::memset(P, 0, L.upload_end);
     uint64_t n_pages = 0, n_units2 = 0;
@@ -220,45 +220,50 @@ int crum_snapshot_noalloc(crum_ctx* c, const crum_region* regions, uint32_t n_re
     uint8_t* rb = P + rb_off;
     const uint32_t hdr_blocks = header_blocks(n_regions, W, G);
 
+    uint64_t* h_count = reinterpret_cast<uint64_t*>(rb + 64);
+    *h_count = kNoCount;
+    void* d_status = mapped_status(h_status);
+    const FlagSource flag_src{d_regs, n_regions, d_flags};
+    HostNote note;
+    note.out = reinterpret_cast<uint64_t*>(rb);
+    note.count = h_count;
+
     // after this context's previous call (whose kernels may still use the array)
     c->partial_call = true;
     CRUM_TRY_C(hipStreamWaitEvent(stream, c->ev_done, 0));
-    CRUM_TRY_C(hipMemcpyAsync(S, P, L.upload_end, hipMemcpyHostToDevice, stream));
-    CRUM_TRY_C(hipEventRecord(c->ev_upload, stream));
+    CRUM_TRY_C(launch_begin(P, S, L.upload_end, nullptr, stream));
     if (any_shadow(regions, n_regions))
-        CRUM_TRY_C(launch_diff(d_regs, n_regions, 0, n_units, d_flags, ctx_diff_blocks(c, false),
-                               c->diff_nt, c->diff_prio, stream, nullptr, nullptr,
-                               ctx_diff_group(c, us)));
-    CRUM_TRY_C(launch_bitmap(d_regs, n_regions, 0, W, d_flags, d_bitmap, stream));
-    CRUM_TRY_C(launch_scan(d_bitmap, 0, W, W, d_prefix, d_bounds, 1, d_reqs, 0, 1, d_out, d_glob,
-                           capacity, 0, nullptr, stream));
-    CRUM_TRY_C(hipMemcpyAsync(rb, d_out, 128, hipMemcpyDeviceToHost, stream));
-    CRUM_TRY_C(hipEventRecord(c->ev_count, stream));
-    CRUM_TRY_C(hipEventSynchronize(c->ev_count));
-    DevReqOut o;
-    std::memcpy(&o, rb, sizeof(o));
-    uint64_t copy_bytes = 0;  // ENOSPC: the prefix stays in staging, as crum_snapshot's
-    if (o.code == CRUM_OK) {
-        const uint64_t D = o.n_dirty;
-        if (D) {
-            CRUM_TRY_C(launch_list(d_bitmap, d_prefix, 0, W, d_list, stream));
-            const SlotRange sr{0, D, nullptr, 0, D};
-            CRUM_TRY_C(launch_pack(kModePack, d_regs, n_regions, d_reqs, d_out, d_list, sr,
-                                   np_shift, pc_shift, d_flags, staging, d_crcs, d_partials,
-                                   c->d_tabs, d_glob, c->shape.pack_blocks, stream,
-                                   ctx_pack_flags(c, h_image ? 0 : G << ps)));
-            CRUM_TRY_C(launch_finalize(kModePack, d_regs, n_regions, d_reqs, d_out, d_list, sr,
-                                       np_shift, pc_shift, d_partials, d_crcs, staging, d_glob,
-                                       c->d_tabs, stream));
-        }
-        copy_bytes = o.image_bytes;
-    }
+        CRUM_TRY_C(launch_diff(d_regs, n_regions, 0, n_units, d_flags, ctx_diff_blocks(c, false), c->diff_nt, c->diff_prio, stream,
+                               nullptr, nullptr, ctx_diff_group(c, us)));
+    CRUM_TRY_C(launch_scan(d_bitmap, 0, W, d_prefix, d_bounds, 1, d_reqs, 0, 1, d_out, d_glob,
+                           capacity, 0, d_list, stream, flag_src, note));
+    // the kernels behind the scan take the slot count and the capacity check's
+    // result from the device (nothing is packed when the image does not fit)
+    const SlotRange sr{0, 0, d_bounds, 0, G};
+    CRUM_TRY_C(launch_pack(kModePack, d_regs, n_regions, d_reqs, d_out, d_list, sr, np_shift,
+                           pc_shift, d_flags, staging, d_crcs, d_partials, c->d_tabs, d_glob,
+                           c->shape.pack_blocks, stream,
+                           ctx_pack_flags(c, h_image ? 0 : G << ps)));
+    CRUM_TRY_C(launch_finalize(kModePack, d_regs, n_regions, d_reqs, d_out, d_list, sr, np_shift,
+                               pc_shift, d_partials, d_crcs, staging, d_glob, c->d_tabs,
+                               stream));
     CRUM_TRY_C(launch_header(d_regs, d_reqs, 0, 1, hdr_blocks, d_out, d_bitmap, d_crcs, staging,
-                             capacity, c->d_tabs, stream));
-    if (h_image && copy_bytes)
-        CRUM_TRY_C(hipMemcpyAsync(h_image, staging, copy_bytes, hipMemcpyDeviceToHost, stream));
-    CRUM_TRY_C(hipMemcpyAsync(h_status, d_out, sizeof(crum_status), hipMemcpyDeviceToHost,
-                              stream));
+                             capacity, c->d_tabs, stream, d_status));
+    if (h_image) {
+        if (wait_count(h_count, nullptr, stream) != CRUM_OK)
+            return CRUM_EHIP;
+        crum_status o;
+        std::memcpy(&o, rb, sizeof(o));
+        // ENOSPC: the prefix stays in staging, as crum_snapshot's
+        if (o.code == CRUM_OK)
+            CRUM_TRY_C(hipMemcpyAsync(h_image, staging, o.image_bytes, hipMemcpyDeviceToHost,
+                                      stream));
+    } else {
+        CRUM_TRY_C(hipEventRecord(c->ev_upload, stream));
+    }
+    if (!d_status)
+        CRUM_TRY_C(hipMemcpyAsync(h_status, d_out, sizeof(crum_status), hipMemcpyDeviceToHost,
+                                  stream));
     CRUM_TRY_C(hipEventRecord(c->ev_done, stream));
     c->partial_call = false;
     return CRUM_OK;

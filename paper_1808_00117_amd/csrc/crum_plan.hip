@@ -301,33 +301,32 @@ int crum_plan_create(crum_ctx* c, const crum_request* reqs, uint32_t n_reqs, voi
         const uint64_t w0 = q0 < n_reqs ? dreq[q0].first_word : W;
         const uint64_t w1 = q1 < n_reqs ? dreq[q1].first_word : W;
         const uint64_t u0 = req_unit0[q0], u1 = req_unit0[q1];
-        p->diff_units.push_back(u1 - u0);
         uint32_t hdr_blocks = 1, min_us = 64;
+        bool shadowed = p->diff_timed;  // a timed plan counts a diff for every group
         for (uint32_t q = q0; q < q1; ++q) {
+            shadowed |= (dreq[q].flags & kReqShadow) != 0;
             hdr_blocks = std::max(hdr_blocks, header_blocks(dreq[q].n_regions, dreq[q].n_words,
                                                             dreq[q].n_pages));
             if (dreq[q].n_regions)
                 min_us = std::min(min_us, dregs[dreq[q].first_region].unit_shift);
         }
+        p->diff_units.push_back(shadowed ? u1 - u0 : 0);
         hipStream_t s = p->cap_stream;
         if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) != hipSuccess)
             return fail(CRUM_EHIP);
         hipError_t e = hipSuccess;
         if (gi == 0)
             e = launch_plan_init(d_glob, s);
-        if (e == hipSuccess)
-            e = launch_diff(d_regs, p->n_regs, u0, u1, d_flags, ctx_diff_blocks(c, false),
-                            ctx_diff_nt(c), ctx_diff_prio(c), s, nullptr,
-                            p->d_stamp ? p->d_stamp + 2 * gi : nullptr,
+        if (e == hipSuccess && shadowed)
+            e = launch_diff(d_regs, p->n_regs, u0, u1, d_flags, ctx_diff_blocks(c, false), ctx_diff_nt(c), ctx_diff_prio(c), s,
+                            nullptr, p->d_stamp ? p->d_stamp + 2 * gi : nullptr,
                             ctx_diff_group(c, min_us));
+        const FlagSource flag_src{d_regs, p->n_regs, d_flags};
+        HostNote note;
+        note.used = reinterpret_cast<uint64_t*>(p->h_rb + 8 * gi);
         if (e == hipSuccess)
-            e = launch_bitmap(d_regs, p->n_regs, w0, w1, d_flags, d_bitmap, s);
-        if (e == hipSuccess)
-            e = launch_scan(d_bitmap, w0, w1, W, d_prefix, d_bounds + gi, 1, d_reqs, q0, q1,
-                            d_out, d_glob, capacity, 0, d_list, s);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(p->h_rb + 8 * gi, &d_glob->staging_used, 8,
-                               hipMemcpyDeviceToHost, s);
+            e = launch_scan(d_bitmap, w0, w1, d_prefix, d_bounds + gi, 1, d_reqs, q0, q1,
+                            d_out, d_glob, capacity, 0, d_list, s, flag_src, note);
         SlotRange sr{0, 0, d_bounds, (uint32_t)gi, (w1 - w0) * 64};
         if (e == hipSuccess)
             e = launch_pack(kModePack, d_regs, p->n_regs, d_reqs, d_out, d_list, sr, np_shift,
