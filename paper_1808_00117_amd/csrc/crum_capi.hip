@@ -912,16 +912,13 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
         {
             Span sp(c, kTScan, stream);
             HostNote note;
-            note.out = reinterpret_cast<uint64_t*>(rb);
             note.count = h_counts;
             CRUM_TRY(launch_scan(d_bitmap, 0, W, d_prefix, d_bounds, 1, d_reqs, 0, 1, d_out,
                                  d_glob, capacity, 0, d_list, stream, flag_src, note));
         }
         if (wait_count(h_counts, nullptr, stream) != CRUM_OK)
             return CRUM_EHIP;
-        crum_status o;
-        std::memcpy(&o, rb, sizeof(o));
-        if (o.code != CRUM_OK) {
+        if (h_counts[0] & kCountNoSpace) {
             // ENOSPC: header, table and bitmap only; nothing packed or drained
             Span sp(c, kTHeader, stream);
             CRUM_TRY(launch_header(d_regs, d_reqs, 0, 1, hdr_blocks, d_out, d_bitmap, d_crcs,
@@ -934,8 +931,8 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
             c->partial_call = false;
             return CRUM_OK;
         }
-        D = o.n_dirty;
-        image_bytes = o.image_bytes;
+        D = h_counts[0];
+        image_bytes = data_off + (D << ps) + round_up(4 * D, 8);
         // pack in slot chunks with the drain of each behind it
         uint64_t k0 = 0;
         uint64_t chunk_bytes = c->drain_chunk_bytes;

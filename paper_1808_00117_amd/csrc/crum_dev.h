@@ -121,11 +121,11 @@ struct SlotRange {
 
 // Pinned host words that a scan writes itself (each may be null), so that the
 // host need not wait for a copy or an event: used = the staging bytes the images
-// occupy; out = the first 32 bytes of request q0's results (final scans); count,
-// written last and with release order, = the running total of dirty pages.
+// occupy; count = the running total of dirty pages, with kCountNoSpace when a
+// table's one request does not fit.
+constexpr uint64_t kCountNoSpace = 1ull << 63;
 struct HostNote {
     uint64_t* used = nullptr;
-    uint64_t* out = nullptr;
     uint64_t* count = nullptr;
 };
 

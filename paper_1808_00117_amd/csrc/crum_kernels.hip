@@ -582,10 +582,12 @@ __global__ __launch_bounds__(256) void k_bitmap(const DevRegion* __restrict__ re
 constexpr uint64_t kScanListWords = 512;
 
 // A range of at most this many words gets its bitmap from the unit flags in
-// k_scan itself: 16 waves with 8 words each in flight, one round, about 2 us against
-// 4.6 for a k_bitmap launch.  A second round would cost as much as the launch.
+// k_scan itself: 16 waves with 8 words each in flight, one round of three
+// dependent reads, against a k_bitmap launch of 4.6 us.  A second round would cost
+// as much as the launch, and so would a search over more regions than a wave
+// has lanes to hold their starts.
 constexpr uint64_t kScanFlagWords = 128;
-constexpr uint32_t kScanFlagRegions = 256;  // region starts held in LDS
+constexpr uint32_t kScanFlagRegions = 64;
 
 __global__ __launch_bounds__(1024) void k_scan(uint64_t* __restrict__ bitmap, uint64_t w0,
                                                uint64_t w1,
@@ -605,36 +607,43 @@ __global__ __launch_bounds__(1024) void k_scan(uint64_t* __restrict__ bitmap, ui
     __shared__ uint64_t s_tot[16];
     __shared__ uint64_t s_used;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
+    // what the end needs, read before the words (single: one request whose last
+    // word is the range's, as in every call but a plan's)
+    const DevRequest& Q0 = reqs[q0];
+    const bool single = final && q1 == q0 + 1 && Q0.first_word + Q0.n_words == w1;
+    const uint32_t carry0 = (uint32_t)glob->running;
+    const uint64_t img_next = glob->img_next, staged = glob->staging_used;
+    const bool full = glob->code != 0;
+    uint64_t p_first = carry0;
+    if (single && Q0.first_word != w0)
+        p_first = prefix[Q0.first_word];  // written by an earlier launch
     if (fs.regs) {
-        __shared__ uint64_t s_first[kScanFlagRegions];
-        for (uint32_t i = tid; i < fs.n_regs; i += 1024)
-            s_first[i] = fs.regs[i].first_page;
-        __syncthreads();
-        bool dirty[kScanFlagWords / 16];
+        const uint64_t first = lane < fs.n_regs ? fs.regs[lane].first_page : ~0ull;
+        uint32_t r[kScanFlagWords / 16] = {};
+        for (uint32_t k = 1; k < fs.n_regs; ++k) {
+            const uint64_t f =
+                (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)first, (int)k) |
+                (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(first >> 32), (int)k)
+                    << 32;
 #pragma unroll
-        for (uint32_t i = 0; i < kScanFlagWords / 16; ++i) {
-            const uint64_t g = (w0 + wv + 16 * i) * 64 + lane;
-            uint32_t lo = 0, hi = fs.n_regs;
-            while (hi - lo > 1) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (s_first[mid] <= g)
-                    lo = mid;
-                else
-                    hi = mid;
-            }
-            dirty[i] = w0 + wv + 16 * i < w1 && page_dirty(fs.regs[lo], g, fs.unit_flags);
+            for (uint32_t i = 0; i < kScanFlagWords / 16; ++i)
+                r[i] += f <= (w0 + wv + 16 * i) * 64 + lane;
         }
 #pragma unroll
         for (uint32_t i = 0; i < kScanFlagWords / 16; ++i) {
-            const uint64_t m = __ballot(dirty[i]);
-            if (lane == 0 && w0 + wv + 16 * i < w1) {
-                bitmap[w0 + wv + 16 * i] = m;
-                s_words[wv + 16 * i] = m;
+            const uint64_t w = w0 + wv + 16 * i;
+            if (w < w1) {
+                const uint64_t m =
+                    __ballot(page_dirty(fs.regs[r[i]], w * 64 + lane, fs.unit_flags));
+                if (lane == 0) {
+                    bitmap[w] = m;
+                    s_words[w - w0] = m;
+                }
             }
         }
         __syncthreads();
     }
-    uint32_t carry = (uint32_t)glob->running;
+    uint32_t carry = carry0;
     for (uint64_t base = w0; base < w1; base += 1024 * V) {
         uint32_t c[V];
         uint32_t local = 0;
@@ -699,16 +708,15 @@ __global__ __launch_bounds__(1024) void k_scan(uint64_t* __restrict__ bitmap, ui
             }
         }
     }
-    __threadfence_block();
-    __syncthreads();
-    if (final) {
+    if (final && !single) {
+        __threadfence_block();
+        __syncthreads();
         // results of requests [q0, q1), a thread each; their images follow
         // glob->img_next, 4 KiB aligned, so an image starts at the sum of the
         // rounded sizes before it
-        uint64_t img0 = glob->img_next;
-        const bool full = glob->code != 0;
+        uint64_t img0 = img_next;
         if (tid == 0)
-            s_used = glob->staging_used;
+            s_used = staged;
         for (uint32_t base = q0; base < q1; base += 1024) {
             const uint32_t q = base + tid;
             uint64_t D = 0, p0 = 0, ib = 0, pages = 0;
@@ -780,17 +788,40 @@ __global__ __launch_bounds__(1024) void k_scan(uint64_t* __restrict__ bitmap, ui
         glob->total_dirty = carry;
     if (bounds_out)
         *bounds_out = carry;
-    if (note.used)
+    bool no_space = false;
+    if (single) {
+        DevReqOut o = out[q0];  // a restore's sizes and place are there already
+        o.n_dirty = carry - p_first;
+        o.total_pages = Q0.n_pages;
+        o.slot_base = p_first;
+        o.acc[0] = o.acc[1] = o.acc[2] = o.acc[3] = 0;
+        if (!restore_mode) {
+            o.first_bad = 0;
+            o.image_bytes =
+                Q0.data_off + (o.n_dirty << Q0.page_shift) + ((4 * o.n_dirty + 7) & ~7ull);
+            o.img_base = img_next;
+            const uint64_t used = img_next + o.image_bytes;
+            o.code = full || used > capacity ? -2 : 0;  // CRUM_ENOSPC: nothing is packed
+            if (o.code == 0) {
+                glob->staging_used = used;
+                glob->img_next = (used + 4095) & ~4095ull;
+            } else {
+                glob->code = -2;
+            }
+            if (note.used)
+                __hip_atomic_store(note.used, o.code == 0 ? used : staged, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        out[q0] = o;
+        no_space = o.code != 0 && !restore_mode;
+    } else if (note.used) {
         __hip_atomic_store(note.used, glob->staging_used, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_SYSTEM);
-    if (note.out && final) {
-        const uint64_t* o = reinterpret_cast<const uint64_t*>(&out[q0]);
-        for (int i = 0; i < 4; ++i)
-            __hip_atomic_store(note.out + i, o[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
+    // one relaxed word: a release would write the L2 back first
     if (note.count)
-        __hip_atomic_store(note.count, (uint64_t)carry, __ATOMIC_RELEASE,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(note.count, carry | (no_space ? kCountNoSpace : 0ull),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 hipError_t launch_scan(uint64_t* bitmap, uint64_t w0, uint64_t w1, uint32_t* prefix,

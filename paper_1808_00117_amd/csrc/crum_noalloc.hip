@@ -220,12 +220,11 @@ int crum_snapshot_noalloc(crum_ctx* c, const crum_region* regions, uint32_t n_re
     uint8_t* rb = P + rb_off;
     const uint32_t hdr_blocks = header_blocks(n_regions, W, G);
 
-    uint64_t* h_count = reinterpret_cast<uint64_t*>(rb + 64);
+    uint64_t* h_count = reinterpret_cast<uint64_t*>(rb);
     *h_count = kNoCount;
     void* d_status = mapped_status(h_status);
     const FlagSource flag_src{d_regs, n_regions, d_flags};
     HostNote note;
-    note.out = reinterpret_cast<uint64_t*>(rb);
     note.count = h_count;
 
     // after this context's previous call (whose kernels may still use the array)
@@ -252,12 +251,12 @@ int crum_snapshot_noalloc(crum_ctx* c, const crum_region* regions, uint32_t n_re
     if (h_image) {
         if (wait_count(h_count, nullptr, stream) != CRUM_OK)
             return CRUM_EHIP;
-        crum_status o;
-        std::memcpy(&o, rb, sizeof(o));
         // ENOSPC: the prefix stays in staging, as crum_snapshot's
-        if (o.code == CRUM_OK)
-            CRUM_TRY_C(hipMemcpyAsync(h_image, staging, o.image_bytes, hipMemcpyDeviceToHost,
-                                      stream));
+        const uint64_t D = *h_count;
+        if (!(D & kCountNoSpace))
+            CRUM_TRY_C(hipMemcpyAsync(h_image, staging,
+                                      data_off + (D << ps) + round_up(4 * D, 8),
+                                      hipMemcpyDeviceToHost, stream));
     } else {
         CRUM_TRY_C(hipEventRecord(c->ev_upload, stream));
     }
