@@ -518,8 +518,8 @@ int crum_ctx_timing_reset(crum_ctx* ctx);
  * h_image into d_staging (at their image offsets), CRC-checked with
  * CRUM_VERIFY, and written to the page (and its shadow with
  * CRUM_UPDATE_SHADOW), in runs of consecutive packed pages, one copy per run
- * (runs of up to 2 MiB are read in place from h_image when the device maps
- * it at the same address, as hipHostMalloc memory is).
+ * (runs of up to 2 MiB are read by the kernels from h_image when the device
+ * maps it at the same address, as hipHostMalloc memory is).
  *
  * Verification is per fetched run: a run that fails is not written, and
  * neither is anything fetched after it; pages written before stay written.

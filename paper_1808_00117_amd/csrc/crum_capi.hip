@@ -766,7 +766,7 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
     // the previous call on this context may still be draining from scratch
     c->partial_call = true;  // cleared once ev_done is recorded
     CRUM_TRY(hipStreamWaitEvent(stream, c->ev_done, 0));
-    CRUM_TRY(launch_begin(P, S, L.upload_end, nullptr, stream));
+    CRUM_TRY(launch_begin(CopyList{}.add(0, P, S, L.upload_end), nullptr, stream));
     // a call that waits for a count knows that its tables have been read
     if (direct || (eager && !h_image))
         CRUM_TRY(hipEventRecord(c->ev_upload, stream));
@@ -1058,7 +1058,7 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
             *done = kNoCount;
             c->partial_call = true;
             CRUM_TRY(hipStreamWaitEvent(stream, c->ev_done, 0));
-            CRUM_TRY(launch_begin(d_staging, c->h_pin, fetch, done, stream));
+            CRUM_TRY(launch_begin(CopyList{}.add(0, d_staging, c->h_pin, fetch), done, stream));
             if (wait_count(done, nullptr, stream) != CRUM_OK)
                 return CRUM_EHIP;
             c->partial_call = false;
@@ -1127,7 +1127,7 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
 
     c->partial_call = true;
     CRUM_TRY(hipStreamWaitEvent(stream, c->ev_done, 0));
-    CRUM_TRY(launch_begin(P, S, L.upload_end, nullptr, stream));
+    CRUM_TRY(launch_begin(CopyList{}.add(0, P, S, L.upload_end), nullptr, stream));
     CRUM_TRY(hipEventRecord(c->ev_upload, stream));
     if (h_image)
         CRUM_TRY(hipMemcpyAsync(staging, h_image, image_bytes, hipMemcpyHostToDevice, stream));

@@ -80,7 +80,7 @@ struct DevGlobal {
     int32_t code;            // CRUM_OK or CRUM_ENOSPC (any request) / CRUM_EFORMAT
     uint32_t fmt_bad;        // restore: image check failed
     uint32_t crc_bad;        // restore: lowest failing slot, kNoBad if none
-    uint32_t pad0;
+    uint32_t bad_call;       // on-demand restore: first call that found a bad page
     uint64_t running;        // dirty pages counted by the scans so far
     uint64_t img_next;       // 4 KiB-aligned staging offset for the next image
     uint64_t pad[2];
@@ -103,7 +103,7 @@ struct CrcTables {
     uint32_t mf[16][64][4];
 };
 
-enum PackMode { kModePack = 0, kModeVerify = 1, kModeScatter = 2 };
+enum PackMode { kModePack = 0, kModeVerify = 1, kModeScatter = 2, kModePull = 3 };
 
 struct LaunchShape {
     int diff_blocks;   // persistent grid of the diff kernel (256-thread blocks)
@@ -117,6 +117,17 @@ struct SlotRange {
     const uint64_t* bounds;
     uint32_t chunk;
     uint64_t max_slots;  // upper bound on hi - lo (grid sizing)
+};
+
+// Runs of consecutive slots laid end to end, for launches over several at once
+// (on-demand restores).
+constexpr uint32_t kMaxRuns = 16;
+struct RunList {
+    uint32_t n = 0;
+    uint32_t call = 0;            // number of the session call they belong to
+    uint64_t first[kMaxRuns] = {};  // first slot of run r
+    uint64_t end[kMaxRuns] = {};    // slots in runs 0..r
+    const uint8_t* host = nullptr;  // read here (the host image, mapped by the device)
 };
 
 // Pinned host words that a scan writes itself (each may be null), so that the
@@ -137,11 +148,24 @@ struct FlagSource {
     const uint8_t* unit_flags = nullptr;
 };
 
+// Up to three copies of one launch: 8-byte aligned, whole 8-byte words.
+struct CopyList {
+    const void* src[3] = {};
+    void* dst[3] = {};
+    uint64_t bytes[3] = {};
+    CopyList& add(int k, const void* s, void* d, uint64_t n)
+    {
+        src[k] = s;
+        dst[k] = d;
+        bytes[k] = n;
+        return *this;
+    }
+};
+
 // Kernel launchers (crum_kernels.hip).  All enqueue on `s`.
-// Copies `bytes` (rounded up to 16; both ends 16-byte aligned) from or to pinned
-// host memory; with done (pinned), one workgroup copies and then stores 1 there.
-hipError_t launch_begin(const void* src, void* dst, uint64_t bytes, uint64_t* done,
-                        hipStream_t s);
+// Copies the pieces of `list` from or to pinned host memory; with done (pinned),
+// one workgroup copies and then stores 1 there.
+hipError_t launch_begin(const CopyList& list, uint64_t* done, hipStream_t s);
 const CrcTables& crc_tables();  // the constants, in host memory
 // cand (may be null): bitmap over global pages; pages whose bit is clear are
 // flagged clean without being read (they are known to equal their shadow).
@@ -178,18 +202,20 @@ hipError_t launch_list(const uint64_t* bitmap, const uint32_t* prefix, uint64_t 
 // whose flags bit 0 is set.  unit_flags (pack only, may be null): the diff's
 // per-unit flags of the same page space (4-byte aligned, padded to whole
 // words); units flagged clean are then read from the shadow.  nt: kPackNt*
-// bits.  update_shadow (scatter only): pages go to the shadows as well.
+// bits.  update_shadow (scatter only): pages go to the shadows as well.  runs
+// (may be null; verify, scatter, pull): the slots, instead of range.
 hipError_t launch_pack(int mode, const DevRegion* regs, uint32_t n_regs, const DevRequest* reqs,
                        const DevReqOut* out, const uint32_t* list, SlotRange range,
                        uint32_t np_shift, uint32_t piece_shift, const uint8_t* unit_flags,
                        uint8_t* staging, uint32_t* crc_out, uint32_t* partials,
                        const CrcTables* tabs, DevGlobal* glob, int blocks, hipStream_t s, int nt,
-                       int update_shadow = 0);
+                       int update_shadow = 0, const RunList* runs = nullptr);
 hipError_t launch_finalize(int mode, const DevRegion* regs, uint32_t n_regs,
                            const DevRequest* reqs, const DevReqOut* out, const uint32_t* list,
                            SlotRange range, uint32_t np_shift, uint32_t piece_shift,
                            const uint32_t* partials, uint32_t* crc_out, uint8_t* staging,
-                           DevGlobal* glob, const CrcTables* tabs, hipStream_t s);
+                           DevGlobal* glob, const CrcTables* tabs, hipStream_t s,
+                           const RunList* runs = nullptr);
 // Workgroups per request for launch_header and launch_restore_check, from
 // the request's region count, bitmap words and (a bound on) its CRC count.
 uint32_t header_blocks(uint64_t n_regions, uint64_t n_words, uint64_t n_crcs);

@@ -34,6 +34,7 @@
 #include "crum_dev.h"
 #include "gf2.h"
 
+#include <algorithm>
 #include <cstring>
 
 namespace crum {
@@ -262,16 +263,20 @@ __device__ __forceinline__ uint32_t columns_crc(const uint32_t* __restrict__ lds
 
 // ------------------------------------------------------------ k_begin
 
-// Copies n16 16-byte words between pinned host memory and the device: a call's
-// region and request tables and counters, or an image's header.  With `done`
-// (pinned), stores 1 there once its one workgroup's copy is visible to the host.
-__global__ __launch_bounds__(256) void k_begin(const u32x4* __restrict__ src,
-                                               u32x4* __restrict__ dst, uint64_t n16,
-                                               uint64_t* __restrict__ done)
+// Copies up to three pieces of whole 8-byte words between pinned host memory and
+// the device: a call's region and request tables and counters, an image's header,
+// its prefix and CRC array.  With `done` (pinned), stores 1 there once its one
+// workgroup's copy is visible to the host.
+__global__ __launch_bounds__(256) void k_begin(CopyList list, uint64_t* __restrict__ done)
 {
-    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n16;
-         i += (uint64_t)gridDim.x * 256)
-        dst[i] = src[i];
+    for (int k = 0; k < 3; ++k) {
+        const uint64_t* src = static_cast<const uint64_t*>(list.src[k]);
+        uint64_t* dst = static_cast<uint64_t*>(list.dst[k]);
+        const uint64_t n = list.bytes[k] / 8;
+        for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n;
+             i += (uint64_t)gridDim.x * 256)
+            dst[i] = src[i];
+    }
     if (done) {
         __threadfence_system();
         __syncthreads();
@@ -280,12 +285,12 @@ __global__ __launch_bounds__(256) void k_begin(const u32x4* __restrict__ src,
     }
 }
 
-hipError_t launch_begin(const void* src, void* dst, uint64_t bytes, uint64_t* done, hipStream_t s)
+hipError_t launch_begin(const CopyList& list, uint64_t* done, hipStream_t s)
 {
-    const uint64_t n16 = (bytes + 15) / 16, need = (n16 + 255) / 256;
+    const uint64_t most = std::max(list.bytes[0], std::max(list.bytes[1], list.bytes[2]));
+    const uint64_t need = (most / 8 + 255) / 256;
     const unsigned nb = done ? 1u : (unsigned)(need < 1 ? 1 : need < 256 ? need : 256);
-    hipLaunchKernelGGL(k_begin, dim3(nb), dim3(256), 0, s, static_cast<const u32x4*>(src),
-                       static_cast<u32x4*>(dst), n16, done);
+    hipLaunchKernelGGL(k_begin, dim3(nb), dim3(256), 0, s, list, done);
     return hipGetLastError();
 }
 
@@ -917,6 +922,20 @@ __device__ __forceinline__ bool unit_dirty(const uint8_t* __restrict__ flags, ui
     return (w >> (8 * (uint32_t)(u & 3))) & 0xFFu;
 }
 
+// The slot at index i of the runs laid end to end, and where its run ends.
+struct RunSlot {
+    uint64_t slot, run_end;
+};
+
+__device__ __forceinline__ RunSlot run_slot(const RunList& runs, uint64_t i)
+{
+    uint32_t r = 0;
+    while (r + 1 < runs.n && i >= runs.end[r])
+        ++r;
+    const uint64_t base = r ? runs.end[r - 1] : 0;
+    return {runs.first[r] + (i - base), runs.first[r] + (runs.end[r] - base)};
+}
+
 // Work item = (slot, piece); pieces per slot = 2^np_shift for the launch.
 // Pack: copy the dirty page into the image's page area (and the shadow) and
 // write its CRC to crc_out[slot].  Verify: recompute the CRC of a packed page
@@ -936,7 +955,14 @@ __device__ __forceinline__ bool unit_dirty(const uint8_t* __restrict__ flags, ui
 // snapshot (2 MiB pages) from 428 to 418 us, of 570 MB of 4 KiB pages with
 // their shadows from 412 to 402.  The matrix takes 64 registers, so a SIMD
 // holds four waves; their 8 KiB each in flight cover the memory's latency.
-template <int MODE, bool NT_LOAD, bool NT_STORE>
+//
+// RUNS: the items are the slots of up to kMaxRuns runs instead of one range,
+// read from runs.host (the host image, at the same offsets) when that is given,
+// and the checks note in glob->bad_call the first call that found a bad page: a
+// scatter writes the runs that end before that page, and none of a later call.
+// Pull: a verify that also leaves the pages in staging, so that the scatter does
+// not read the host link again.
+template <int MODE, bool NT_LOAD, bool NT_STORE, bool RUNS = false>
 __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ regs, uint32_t n_regs,
                                               const DevRequest* __restrict__ reqs,
                                               const DevReqOut* __restrict__ out,
@@ -948,16 +974,26 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
                                               uint32_t* __restrict__ partials,
                                               const CrcTables* __restrict__ tabs,
                                               DevGlobal* __restrict__ glob,
-                                              uint32_t update_shadow)
+                                              uint32_t update_shadow, RunList runs)
 {
     constexpr bool CRC = MODE != kModeScatter;
     __shared__ __attribute__((aligned(16))) uint32_t lds[CRC ? kCrcLdsWords : 4];
     if (MODE != kModePack && glob->fmt_bad)
         return;
-    if (MODE == kModeScatter && glob->crc_bad != kNoBad)
-        return;
-    uint64_t slot0, slot1;
-    slot_range(sr, &slot0, &slot1);
+    uint64_t slot0 = 0, slot1 = 0;
+    uint64_t stop = ~0ull;  // first slot that is not written any more (scatter)
+    if (RUNS) {
+        slot1 = runs.end[runs.n - 1];
+        if (MODE == kModeScatter && glob->crc_bad != kNoBad) {
+            if (glob->bad_call < runs.call)
+                return;
+            stop = glob->crc_bad;
+        }
+    } else {
+        slot_range(sr, &slot0, &slot1);
+        if (MODE == kModeScatter && glob->crc_bad != kNoBad)
+            return;
+    }
     const uint64_t n_items = (slot1 - slot0) << np_shift;
     // a grid sized for the most slots the launch could get: workgroups past
     // the items leave before staging their tables
@@ -979,7 +1015,13 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
     // the first item at or after `item` (this wave's items) that is a piece
     auto find = [&](uint64_t item, Piece& p) __attribute__((always_inline)) -> bool {
         for (; item < n_items; item += n_waves) {
-            const uint64_t k = slot0 + (item >> np_shift);
+            uint64_t k = slot0 + (item >> np_shift);
+            if (RUNS) {
+                const RunSlot s = run_slot(runs, k);
+                k = s.slot;
+                if (MODE == kModeScatter && s.run_end > stop)
+                    continue;
+            }
             const uint32_t piece = (uint32_t)(item & ((1ull << np_shift) - 1));
             const uint64_t g = list[k];
             if (g < r_lo || g >= r_hi) {
@@ -1004,8 +1046,8 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
             p.slot = k;
             p.region = r;
             p.batches = 1u << (pb_shift - 12);
-            p.src = packed;
-            p.dst = nullptr;
+            p.src = RUNS && runs.host ? runs.host + (packed - staging) : packed;
+            p.dst = MODE == kModePull ? packed : nullptr;
             p.shadow = nullptr;
             p.update = 0;
             p.unit = 0;
@@ -1098,8 +1140,11 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
                     const uint64_t local = cur.slot - O.slot_base;
                     const uint32_t* img_crc = reinterpret_cast<const uint32_t*>(
                         staging + O.img_base + Q.data_off + (O.n_dirty << ps));
-                    if (crc != img_crc[local] && lane == 0)
+                    if (crc != img_crc[local] && lane == 0) {
                         atomicMin(&glob->crc_bad, (uint32_t)local);
+                        if (RUNS)
+                            atomicMin(&glob->bad_call, runs.call);
+                    }
                 }
             }
         }
@@ -1117,9 +1162,9 @@ hipError_t launch_pack(int mode, const DevRegion* regs, uint32_t n_regs, const D
                        uint32_t np_shift, uint32_t piece_shift, const uint8_t* unit_flags,
                        uint8_t* staging, uint32_t* crc_out, uint32_t* partials,
                        const CrcTables* tabs, DevGlobal* glob, int blocks, hipStream_t s,
-                       int nt, int update_shadow)
+                       int nt, int update_shadow, const RunList* runs)
 {
-    const uint64_t max_items = range.max_slots << np_shift;
+    const uint64_t max_items = (runs ? runs->end[runs->n - 1] : range.max_slots) << np_shift;
     if (max_items == 0)
         return hipSuccess;
     if (piece_shift < kPieceShiftMin || piece_shift > kPieceShift)
@@ -1127,10 +1172,11 @@ hipError_t launch_pack(int mode, const DevRegion* regs, uint32_t n_regs, const D
     const uint64_t need = (max_items + 3) / 4;
     const uint64_t nb = need < (uint64_t)blocks ? need : (uint64_t)blocks;
     const dim3 grid((unsigned)nb);
-#define CRUM_PACK(M, L, S, F)                                                                  \
-    hipLaunchKernelGGL((k_pack<M, L, S>), grid, dim3(256), 0, s, regs, n_regs, reqs, out, list, \
-                       range, np_shift, piece_shift, F, staging, crc_out, partials, tabs, glob, \
-                       (uint32_t)update_shadow)
+#define CRUM_PACK_R(M, L, S, F, ...)                                                           \
+    hipLaunchKernelGGL((k_pack<M, L, S, ##__VA_ARGS__>), grid, dim3(256), 0, s, regs, n_regs,   \
+                       reqs, out, list, range, np_shift, piece_shift, F, staging, crc_out,      \
+                       partials, tabs, glob, (uint32_t)update_shadow, runs ? *runs : RunList{})
+#define CRUM_PACK(M, L, S, F) CRUM_PACK_R(M, L, S, F)
 #define CRUM_PACK_NT(M, F)                                                                     \
     switch (nt & (kPackNtLoad | kPackNtStore)) {                                               \
     case 0: CRUM_PACK(M, false, false, F); break;                                              \
@@ -1138,7 +1184,14 @@ hipError_t launch_pack(int mode, const DevRegion* regs, uint32_t n_regs, const D
     case kPackNtLoad: CRUM_PACK(M, true, false, F); break;                                     \
     default: CRUM_PACK(M, true, true, F); break;                                               \
     }
-    if (mode == kModeScatter) {
+    if (runs) {
+        if (mode == kModePull)
+            CRUM_PACK_R(kModePull, false, false, nullptr, true);
+        else if (mode == kModeVerify)
+            CRUM_PACK_R(kModeVerify, false, false, nullptr, true);
+        else
+            CRUM_PACK_R(kModeScatter, false, false, nullptr, true);
+    } else if (mode == kModeScatter) {
         CRUM_PACK_NT(kModeScatter, nullptr);
     } else if (mode == kModeVerify) {
         if (nt & kPackNtLoad)
@@ -1149,6 +1202,7 @@ hipError_t launch_pack(int mode, const DevRegion* regs, uint32_t n_regs, const D
         CRUM_PACK_NT(kModePack, unit_flags);
     }
 #undef CRUM_PACK_NT
+#undef CRUM_PACK_R
 #undef CRUM_PACK
     return hipGetLastError();
 }
@@ -1172,20 +1226,26 @@ __global__ __launch_bounds__(256) void k_finalize(const DevRegion* __restrict__ 
                                                   uint32_t* __restrict__ crc_out,
                                                   uint8_t* __restrict__ staging,
                                                   DevGlobal* __restrict__ glob,
-                                                  const CrcTables* __restrict__ tabs)
+                                                  const CrcTables* __restrict__ tabs,
+                                                  RunList runs)
 {
     if (MODE == kModeVerify && glob->fmt_bad)
         return;
-    uint64_t slot0, slot1;
-    slot_range(sr, &slot0, &slot1);
+    uint64_t slot0 = 0, slot1 = 0;
+    if (runs.n)
+        slot1 = runs.end[runs.n - 1];
+    else
+        slot_range(sr, &slot0, &slot1);
     const uint32_t l_shift = np_shift < 6 ? np_shift : 6;
     const uint64_t i = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> l_shift;
     const uint32_t l = threadIdx.x & ((1u << l_shift) - 1);
     // a slot's lanes stay together through the shuffles: none leaves early
-    const uint64_t k = slot0 + i;
+    uint64_t k = slot0 + i;
     uint32_t e = 0;  // log2 of the slot's pieces, 0: nothing to combine
     uint32_t r = 0;
     if (i < slot1 - slot0) {
+        if (runs.n)
+            k = run_slot(runs, i).slot;
         const uint64_t g = list[k];
         r = find_region<3>(regs, n_regs, g);
         const DevRegion& R = regs[r];
@@ -1221,8 +1281,11 @@ __global__ __launch_bounds__(256) void k_finalize(const DevRegion* __restrict__ 
         const uint64_t local = k - O.slot_base;
         const uint32_t* img_crc = reinterpret_cast<const uint32_t*>(
             staging + O.img_base + Q.data_off + (O.n_dirty << R.page_shift));
-        if (crc != img_crc[local])
+        if (crc != img_crc[local]) {
             atomicMin(&glob->crc_bad, (uint32_t)local);
+            if (runs.n)
+                atomicMin(&glob->bad_call, runs.call);
+        }
     }
 }
 
@@ -1230,20 +1293,23 @@ hipError_t launch_finalize(int mode, const DevRegion* regs, uint32_t n_regs,
                            const DevRequest* reqs, const DevReqOut* out, const uint32_t* list,
                            SlotRange range, uint32_t np_shift, uint32_t piece_shift,
                            const uint32_t* partials, uint32_t* crc_out, uint8_t* staging,
-                           DevGlobal* glob, const CrcTables* tabs, hipStream_t s)
+                           DevGlobal* glob, const CrcTables* tabs, hipStream_t s,
+                           const RunList* runs)
 {
-    if (range.max_slots == 0 || np_shift == 0)
+    const uint64_t n_slots = runs ? runs->end[runs->n - 1] : range.max_slots;
+    if (n_slots == 0 || np_shift == 0)
         return hipSuccess;
     const uint32_t l_shift = np_shift < 6 ? np_shift : 6;
-    const unsigned nb = (unsigned)(((range.max_slots << l_shift) + 255) / 256);
+    const unsigned nb = (unsigned)(((n_slots << l_shift) + 255) / 256);
+    const RunList rl = runs ? *runs : RunList{};
     if (mode == kModePack)
         hipLaunchKernelGGL(k_finalize<kModePack>, dim3(nb), dim3(256), 0, s, regs, n_regs, reqs,
                            out, list, range, np_shift, piece_shift, partials, crc_out, staging,
-                           glob, tabs);
+                           glob, tabs, rl);
     else
         hipLaunchKernelGGL(k_finalize<kModeVerify>, dim3(nb), dim3(256), 0, s, regs, n_regs,
                            reqs, out, list, range, np_shift, piece_shift, partials, crc_out,
-                           staging, glob, tabs);
+                           staging, glob, tabs, rl);
     return hipGetLastError();
 }
 

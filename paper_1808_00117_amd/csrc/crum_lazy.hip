@@ -12,10 +12,13 @@
 // region's end, or the whole region when the region is small.  The absent
 // image pages of the window are fetched in runs of consecutive slots: one
 // host-to-device copy of the run's packed pages into the staging buffer (at
-// their offsets in the image layout), the CRC check of the run (with
-// CRUM_VERIFY) and the scatter of the run into the regions.  Runs of up to
-// 2 MiB skip the copy: when the host image is device-mapped pinned memory,
-// their check and scatter read the packed pages from it in place.
+// their offsets in the image layout), the CRC check of the runs (with
+// CRUM_VERIFY) and their scatter into the regions.  Runs of up to 2 MiB skip the
+// copy: when the host image is device-mapped pinned memory, the check reads
+// the packed pages from it and leaves them in staging for the scatter.  All runs
+// of a window (up to 16 per launch) share their launches: 256 MiB with 48
+// accesses and 8 runs at the end spent 330 us after the last copy in three
+// launches per run, now 60.
 //
 // Open uploads only the image prefix (header, table, bitmap) and the CRC
 // array, checks them on the device as a full restore does and builds the
@@ -53,6 +56,7 @@ struct crum_lazy {
     uint64_t small_bytes = 0;
     uint32_t pc_shift = 0, np_shift = 0;
     int pack_blocks = 0;
+    uint32_t calls = 0;  // touches and finishes that fetched something
     std::vector<uint64_t> bitmap;   // image bitmap, W words
     std::vector<uint64_t> prefix;   // slots before word w
     std::vector<uint64_t> fetched;  // bit per page: its fetch has been enqueued
@@ -132,18 +136,17 @@ uint32_t run_piece_shift(const crum_lazy* z, uint64_t n)
     return pcs;
 }
 
-// Runs of at most this many packed bytes are checked and scattered straight
-// from the pinned host image (the kernels read it over the host link): a
-// copy to staging and the wait for it cost more than the transfer itself.
+// Runs of at most this many packed bytes are read straight from the pinned host
+// image (the kernels read it over the host link): a copy to staging and the
+// wait for it cost more than the transfer itself.
 constexpr uint64_t kInPlaceRunBytes = 2ull << 20;
 
-// Checks and scatter of slots [k0, k1), whose packed pages are at their
-// image offsets from `src` (the staging buffer, or the host image itself).
-hipError_t run_kernels(crum_lazy* z, uint64_t k0, uint64_t k1, uint8_t* src, hipStream_t s)
+// One launch of a run list's check (and, with CRUM_VERIFY, the combination of
+// its piece CRCs) or scatter.
+hipError_t run_launch(crum_lazy* z, int mode, const RunList& runs, hipStream_t s)
 {
     const uint32_t ps = z->info.ps;
-    const uint64_t n = k1 - k0;
-    const uint32_t pcs = run_piece_shift(z, n);
+    const uint32_t pcs = run_piece_shift(z, runs.end[runs.n - 1]);
     const uint32_t nps = ps > pcs ? ps - pcs : 0;
     uint8_t* M = z->d_mem;
     const DevRegion* regs = reinterpret_cast<const DevRegion*>(M + z->o_regs);
@@ -154,28 +157,68 @@ hipError_t run_kernels(crum_lazy* z, uint64_t k0, uint64_t k1, uint8_t* src, hip
     uint32_t* partials = reinterpret_cast<uint32_t*>(M + z->o_partials);
     uint32_t* crcs = reinterpret_cast<uint32_t*>(M + z->o_crcs);
     const uint32_t nr = (uint32_t)z->regions.size();
-    hipError_t e;
-    if (z->flags & CRUM_VERIFY) {
-        const SlotRange sr{k0, k1, nullptr, 0, n};
-        e = launch_pack(kModeVerify, regs, nr, req, out, list, sr, nps, pcs,
-                        nullptr, src, crcs, partials, ctx_tables(z->ctx), glob,
-                        z->pack_blocks, s, 0);
-        if (e != hipSuccess)
-            return e;
-        e = launch_finalize(kModeVerify, regs, nr, req, out, list, sr, nps, pcs,
-                            partials, crcs, src, glob, ctx_tables(z->ctx), s);
-        if (e != hipSuccess)
-            return e;
+    const CrcTables* tabs = ctx_tables(z->ctx);
+    hipError_t e = launch_pack(mode, regs, nr, req, out, list, SlotRange{}, nps, pcs, nullptr,
+                               z->staging, crcs, partials, tabs, glob, z->pack_blocks, s, 0,
+                               (z->flags & CRUM_UPDATE_SHADOW) ? 1 : 0, &runs);
+    if (e == hipSuccess && mode != kModeScatter)
+        e = launch_finalize(kModeVerify, regs, nr, req, out, list, SlotRange{}, nps, pcs,
+                            partials, crcs, z->staging, glob, tabs, s, &runs);
+    return e;
+}
+
+typedef std::vector<std::pair<uint64_t, uint64_t>> Runs;  // slots [first, second)
+
+// The checks and scatters of `rs` on `s`, in run lists of up to kMaxRuns runs, in
+// slot order.  in_place(r): the run is read from the host image, else its pages
+// are in staging once `s` has waited for z->ev_copied.  With CRUM_VERIFY a list
+// is checked before any page of it is written, and runs read in place are left in
+// staging by the check; without, they are scattered straight from the host
+// image.
+template <typename InPlace>
+hipError_t enqueue_runs(crum_lazy* z, const Runs& rs, InPlace in_place, hipStream_t s)
+{
+    const bool verify = (z->flags & CRUM_VERIFY) != 0;
+    bool waited = false;
+    for (size_t i = 0; i < rs.size();) {
+        RunList all, part[2];  // part[1]: read in place
+        for (; i < rs.size() && all.n < kMaxRuns; ++i) {
+            const bool ip = in_place(rs[i]);
+            for (RunList* l : {&all, &part[ip]}) {
+                l->first[l->n] = rs[i].first;
+                l->end[l->n] = (l->n ? l->end[l->n - 1] : 0) + rs[i].second - rs[i].first;
+                ++l->n;
+            }
+        }
+        all.call = part[0].call = part[1].call = z->calls;
+        part[1].host = z->h_image;
+        for (int k = 1; k >= 0; --k) {  // the link first
+            if (!part[k].n)
+                continue;
+            if (k == 0 && !waited) {
+                const hipError_t e = hipStreamWaitEvent(s, z->ev_copied, 0);
+                if (e != hipSuccess)
+                    return e;
+                waited = true;
+            }
+            const hipError_t e = run_launch(
+                z, !verify ? kModeScatter : k ? kModePull : kModeVerify, part[k], s);
+            if (e != hipSuccess)
+                return e;
+        }
+        if (verify) {
+            const hipError_t e = run_launch(z, kModeScatter, all, s);
+            if (e != hipSuccess)
+                return e;
+        }
     }
-    return launch_pack(kModeScatter, regs, nr, req, out, list, SlotRange{k0, k1, nullptr, 0, n},
-                       nps, pcs, nullptr, src, crcs, partials, ctx_tables(z->ctx), glob,
-                       z->pack_blocks, s, 0, (z->flags & CRUM_UPDATE_SHADOW) ? 1 : 0);
+    return hipSuccess;
 }
 
 // Fetch every absent image page of global pages [g0, g1): the copies of the
 // runs that are not read in place on the copy stream, then on `s` a wait for
-// them and each run's kernels.  Returns the pages enqueued in *pages and the
-// runs in *runs.
+// them and the kernels.  Returns the pages enqueued in *pages and the runs in
+// *runs.
 hipError_t fetch_window(crum_lazy* z, uint64_t g0, uint64_t g1, hipStream_t s, uint64_t* pages,
                         uint64_t* runs)
 {
@@ -183,7 +226,7 @@ hipError_t fetch_window(crum_lazy* z, uint64_t g0, uint64_t g1, hipStream_t s, u
     *runs = 0;
     if (g1 <= g0)
         return hipSuccess;
-    std::vector<std::pair<uint64_t, uint64_t>> rs;  // runs of slots [first, second)
+    Runs rs;
     for (uint64_t w = g0 >> 6; w <= (g1 - 1) >> 6; ++w) {
         uint64_t m = z->bitmap[w] & ~z->fetched[w];
         if (w == g0 >> 6)
@@ -206,7 +249,6 @@ hipError_t fetch_window(crum_lazy* z, uint64_t g0, uint64_t g1, hipStream_t s, u
     if (rs.empty())
         return hipSuccess;
     const ImageInfo& I = z->info;
-    uint8_t* host = const_cast<uint8_t*>(z->h_image);  // read only
     auto in_place = [&](const std::pair<uint64_t, uint64_t>& r) {
         return z->host_mapped && ((r.second - r.first) << I.ps) <= kInPlaceRunBytes;
     };
@@ -224,18 +266,13 @@ hipError_t fetch_window(crum_lazy* z, uint64_t g0, uint64_t g1, hipStream_t s, u
     }
     if (copied) {
         e = hipEventRecord(z->ev_copied, z->copy);
-        if (e == hipSuccess)
-            e = hipStreamWaitEvent(s, z->ev_copied, 0);
         if (e != hipSuccess)
             return e;
     }
-    for (const auto& r : rs) {
-        e = run_kernels(z, r.first, r.second, in_place(r) ? host : z->staging, s);
-        if (e != hipSuccess)
-            return e;
-    }
+    ++z->calls;
+    e = enqueue_runs(z, rs, in_place, s);
     *runs = rs.size();
-    return hipSuccess;
+    return e;
 }
 
 // Status of the session after the work enqueued so far, into h_status (the
@@ -246,8 +283,9 @@ hipError_t enqueue_status(crum_lazy* z, crum_status* h_status, hipStream_t s)
         return hipSuccess;
     DevReqOut* out = reinterpret_cast<DevReqOut*>(z->d_mem + z->o_out);
     DevGlobal* glob = reinterpret_cast<DevGlobal*>(z->d_mem + z->o_glob);
-    hipError_t e = launch_restore_finish(out, 1, glob, s);
-    if (e != hipSuccess)
+    void* d_status = mapped_status(h_status);
+    hipError_t e = launch_restore_finish(out, 1, glob, s, d_status);
+    if (e != hipSuccess || d_status)
         return e;
     return hipMemcpyAsync(h_status, out, sizeof(crum_status), hipMemcpyDeviceToHost, s);
 }
@@ -415,6 +453,7 @@ int crum_lazy_open(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
     std::memcpy(P + z->o_out, &o, sizeof(o));
     DevGlobal gl{};
     gl.crc_bad = kNoBad;
+    gl.bad_call = kNoBad;
     std::memcpy(P + z->o_glob, &gl, sizeof(gl));
 
     uint8_t* M = z->d_mem;
@@ -431,10 +470,25 @@ int crum_lazy_open(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
         lazy_free(z);
         return CRUM_EHIP;
     };
-    if (hipMemcpyAsync(M, P, z->upload_end, hipMemcpyHostToDevice, stream) != hipSuccess ||
-        hipMemcpyAsync(z->staging, h, I.data_off, hipMemcpyHostToDevice, stream) != hipSuccess ||
-        hipMemcpyAsync(z->staging + pages_end, h + pages_end, image_bytes - pages_end,
-                       hipMemcpyHostToDevice, stream) != hipSuccess ||
+    // tables, prefix and CRC array (whole 8-byte words): one launch reads them,
+    // or three copies when kernels cannot read the host image
+    auto upload = [&]() {
+        if (z->host_mapped && (reinterpret_cast<uintptr_t>(h) & 7u) == 0)
+            return launch_begin(CopyList{}
+                                    .add(0, P, M, z->upload_end)
+                                    .add(1, h, z->staging, I.data_off)
+                                    .add(2, h + pages_end, z->staging + pages_end,
+                                         image_bytes - pages_end),
+                                nullptr, stream);
+        hipError_t e = hipMemcpyAsync(M, P, z->upload_end, hipMemcpyHostToDevice, stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(z->staging, h, I.data_off, hipMemcpyHostToDevice, stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(z->staging + pages_end, h + pages_end, image_bytes - pages_end,
+                               hipMemcpyHostToDevice, stream);
+        return e;
+    };
+    if (upload() != hipSuccess ||
         launch_restore_check(d_req, 1, header_blocks(n_regions, W, D), d_out, z->staging,
                              ctx_tables(c), d_glob, stream) !=
             hipSuccess ||

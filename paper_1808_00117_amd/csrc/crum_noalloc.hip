@@ -230,7 +230,7 @@ int crum_snapshot_noalloc(crum_ctx* c, const crum_region* regions, uint32_t n_re
     // after this context's previous call (whose kernels may still use the array)
     c->partial_call = true;
     CRUM_TRY_C(hipStreamWaitEvent(stream, c->ev_done, 0));
-    CRUM_TRY_C(launch_begin(P, S, L.upload_end, nullptr, stream));
+    CRUM_TRY_C(launch_begin(CopyList{}.add(0, P, S, L.upload_end), nullptr, stream));
     if (any_shadow(regions, n_regions))
         CRUM_TRY_C(launch_diff(d_regs, n_regions, 0, n_units, d_flags, ctx_diff_blocks(c, false), c->diff_nt, c->diff_prio, stream,
                                nullptr, nullptr, ctx_diff_group(c, us)));
