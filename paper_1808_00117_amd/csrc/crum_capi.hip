@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <cstddef>
 #include <cstdlib>
 #include <cstring>
 #include <utility>
@@ -25,8 +26,8 @@ struct Layout {
            total = 0;
 };
 
-Layout make_layout(uint32_t n_regs, uint32_t n_reqs, uint64_t n_units, uint64_t n_words,
-                   uint64_t list_cap, uint64_t partial_cap, uint64_t n_chunks,
+Layout make_layout(uint32_t n_regs, uint64_t n_units, uint64_t n_words, uint64_t list_cap,
+                   uint64_t partial_cap, uint64_t n_chunks,
                    uint64_t cand_words = 0)
 {
     Layout L;
@@ -36,10 +37,11 @@ Layout make_layout(uint32_t n_regs, uint32_t n_reqs, uint64_t n_units, uint64_t 
         off = round_up(off + bytes, 256);
         return o;
     };
-    L.regs = take(64ull * std::max<uint32_t>(1, n_regs));
-    L.reqs = take(64ull * n_reqs);
-    L.out = take(64ull * n_reqs + 64);
-    L.glob = L.out + 64ull * n_reqs;
+    // as in CallTables, which a call may store here
+    L.reqs = take(std::max<size_t>(sizeof(CallTables), offsetof(CallTables, regs) + 64ull * n_regs));
+    L.out = L.reqs + offsetof(CallTables, out);
+    L.glob = L.reqs + offsetof(CallTables, glob);
+    L.regs = L.reqs + offsetof(CallTables, regs);
     L.cand = take(8 * cand_words);
     L.upload_end = off;
     L.flags = take(std::max<uint64_t>(n_units, 1));
@@ -710,7 +712,7 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
     uint64_t n_pages = 0, n_units = 0;
     flatten_regions(regions, n_regions, ps, c->unit_shift_max,
                     (flags & CRUM_UPDATE_SHADOW) ? 1u : 0u, dregs.data(), &n_pages, &n_units);
-    const Layout L = make_layout(n_regions, 1, n_units, W, W * 64, np_shift ? G << np_shift : 0,
+    const Layout L = make_layout(n_regions, n_units, W, W * 64, np_shift ? G << np_shift : 0,
                                  n_chunks, h_cand ? W : 0);
     CRUM_TRY(ensure_scratch(c, L.total));
     const size_t rb_off = round_up(L.upload_end, 256);
@@ -719,8 +721,6 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
     CRUM_TRY(ensure_events(c->ev_cnt, n_chunks));
     CRUM_TRY(settle(c));
     uint8_t* P = c->h_pin;
-    std::memset(P, 0, L.upload_end);
-    std::memcpy(P + L.regs, dregs.data(), sizeof(DevRegion) * n_regions);
     DevRequest rq{};
     rq.first_word = 0;
     rq.n_words = W;
@@ -731,13 +731,19 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
     rq.data_off = data_off;
     rq.seq = seq;
     rq.page_shift = ps;
-    rq.init_fix = crc_init_fix(page_size);
-    std::memcpy(P + L.reqs, &rq, sizeof(rq));
+    rq.init_fix = crc_tables().init_fix[ps];
     DevGlobal gl{};
     gl.crc_bad = kNoBad;
-    std::memcpy(P + L.glob, &gl, sizeof(gl));
-    if (h_cand && W)
-        std::memcpy(P + L.cand, h_cand, 8 * W);
+    // few regions: the tables go to the device as arguments of the diff
+    const bool by_args = need_diff && !h_cand && n_chunks == 1 && n_regions <= kArgRegions;
+    if (!by_args) {
+        std::memset(P, 0, L.upload_end);
+        std::memcpy(P + L.reqs, &rq, sizeof(rq));
+        std::memcpy(P + L.glob, &gl, sizeof(gl));
+        std::memcpy(P + L.regs, dregs.data(), sizeof(DevRegion) * n_regions);
+        if (h_cand && W)
+            std::memcpy(P + L.cand, h_cand, 8 * W);
+    }
 
     uint8_t* S = c->d_scratch;
     const uint64_t* d_cand = h_cand ? reinterpret_cast<const uint64_t*>(S + L.cand) : nullptr;
@@ -766,20 +772,33 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
     // the previous call on this context may still be draining from scratch
     c->partial_call = true;  // cleared once ev_done is recorded
     CRUM_TRY(hipStreamWaitEvent(stream, c->ev_done, 0));
-    CRUM_TRY(launch_begin(CopyList{}.add(0, P, S, L.upload_end), nullptr, stream));
-    // a call that waits for a count knows that its tables have been read
-    if (direct || (eager && !h_image))
-        CRUM_TRY(hipEventRecord(c->ev_upload, stream));
+    if (!by_args) {
+        CRUM_TRY(launch_begin(CopyList{}.add(0, P, S, L.upload_end), nullptr, stream));
+        // a call that waits for a count knows that its tables have been read
+        if (direct || (eager && !h_image))
+            CRUM_TRY(hipEventRecord(c->ev_upload, stream));
+    }
+    // the diff of the whole page space (one chunk)
+    auto diff_all = [&]() {
+        if (!need_diff)
+            return hipSuccess;
+        Span sp(c, kTDiff, stream);
+        if (!by_args)
+            return launch_diff(d_regs, n_regions, 0, n_units, d_flags, diff_blocks, c->diff_nt,
+                               c->diff_prio, stream, d_cand, nullptr, ctx_diff_group(c, us));
+        CallTables t{};
+        t.req = rq;
+        t.glob = gl;
+        std::memcpy(t.regs, dregs.data(), sizeof(DevRegion) * n_regions);
+        return launch_diff_first(t, reinterpret_cast<CallTables*>(S), n_regions, n_units, d_flags,
+                                 diff_blocks, c->diff_nt, c->diff_prio, stream,
+                                 ctx_diff_group(c, us));
+    };
 
     if (direct) {
         // ---- direct order: diff, scan (with the capacity check), list, then
         // pack and header into the host image; slot counts stay on the device
-        if (need_diff) {
-            Span sp(c, kTDiff, stream);
-            CRUM_TRY(launch_diff(d_regs, n_regions, 0, n_units, d_flags, diff_blocks,
-                                 c->diff_nt, c->diff_prio, stream, d_cand, nullptr,
-                                 ctx_diff_group(c, us)));
-        }
+        CRUM_TRY(diff_all());
         {
             Span sp(c, kTScan, stream);
             CRUM_TRY(launch_scan(d_bitmap, 0, W, d_prefix, d_bounds, 1, d_reqs, 0, 1, d_out,
@@ -815,12 +834,13 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
         for (size_t ci = 0; ci < n_chunks; ++ci) {
             const uint64_t g0 = cuts[ci], g1 = cuts[ci + 1];
             const uint64_t w0 = g0 / 64, w1 = (g1 + 63) / 64;
-            if (need_diff) {
+            if (n_chunks == 1) {
+                CRUM_TRY(diff_all());
+            } else if (need_diff) {
                 Span sp(c, kTDiff, stream);
                 CRUM_TRY(launch_diff(d_regs, n_regions, g0 << (ps - us), g1 << (ps - us), d_flags,
-                                     diff_blocks, c->diff_nt, c->diff_prio, stream,
-                                     d_cand, nullptr,
-                                     ctx_diff_group(c, us)));
+                                     diff_blocks, c->diff_nt, c->diff_prio, stream, d_cand,
+                                     nullptr, ctx_diff_group(c, us)));
             }
             {
                 Span sp(c, kTScan, stream);
@@ -838,7 +858,8 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
                 SlotRange sr{0, 0, d_bounds, (uint32_t)ci, g1 - g0};
                 CRUM_TRY(launch_pack(kModePack, d_regs, n_regions, d_reqs, d_out, d_list, sr,
                                      np_shift, pc_shift, d_flags, staging, d_crcs,
-                                     d_partials, c->d_tabs, d_glob, c->shape.pack_blocks, stream, pack_flags));
+                                     d_partials, c->d_tabs, d_glob, c->shape.pack_blocks, stream,
+                                     pack_flags));
                 sp.end();  // k_finalize is not part of the pack's timing
                 CRUM_TRY(launch_finalize(kModePack, d_regs, n_regions, d_reqs, d_out, d_list, sr,
                                          np_shift, pc_shift, d_partials, d_crcs, staging, d_glob,
@@ -903,12 +924,7 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
         return CRUM_OK;
     } else {
         // ---- checked order: whole diff, scan with the capacity check, readback
-        if (need_diff) {
-            Span sp(c, kTDiff, stream);
-            CRUM_TRY(launch_diff(d_regs, n_regions, 0, n_units, d_flags, diff_blocks,
-                                 c->diff_nt, c->diff_prio, stream, d_cand, nullptr,
-                                 ctx_diff_group(c, us)));
-        }
+        CRUM_TRY(diff_all());
         {
             Span sp(c, kTScan, stream);
             HostNote note;
@@ -1088,7 +1104,7 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
     uint64_t n_pages = 0, n_units = 0;
     flatten_regions(regions, n_regions, ps, c->unit_shift_max, 0, dregs.data(), &n_pages,
                     &n_units);
-    const Layout L = make_layout(n_regions, 1, 0, W, W * 64, np_shift ? D << np_shift : 0, 1);
+    const Layout L = make_layout(n_regions, 0, W, W * 64, np_shift ? D << np_shift : 0, 1);
     CRUM_TRY(ensure_scratch(c, L.total));
     CRUM_TRY(ensure_pinned(c, L.upload_end));
     uint8_t* P = c->h_pin;
@@ -1102,7 +1118,7 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
     rq.data_off = data_off;
     rq.seq = seq;
     rq.page_shift = ps;
-    rq.init_fix = crc_init_fix(page_size);
+    rq.init_fix = crc_tables().init_fix[ps];
     std::memcpy(P + L.reqs, &rq, sizeof(rq));
     DevReqOut o{};
     o.n_dirty = D;

@@ -87,6 +87,16 @@ struct DevGlobal {
 };
 static_assert(sizeof(DevGlobal) == 64, "DevGlobal layout");
 
+// The tables of a call with one request and few regions, passed as a kernel
+// argument; scratch holds them in this layout too.
+constexpr uint32_t kArgRegions = 16;
+struct CallTables {
+    DevRequest req;
+    DevReqOut out;
+    DevGlobal glob;
+    DevRegion regs[kArgRegions];
+};
+
 // CRC constants held in device memory:
 // z4k[i][b] = (b << 8i) * x^(8 * 4096): byte i of a state carried through 4 KiB
 // of zeros (staged into LDS); xp[i] = x^(8 * 2^i); xb[k][i] = x^(8 * 4096 *
@@ -101,6 +111,8 @@ struct CrcTables {
     uint32_t xr[1024];
     uint32_t col[8][16][32];
     uint32_t mf[16][64][4];
+    uint32_t init_fix[31];  // host: crc_init_fix of a page of 2^i bytes
+    uint32_t pad;
 };
 
 enum PackMode { kModePack = 0, kModeVerify = 1, kModeScatter = 2, kModePull = 3 };
@@ -193,6 +205,10 @@ hipError_t launch_scan(uint64_t* bitmap, uint64_t w0, uint64_t w1, uint32_t* pre
                        uint32_t q1, DevReqOut* out, DevGlobal* glob, uint64_t capacity,
                        int restore_mode, uint32_t* list, hipStream_t s, const FlagSource& fs,
                        const HostNote& note = HostNote{});
+// launch_diff over units [0, u1) of a call's tables, which it also stores at `to`.
+hipError_t launch_diff_first(const CallTables& t, CallTables* to, uint32_t n_regs, uint64_t u1,
+                             uint8_t* unit_flags, int blocks, int nontemporal, int prio,
+                             hipStream_t s, int group);
 hipError_t launch_list(const uint64_t* bitmap, const uint32_t* prefix, uint64_t w0, uint64_t w1,
                        uint32_t* list, hipStream_t s);
 // Pack, verify and scatter work on (slot, piece) items: a page of 2^ps bytes

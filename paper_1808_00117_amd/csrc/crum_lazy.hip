@@ -444,7 +444,7 @@ int crum_lazy_open(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
     rq.data_off = I.data_off;
     rq.seq = I.seq;
     rq.page_shift = I.ps;
-    rq.init_fix = crc_init_fix(I.page_size);
+    rq.init_fix = crc_tables().init_fix[I.ps];
     std::memcpy(P + z->o_req, &rq, sizeof(rq));
     DevReqOut o{};
     o.n_dirty = D;

@@ -23,6 +23,7 @@
 #include "gf2.h"
 
 #include <algorithm>
+#include <cstddef>
 #include <cstring>
 #include <mutex>
 #include <utility>
@@ -53,10 +54,11 @@ NaLayout na_layout(uint64_t n_regs, uint64_t n_units, uint64_t n_words, uint64_t
         off = round_up(off + bytes, 256);
         return o;
     };
-    L.regs = take(64 * std::max<uint64_t>(1, n_regs));
-    L.reqs = take(64);
-    L.out = take(128);
-    L.glob = L.out + 64;
+    // as in CallTables, which a call may store here
+    L.reqs = take(std::max<uint64_t>(sizeof(CallTables), offsetof(CallTables, regs) + 64 * n_regs));
+    L.out = L.reqs + offsetof(CallTables, out);
+    L.glob = L.reqs + offsetof(CallTables, glob);
+    L.regs = L.reqs + offsetof(CallTables, regs);
     L.upload_end = off;
     L.flags = take(std::max<uint64_t>(n_units, 1));
     L.bitmap = take(8 * std::max<uint64_t>(n_words, 1));
@@ -183,22 +185,27 @@ int crum_snapshot_noalloc(crum_ctx* c, const crum_region* regions, uint32_t n_re
     // the previous upload from the pinned buffer must have left it
     CRUM_TRY_C(c->partial_call ? hipDeviceSynchronize() : hipEventSynchronize(c->ev_upload));
     uint8_t* P = c->na_pin;
+    const bool need_diff = any_shadow(regions, n_regions);
+    // few regions: the tables go to the device as arguments of the diff
+    const bool by_args = need_diff && n_regions <= kArgRegions;
+    CallTables t{};
     std::memset(P, 0, L.upload_end);
     uint64_t n_pages = 0, n_units2 = 0;
     flatten_regions(regions, n_regions, ps, c->unit_shift_max,
                     (flags & CRUM_UPDATE_SHADOW) ? 1u : 0u,
-                    reinterpret_cast<DevRegion*>(P + L.regs), &n_pages, &n_units2);
+                    by_args ? t.regs : reinterpret_cast<DevRegion*>(P + L.regs), &n_pages,
+                    &n_units2);
     DevRequest rq{};
     rq.first_word = 0;
     rq.n_words = W;
     rq.n_pages = G;
     rq.first_region = 0;
     rq.n_regions = n_regions;
-    rq.flags = any_shadow(regions, n_regions) ? kReqShadow : 0;
+    rq.flags = need_diff ? kReqShadow : 0;
     rq.data_off = data_off;
     rq.seq = seq;
     rq.page_shift = ps;
-    rq.init_fix = crc_init_fix(page_size);
+    rq.init_fix = crc_tables().init_fix[ps];
     std::memcpy(P + L.reqs, &rq, sizeof(rq));
     DevGlobal gl{};
     gl.crc_bad = kNoBad;
@@ -230,10 +237,19 @@ int crum_snapshot_noalloc(crum_ctx* c, const crum_region* regions, uint32_t n_re
     // after this context's previous call (whose kernels may still use the array)
     c->partial_call = true;
     CRUM_TRY_C(hipStreamWaitEvent(stream, c->ev_done, 0));
-    CRUM_TRY_C(launch_begin(CopyList{}.add(0, P, S, L.upload_end), nullptr, stream));
-    if (any_shadow(regions, n_regions))
-        CRUM_TRY_C(launch_diff(d_regs, n_regions, 0, n_units, d_flags, ctx_diff_blocks(c, false), c->diff_nt, c->diff_prio, stream,
-                               nullptr, nullptr, ctx_diff_group(c, us)));
+    if (by_args) {
+        t.req = rq;
+        t.glob = gl;
+        CRUM_TRY_C(launch_diff_first(t, reinterpret_cast<CallTables*>(S + L.reqs), n_regions,
+                                     n_units, d_flags, ctx_diff_blocks(c, false), c->diff_nt,
+                                     c->diff_prio, stream, ctx_diff_group(c, us)));
+    } else {
+        CRUM_TRY_C(launch_begin(CopyList{}.add(0, P, S, L.upload_end), nullptr, stream));
+        if (need_diff)
+            CRUM_TRY_C(launch_diff(d_regs, n_regions, 0, n_units, d_flags,
+                                   ctx_diff_blocks(c, false), c->diff_nt, c->diff_prio, stream,
+                                   nullptr, nullptr, ctx_diff_group(c, us)));
+    }
     CRUM_TRY_C(launch_scan(d_bitmap, 0, W, d_prefix, d_bounds, 1, d_reqs, 0, 1, d_out, d_glob,
                            capacity, 0, d_list, stream, flag_src, note));
     // the kernels behind the scan take the slot count and the capacity check's
@@ -257,7 +273,7 @@ int crum_snapshot_noalloc(crum_ctx* c, const crum_region* regions, uint32_t n_re
             CRUM_TRY_C(hipMemcpyAsync(h_image, staging,
                                       data_off + (D << ps) + round_up(4 * D, 8),
                                       hipMemcpyDeviceToHost, stream));
-    } else {
+    } else if (!by_args) {
         CRUM_TRY_C(hipEventRecord(c->ev_upload, stream));
     }
     if (!d_status)

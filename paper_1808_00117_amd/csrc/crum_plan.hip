@@ -163,7 +163,7 @@ int crum_plan_create(crum_ctx* c, const crum_request* reqs, uint32_t n_reqs, voi
         Q.flags = any_shadow(r.regions, r.n_regions) ? kReqShadow : 0;
         Q.seq = r.seq;
         Q.page_shift = ps;
-        Q.init_fix = crc_init_fix(r.page_size);
+        Q.init_fix = crc_tables().init_fix[ps];
         req_unit0[q] = unit;
         uint64_t g = 0;
         for (uint32_t i = 0; i < r.n_regions; ++i, ++ri) {
