@@ -1480,20 +1480,23 @@ struct WaveRole {
     }
 };
 
-// Called once by every workgroup of a request after its atomics: true in
+// Called once by every workgroup of a request after thread 0's atomics: true in
 // exactly one of them, the last to arrive, which then sees every other
-// workgroup's atomics.  Not called when a request has one workgroup.
+// workgroup's atomics.  Only atomics meet here, so thread 0 waits for its own to be
+// done (a workgroup release) before it counts itself; a device fence would
+// write the L2 back first, one workgroup after the other (the 8 GiB table's header
+// took 13.4 us with device fences, 12.0 without; 1.5 GiB of 4 KiB pages 17.1 and
+// 15.0).  Not called when a request has one workgroup.
 __device__ __forceinline__ bool last_arrival(uint32_t* count, uint32_t nb, uint32_t* s_flag)
 {
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
         *s_flag = atomicAdd(count, 1u) == nb - 1 ? 1u : 0u;
+    }
     __syncthreads();
     const bool last = *s_flag != 0;
     __syncthreads();
-    if (last)
-        __threadfence();
     return last;
 }
 
