@@ -1165,17 +1165,18 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
                                  np_shift, pc_shift, d_partials, d_crcs, staging, d_glob,
                                  c->d_tabs, stream));
     }
-    {
+    void* d_status = mapped_status(h_status);
+    if (D) {
         Span sp(c, kTScatter, stream);
         CRUM_TRY(launch_pack(kModeScatter, d_regs, n_regions, d_reqs, d_out, d_list,
                              SlotRange{0, D, nullptr, 0, D}, np_shift, pc_shift, nullptr,
                              staging, d_crcs, d_partials, c->d_tabs, d_glob,
                              c->shape.pack_blocks, stream,
                              ctx_pack_flags(c, (D << ps) * (flags & CRUM_UPDATE_SHADOW ? 2 : 1)),
-                             (flags & CRUM_UPDATE_SHADOW) ? 1 : 0));
+                             (flags & CRUM_UPDATE_SHADOW) ? 1 : 0, nullptr, d_status));
+    } else {
+        CRUM_TRY(launch_restore_finish(d_out, 1, d_glob, stream, d_status));
     }
-    void* d_status = mapped_status(h_status);
-    CRUM_TRY(launch_restore_finish(d_out, 1, d_glob, stream, d_status));
     if (!d_status)
         CRUM_TRY(hipMemcpyAsync(h_status, d_out, sizeof(crum_status), hipMemcpyDeviceToHost,
                                 stream));

@@ -219,13 +219,15 @@ hipError_t launch_list(const uint64_t* bitmap, const uint32_t* prefix, uint64_t 
 // per-unit flags of the same page space (4-byte aligned, padded to whole
 // words); units flagged clean are then read from the shadow.  nt: kPackNt*
 // bits.  update_shadow (scatter only): pages go to the shadows as well.  runs
-// (may be null; verify, scatter, pull): the slots, instead of range.
+// (may be null; verify, scatter, pull): the slots, instead of range.  A scatter
+// of a range also does what launch_restore_finish does, with h_status.
 hipError_t launch_pack(int mode, const DevRegion* regs, uint32_t n_regs, const DevRequest* reqs,
-                       const DevReqOut* out, const uint32_t* list, SlotRange range,
+                       DevReqOut* out, const uint32_t* list, SlotRange range,
                        uint32_t np_shift, uint32_t piece_shift, const uint8_t* unit_flags,
                        uint8_t* staging, uint32_t* crc_out, uint32_t* partials,
                        const CrcTables* tabs, DevGlobal* glob, int blocks, hipStream_t s, int nt,
-                       int update_shadow = 0, const RunList* runs = nullptr);
+                       int update_shadow = 0, const RunList* runs = nullptr,
+                       void* h_status = nullptr);
 hipError_t launch_finalize(int mode, const DevRegion* regs, uint32_t n_regs,
                            const DevRequest* reqs, const DevReqOut* out, const uint32_t* list,
                            SlotRange range, uint32_t np_shift, uint32_t piece_shift,

@@ -991,12 +991,35 @@ __device__ __forceinline__ RunSlot run_slot(const RunList& runs, uint64_t i)
     return {runs.first[r] + (i - base), runs.first[r] + (runs.end[r] - base)};
 }
 
+// Final code of a restore, once its checks are done (one thread); with h_status
+// (pinned), the status goes there too.
+__device__ __forceinline__ void restore_finish(DevReqOut& O, const DevGlobal& G,
+                                               uint64_t* h_status)
+{
+    int32_t code = 0;
+    uint32_t bad = 0;
+    if (G.fmt_bad) {
+        code = -4;  // CRUM_EFORMAT
+    } else if (G.crc_bad != kNoBad) {
+        code = -3;  // CRUM_ECRC
+        bad = G.crc_bad;
+    }
+    O.code = code;
+    O.first_bad = bad;
+    if (h_status) {
+        h_status[0] = (uint32_t)code | (uint64_t)bad << 32;
+        h_status[1] = O.n_dirty;
+        h_status[2] = O.total_pages;
+        h_status[3] = O.image_bytes;
+    }
+}
+
 // Work item = (slot, piece); pieces per slot = 2^np_shift for the launch.
 // Pack: copy the dirty page into the image's page area (and the shadow) and
 // write its CRC to crc_out[slot].  Verify: recompute the CRC of a packed page
 // of the image and compare with the image's CRC array.  Scatter: copy the
 // packed page to its page (and, with update_shadow, its shadow), unless a check
-// before found the image bad.
+// before found the image bad; its first thread then writes the restore's status.
 //
 // A wave works through its items as one stream of 4 KiB batches, whichever
 // page they belong to: the loads of the next batch are in flight while the
@@ -1020,7 +1043,7 @@ __device__ __forceinline__ RunSlot run_slot(const RunList& runs, uint64_t i)
 template <int MODE, bool NT_LOAD, bool NT_STORE, bool RUNS = false>
 __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ regs, uint32_t n_regs,
                                               const DevRequest* __restrict__ reqs,
-                                              const DevReqOut* __restrict__ out,
+                                              DevReqOut* __restrict__ out,
                                               const uint32_t* __restrict__ list, SlotRange sr,
                                               uint32_t np_shift, uint32_t piece_shift,
                                               const uint8_t* __restrict__ unit_flags,
@@ -1029,9 +1052,12 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
                                               uint32_t* __restrict__ partials,
                                               const CrcTables* __restrict__ tabs,
                                               DevGlobal* __restrict__ glob,
-                                              uint32_t update_shadow, RunList runs)
+                                              uint32_t update_shadow, RunList runs,
+                                              uint64_t* __restrict__ h_status)
 {
     constexpr bool CRC = MODE != kModeScatter;
+    if (MODE == kModeScatter && !RUNS && blockIdx.x == 0 && threadIdx.x == 0)
+        restore_finish(out[0], *glob, h_status);
     __shared__ __attribute__((aligned(16))) uint32_t lds[CRC ? kCrcLdsWords : 4];
     if (MODE != kModePack && glob->fmt_bad)
         return;
@@ -1213,11 +1239,11 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
 }
 
 hipError_t launch_pack(int mode, const DevRegion* regs, uint32_t n_regs, const DevRequest* reqs,
-                       const DevReqOut* out, const uint32_t* list, SlotRange range,
+                       DevReqOut* out, const uint32_t* list, SlotRange range,
                        uint32_t np_shift, uint32_t piece_shift, const uint8_t* unit_flags,
                        uint8_t* staging, uint32_t* crc_out, uint32_t* partials,
                        const CrcTables* tabs, DevGlobal* glob, int blocks, hipStream_t s,
-                       int nt, int update_shadow, const RunList* runs)
+                       int nt, int update_shadow, const RunList* runs, void* h_status)
 {
     const uint64_t max_items = (runs ? runs->end[runs->n - 1] : range.max_slots) << np_shift;
     if (max_items == 0)
@@ -1230,7 +1256,8 @@ hipError_t launch_pack(int mode, const DevRegion* regs, uint32_t n_regs, const D
 #define CRUM_PACK_R(M, L, S, F, ...)                                                           \
     hipLaunchKernelGGL((k_pack<M, L, S, ##__VA_ARGS__>), grid, dim3(256), 0, s, regs, n_regs,   \
                        reqs, out, list, range, np_shift, piece_shift, F, staging, crc_out,      \
-                       partials, tabs, glob, (uint32_t)update_shadow, runs ? *runs : RunList{})
+                       partials, tabs, glob, (uint32_t)update_shadow, runs ? *runs : RunList{}, \
+                       static_cast<uint64_t*>(h_status))
 #define CRUM_PACK(M, L, S, F) CRUM_PACK_R(M, L, S, F)
 #define CRUM_PACK_NT(M, F)                                                                     \
     switch (nt & (kPackNtLoad | kPackNtStore)) {                                               \
@@ -1865,27 +1892,10 @@ hipError_t launch_restore_check(const DevRequest* reqs, uint32_t n_reqs, uint32_
     return hipGetLastError();
 }
 
-// Final code of a restore; with h_status, the status goes there too.
 __global__ void k_restore_finish(DevReqOut* __restrict__ out, DevGlobal* __restrict__ glob,
                                  uint64_t* __restrict__ h_status)
 {
-    DevReqOut& O = out[0];
-    int32_t code = 0;
-    uint32_t bad = 0;
-    if (glob->fmt_bad) {
-        code = -4;  // CRUM_EFORMAT
-    } else if (glob->crc_bad != kNoBad) {
-        code = -3;  // CRUM_ECRC
-        bad = glob->crc_bad;
-    }
-    O.code = code;
-    O.first_bad = bad;
-    if (h_status) {
-        h_status[0] = (uint32_t)code | (uint64_t)bad << 32;
-        h_status[1] = O.n_dirty;
-        h_status[2] = O.total_pages;
-        h_status[3] = O.image_bytes;
-    }
+    restore_finish(out[0], *glob, h_status);
 }
 
 hipError_t launch_restore_finish(DevReqOut* out, uint32_t, DevGlobal* glob, hipStream_t s,
