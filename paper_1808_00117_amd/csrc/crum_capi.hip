@@ -1154,12 +1154,31 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
         CRUM_TRY(launch_scan(img_bitmap, 0, W, d_prefix, nullptr, 1, d_reqs, 0, 1, d_out,
                              d_glob, 0, 1, d_list, stream, FlagSource{}));
     }
+    // An image that the last-level cache does not hold is verified with plain
+    // loads towards its end, which leaves that end cached, and scattered from
+    // there backwards: 280 MB of 64 KiB pages with shadows 257 -> 226 us, 768 MB
+    // of 4 KiB pages with shadows 645 -> 621, 1 GiB of 64 KiB pages 617 -> 602.
+    // A smaller image stays cached by itself and is verified faster with
+    // non-temporal loads (200 MB: 158 us, 176 with plain ones).  Plain loads are
+    // slower for what is not kept, too, so from twice the cache's size on that
+    // part has a launch of its own (1 GiB: 618 us in one launch); below, the
+    // launch costs more (512 MB: 316 and 320 us).  A switch from one kind of
+    // load to the other inside the kernel doubles its stream loop and took
+    // 420 us for 512 MB.
+    uint64_t keep = 0;
+    if ((flags & CRUM_VERIFY) && D << ps > kCachedBytes)
+        keep = D << ps > 2 * kCachedBytes ? kCachedBytes >> ps : D;
     if (flags & CRUM_VERIFY) {
         Span sp(c, kTVerify, stream);
         SlotRange sr{0, D, nullptr, 0, D};
-        CRUM_TRY(launch_pack(kModeVerify, d_regs, n_regions, d_reqs, d_out, d_list, sr, np_shift,
-                             pc_shift, nullptr, staging, d_crcs, d_partials, c->d_tabs,
-                             d_glob, c->shape.pack_blocks, stream, ctx_pack_flags(c, 0)));
+        const uint64_t cut = D - keep;
+        for (const SlotRange& v : {SlotRange{0, cut, nullptr, 0, cut},
+                                   SlotRange{cut, D, nullptr, 0, keep}})
+            CRUM_TRY(launch_pack(kModeVerify, d_regs, n_regions, d_reqs, d_out, d_list, v,
+                                 np_shift, pc_shift, nullptr, staging, d_crcs,
+                                 d_partials + (v.lo << np_shift), c->d_tabs, d_glob,
+                                 c->shape.pack_blocks, stream,
+                                 v.lo == cut && keep ? 0 : ctx_pack_flags(c, 0)));
         sp.end();  // k_finalize is not part of the verify's timing
         CRUM_TRY(launch_finalize(kModeVerify, d_regs, n_regions, d_reqs, d_out, d_list, sr,
                                  np_shift, pc_shift, d_partials, d_crcs, staging, d_glob,
@@ -1169,8 +1188,8 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
     if (D) {
         Span sp(c, kTScatter, stream);
         CRUM_TRY(launch_pack(kModeScatter, d_regs, n_regions, d_reqs, d_out, d_list,
-                             SlotRange{0, D, nullptr, 0, D}, np_shift, pc_shift, nullptr,
-                             staging, d_crcs, d_partials, c->d_tabs, d_glob,
+                             SlotRange{0, D, nullptr, 0, D, keep ? 1u : 0u}, np_shift, pc_shift,
+                             nullptr, staging, d_crcs, d_partials, c->d_tabs, d_glob,
                              c->shape.pack_blocks, stream,
                              ctx_pack_flags(c, (D << ps) * (flags & CRUM_UPDATE_SHADOW ? 2 : 1)),
                              (flags & CRUM_UPDATE_SHADOW) ? 1 : 0, nullptr, d_status));

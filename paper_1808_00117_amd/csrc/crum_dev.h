@@ -129,6 +129,7 @@ struct SlotRange {
     const uint64_t* bounds;
     uint32_t chunk;
     uint64_t max_slots;  // upper bound on hi - lo (grid sizing)
+    uint32_t backward = 0;  // scatter: last slot first
 };
 
 // Runs of consecutive slots laid end to end, for launches over several at once

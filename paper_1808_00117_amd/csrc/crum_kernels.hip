@@ -1096,7 +1096,9 @@ __global__ __launch_bounds__(256, 4) void k_pack(const DevRegion* __restrict__ r
     // the first item at or after `item` (this wave's items) that is a piece
     auto find = [&](uint64_t item, Piece& p) __attribute__((always_inline)) -> bool {
         for (; item < n_items; item += n_waves) {
-            uint64_t k = slot0 + (item >> np_shift);
+            uint64_t k = MODE == kModeScatter && !RUNS && sr.backward
+                             ? slot1 - 1 - (item >> np_shift)
+                             : slot0 + (item >> np_shift);
             if (RUNS) {
                 const RunSlot s = run_slot(runs, k);
                 k = s.slot;
