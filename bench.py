@@ -169,7 +169,7 @@ def pmc_summary(fetch_dir: str, write_dir: str, workload: str) -> dict:
     return res
 
 
-def pmc_table(d: str, kernels=("k_pack<0", "k_pack<1", "k_diff", "k_scatter")) -> str:
+def pmc_table(d: str, kernels=("k_pack<0", "k_pack<1", "k_diff", "k_pack<2")) -> str:
     """Markdown table of a rocprofv3 --pmc run: per kernel (matched by name
     prefix) the dispatch count and the mean of each counter per dispatch."""
     import csv

@@ -134,12 +134,15 @@ int crum_image_bytes(uint32_t n_regions, uint64_t total_pages, uint64_t n_dirty,
  * with their CRC-32C -> image header, all built in d_staging in the image
  * layout above, and the drain of the image to h_image on the context's side
  * stream; `stream` is made to wait for the drain.  The calling thread blocks
- * only on small device-to-host reads of dirty counts.  Two orders give the
+ * only until the device has stored the dirty counts that size the drain's
+ * copies (words in pinned memory, which it reads).  Two orders give the
  * same image: when both capacities hold an image with every page dirty and
  * CRUM_PARAM_EAGER is 1, the page space is processed in chunks and each chunk
  * is drained while later chunks are diffed (an image of one chunk is drained
- * in one copy behind the header); otherwise the whole diff and the capacity
- * check run first, then pack chunks with their drain behind them.  A third order applies when an image with every page dirty is at most
+ * in one copy behind the header, on `stream` itself; without h_image there is
+ * one chunk and the calling thread does not wait); otherwise the whole diff and
+ * the capacity check run first, then pack chunks with their drain behind them.
+ * A third order applies when an image with every page dirty is at most
  * CRUM_PARAM_DIRECT_BYTES and h_image is host memory the device maps at the
  * same address (hipHostMalloc): the pack and header kernels write the image
  * straight into h_image, d_staging is not written, and the calling thread
@@ -250,8 +253,8 @@ int crum_snapshot_tracked(crum_ctx* ctx, const crum_region* regions, uint32_t n_
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Arguments, result and image as crum_snapshot's, always in its diff-first
  * order (whole diff, capacity check, one pack launch, header), the image
- * copied to h_image with one hipMemcpyAsync on `stream`; the calling thread
- * waits for the dirty count.  The device scratch is a fixed array of
+ * copied to h_image with one hipMemcpyAsync on `stream`; with h_image, the
+ * calling thread waits for the dirty count.  The device scratch is a fixed array of
  * CRUM_NOALLOC_SCRATCH_BYTES per device (held until the process ends), the
  * host side a pinned buffer allocated by crum_ctx_create: no call allocates.
  * Inputs whose scratch would not fit (more than CRUM_NOALLOC_MAX_REGIONS
@@ -277,8 +280,8 @@ int crum_snapshot_noalloc(crum_ctx* ctx, const crum_region* regions, uint32_t n_
  * smaller ones), and grouped in that order (groups of whole requests,
  * scanned bytes per group starting at CRUM_PARAM_CHUNK_BYTES and growing by
  * CRUM_PARAM_CHUNK_GROWTH up
- * to CRUM_PARAM_CHUNK_MAX_BYTES); each group's device work -- one persistent diff
- * over all units of its requests, bitmap, scan, compaction, pack with CRCs and
+ * to CRUM_PARAM_CHUNK_MAX_BYTES); each group's device work -- one diff over all
+ * units of its requests, bitmap, scan, compaction, pack with CRCs and
  * headers -- is captured once as a HIP graph at plan creation.  Request images
  * are laid out back to back in processing order in d_staging (each at a 4
  * KiB-aligned offset) and
@@ -420,7 +423,8 @@ void crum_server_destroy(crum_server* server);
  *   compute unit).
  * CRUM_PARAM_CHUNK_BYTES / CRUM_PARAM_CHUNK_MAX_BYTES: scanned bytes of the
  *   first and of the largest chunk when a snapshot with a host image is
- *   pipelined by chunks (128 MiB / 4 GiB); chunks grow by CRUM_PARAM_CHUNK_GROWTH up to the maximum.
+ *   pipelined by chunks (128 MiB / 4 GiB); chunks grow by
+ *   CRUM_PARAM_CHUNK_GROWTH up to the maximum.
  * CRUM_PARAM_EAGER: 1 pipelines the snapshot by chunks whenever the staging
  *   and host capacities hold an image with every page dirty (so ENOSPC is
  *   impossible); 0 always runs the whole diff first (1).
@@ -450,7 +454,8 @@ void crum_server_destroy(crum_server* server);
  *   non-temporal stores; 0 does so only for images of more than 256 MiB scanned
  *   that stay on the device and restores that write as much (0).
  * CRUM_PARAM_PACK_NT_LOAD: 1 reads the pages in the pack and verify kernels
- *   with non-temporal loads, which are not kept in the caches (1).
+ *   with non-temporal loads, which are not kept in the caches, except for the
+ *   last 256 to 512 MiB verified of an image of more than 256 MiB (1).
  * CRUM_PARAM_DIFF_GROUP: 4 KiB diff units per wave of the diff kernel, 1, 2
  *   or 4, for launches whose smallest unit is 4 KiB: 2 or 4 units of one
  *   region are read as one span with 8 or 16 loads per array in flight per

@@ -13,9 +13,9 @@ constexpr uint32_t kUnitShiftDefault = 14;
 constexpr uint32_t kPieceShift = 16;  // largest pack piece: 64 KiB
 constexpr uint32_t kPieceShiftMin = 12;
 // Default piece: 16 KiB.  Four times the waves of whole 64 KiB pages per
-// launch; on the 16 GiB workload's 23 117 dirty 64 KiB pages the pack ran at
-// 4.15-4.43 TB/s pipelined and 5.27-5.32 TB/s in one launch with 16 KiB
-// pieces, against 3.87-3.92 and 5.13-5.26 TB/s with 64 KiB ones.
+// launch; on the 16 GiB workload's 23 117 dirty 64 KiB pages the table-driven
+// pack ran at 4.15-4.43 TB/s pipelined and 5.27-5.32 TB/s in one launch with
+// 16 KiB pieces, against 3.87-3.92 and 5.13-5.26 TB/s with 64 KiB ones.
 constexpr uint32_t kPieceShiftDefault = 14;
 // Flags of launch_pack.
 constexpr int kPackNtStore = 1;  // the image is written with non-temporal stores
@@ -118,7 +118,7 @@ struct CrcTables {
 enum PackMode { kModePack = 0, kModeVerify = 1, kModeScatter = 2, kModePull = 3 };
 
 struct LaunchShape {
-    int diff_blocks;   // persistent grid of the diff kernel (256-thread blocks)
+    int diff_blocks;   // largest grid of a limited diff (256-thread blocks)
     int pack_blocks;   // persistent grid of the pack/verify/scatter kernels
 };
 

@@ -21,7 +21,7 @@
 //   k_header  per request, over one or more workgroups: header, region
 //             table, bitmap, CRC array, pads, crcs_crc, meta_crc.
 // Restore: k_restore_check (the image's own checks, also over one or more
-// workgroups), k_scan, k_list, k_pack (verify), k_scatter.
+// workgroups), k_scan, k_list, k_pack (verify), k_pack (scatter).
 //
 // CRC-32C on the device.  The polynomial arithmetic is in gf2.h.  Page bytes go
 // through the matrix cores (k_pack): a raw CRC is linear over GF(2), so the 32

@@ -27,8 +27,8 @@
 //
 // The host-to-device copies run on the context's side stream (creating a
 // stream per session costs more than the rest of open), and the caller's
-// stream waits for each touch's copies before its checks and scatters: the copies of the next fault then overlap the kernels of this
-// one.  Every run has its own slots of the staging buffer, so a copy never
+// stream waits for each touch's copies before its checks and scatters: the
+// copies of the next fault then overlap the kernels of this one.  Every run has its own slots of the staging buffer, so a copy never
 // overwrites bytes a kernel still reads.  The checks and scatter of a short
 // run cut its pages into smaller pieces, so that it still spreads over many
 // waves (the piece CRCs are combined as for large pages).

@@ -2,14 +2,15 @@
 // HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).
 //
 // It computes what crum_snapshot computes (same kernels, same image), in the
-// diff-first order: the whole diff, the scan with the capacity check, one
-// read-back of the dirty count, the compaction list, one pack launch over all
-// dirty pages, the header, and one copy of the whole image to h_image.  Its
+// diff-first order: the whole diff, the scan with the capacity check, which
+// stores the dirty count in pinned memory, the compaction list, one pack launch
+// over all dirty pages, the header, and one copy of the whole image to h_image,
+// enqueued once the count is there.  Its
 // device scratch (region table, unit flags, bitmap, prefix sums, slot list,
 // CRC array, piece CRCs, counters) is the file-scope array below, of
 // CRUM_NOALLOC_SCRATCH_BYTES bytes: one copy per device, held until the
 // process ends, its address taken once per device when a context is created
-// there.  Uploads and the count read-back go through a small pinned buffer
+// there.  Uploads and the count go through a small pinned buffer
 // that the context allocates when it is created.  Nothing is allocated per
 // call: no hipMalloc, hipHostMalloc, event or stream creation.
 //

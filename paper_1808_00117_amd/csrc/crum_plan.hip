@@ -1,7 +1,7 @@
 // Batched snapshots: many requests (each its own region table, page size and
 // image) flattened into one page space and run as a sequence of captured HIP
-// graphs, one per group of whole requests.  Each group's graph runs one
-// persistent diff over all units of its requests, the bitmap, the scan (which
+// graphs, one per group of whole requests.  Each group's graph runs one diff
+// over all units of its requests, the bitmap, the scan (which
 // lays the group's images out back to back in staging and checks capacity),
 // the compaction list, the pack with CRCs, and the headers.  The host drains
 // each group's images with one contiguous copy as soon as the group is done,
