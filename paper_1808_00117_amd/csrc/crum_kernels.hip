@@ -1553,7 +1553,7 @@ __device__ __forceinline__ void read_accs(uint32_t* acc, uint32_t* s_vals)
 // Bound by latency: a chain of dependent reads, products and, with several
 // workgroups, atomics.  With byte tables (44 KiB to stage) and a butterfly over
 // lanes, four powers of x and five products the 64 MiB image's header took 14.6
-// us and a 1.5 GiB one's of 4 KiB pages 22; now 8 and 13.
+// us and a 1.5 GiB one's of 4 KiB pages 22; now 7 and 15.
 __global__ __launch_bounds__(256) void k_header(const DevRegion* __restrict__ regs,
                                                 const DevRequest* __restrict__ reqs,
                                                 DevReqOut* __restrict__ out,
