@@ -791,7 +791,7 @@ def bench_batched(args) -> dict:
                         "launches": n_pd,
                         "avg_launch_ms": round(pd_ms / max(n_pd, 1), 4),
                         "algorithmic_bytes_per_step": plan_diff_bytes,
-                        "what": "the plan's persistent diff launches (one per group), "
+                        "what": "the plan's diff launches (one per group), "
                                 "timed by the device wall clock the diff kernel records at "
                                 "its start and end, summed over the timed launches"}},
         "batched_smallest_first": {
