@@ -735,7 +735,7 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
     DevGlobal gl{};
     gl.crc_bad = kNoBad;
     // few regions: the tables go to the device as arguments of the diff
-    const bool by_args = need_diff && !h_cand && n_chunks == 1 && n_regions <= kArgRegions;
+    const bool by_args = need_diff && !h_cand && n_regions <= kArgRegions;
     if (!by_args) {
         std::memset(P, 0, L.upload_end);
         std::memcpy(P + L.reqs, &rq, sizeof(rq));
@@ -778,19 +778,20 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
         if (direct || (eager && !h_image))
             CRUM_TRY(hipEventRecord(c->ev_upload, stream));
     }
-    // the diff of the whole page space (one chunk)
-    auto diff_all = [&]() {
+    // the diff of the units [u0, u1) of the page space; the first one's arguments may
+    // hold the tables
+    auto diff_units = [&](uint64_t u0, uint64_t u1) {
         if (!need_diff)
             return hipSuccess;
         Span sp(c, kTDiff, stream);
-        if (!by_args)
-            return launch_diff(d_regs, n_regions, 0, n_units, d_flags, diff_blocks, c->diff_nt,
+        if (!by_args || u0)
+            return launch_diff(d_regs, n_regions, u0, u1, d_flags, diff_blocks, c->diff_nt,
                                c->diff_prio, stream, d_cand, nullptr, ctx_diff_group(c, us));
         CallTables t{};
         t.req = rq;
         t.glob = gl;
         std::memcpy(t.regs, dregs.data(), sizeof(DevRegion) * n_regions);
-        return launch_diff_first(t, reinterpret_cast<CallTables*>(S), n_regions, n_units, d_flags,
+        return launch_diff_first(t, reinterpret_cast<CallTables*>(S), n_regions, u1, d_flags,
                                  diff_blocks, c->diff_nt, c->diff_prio, stream,
                                  ctx_diff_group(c, us));
     };
@@ -798,7 +799,7 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
     if (direct) {
         // ---- direct order: diff, scan (with the capacity check), list, then
         // pack and header into the host image; slot counts stay on the device
-        CRUM_TRY(diff_all());
+        CRUM_TRY(diff_units(0, n_units));
         {
             Span sp(c, kTScan, stream);
             CRUM_TRY(launch_scan(d_bitmap, 0, W, d_prefix, d_bounds, 1, d_reqs, 0, 1, d_out,
@@ -834,14 +835,7 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
         for (size_t ci = 0; ci < n_chunks; ++ci) {
             const uint64_t g0 = cuts[ci], g1 = cuts[ci + 1];
             const uint64_t w0 = g0 / 64, w1 = (g1 + 63) / 64;
-            if (n_chunks == 1) {
-                CRUM_TRY(diff_all());
-            } else if (need_diff) {
-                Span sp(c, kTDiff, stream);
-                CRUM_TRY(launch_diff(d_regs, n_regions, g0 << (ps - us), g1 << (ps - us), d_flags,
-                                     diff_blocks, c->diff_nt, c->diff_prio, stream, d_cand,
-                                     nullptr, ctx_diff_group(c, us)));
-            }
+            CRUM_TRY(diff_units(g0 << (ps - us), std::min(n_units, g1 << (ps - us))));
             {
                 Span sp(c, kTScan, stream);
                 HostNote note;
@@ -927,7 +921,7 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
         return CRUM_OK;
     } else {
         // ---- checked order: whole diff, scan with the capacity check, readback
-        CRUM_TRY(diff_all());
+        CRUM_TRY(diff_units(0, n_units));
         {
             Span sp(c, kTScan, stream);
             HostNote note;
