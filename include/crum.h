@@ -138,8 +138,8 @@ int crum_image_bytes(uint32_t n_regions, uint64_t total_pages, uint64_t n_dirty,
  * copies (words in pinned memory, which it reads).  Two orders give the
  * same image: when both capacities hold an image with every page dirty and
  * CRUM_PARAM_EAGER is 1, the page space is processed in chunks and each chunk
- * is drained while later chunks are diffed (the prefix before the pages, and an
- * image of one chunk as a whole, are copied behind the header on `stream` itself; without h_image there is
+ * is drained while later chunks are diffed (an image of one chunk is drained
+ * in one copy behind the header, on `stream` itself; without h_image there is
  * one chunk and the calling thread does not wait); otherwise the whole diff and
  * the capacity check run first, then pack chunks with their drain behind them.
  * A third order applies when an image with every page dirty is at most

@@ -880,12 +880,6 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
             CRUM_TRY(hipMemcpyAsync(himg, staging, image_bytes, hipMemcpyDeviceToHost, stream));
         } else if (himg) {
             CRUM_TRY(hipEventRecord(c->ev_hdr, stream));
-            {
-                // beside the last chunk's copy: before it on the side stream it cost
-                // 5 us (500 MiB with 63 MB dirty 1233 and 1228, 1.8 GiB 3138 and 3133)
-                Span sp(c, kTDrain, stream);
-                CRUM_TRY(hipMemcpyAsync(himg, staging, data_off, hipMemcpyDeviceToHost, stream));
-            }
             // ---- drain each chunk as soon as its count is known; the last one
             // with the CRC array behind it, after the header
             uint64_t prev = 0;
@@ -897,6 +891,9 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
                 uint64_t bytes = (cnt - prev) << ps;
                 if (last) {
                     CRUM_TRY(hipStreamWaitEvent(c->side, c->ev_hdr, 0));
+                    Span sp(c, kTDrain, c->side);
+                    CRUM_TRY(hipMemcpyAsync(himg, staging, data_off, hipMemcpyDeviceToHost,
+                                            c->side));
                     bytes += round_up(4 * cnt, 8);
                 } else if (bytes) {
                     CRUM_TRY(hipStreamWaitEvent(c->side, c->ev_chunk[ci], 0));
@@ -910,15 +907,14 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
                 prev = cnt;
             }
         }
-        if (himg && n_chunks > 1) {
-            CRUM_TRY(hipEventRecord(c->ev_chunk[n_chunks - 1], c->side));
-            CRUM_TRY(hipStreamWaitEvent(stream, c->ev_chunk[n_chunks - 1], 0));
-        }
+        hipStream_t end = himg && n_chunks > 1 ? c->side : stream;
         if (!d_status)
             CRUM_TRY(hipMemcpyAsync(h_status, d_out, sizeof(crum_status), hipMemcpyDeviceToHost,
-                                    stream));
-        CRUM_TRY(hipEventRecord(c->ev_done, stream));
+                                    end));
+        CRUM_TRY(hipEventRecord(c->ev_done, end));
         c->partial_call = false;
+        if (end != stream)
+            CRUM_TRY(hipStreamWaitEvent(stream, c->ev_done, 0));
         return CRUM_OK;
     } else {
         // ---- checked order: whole diff, scan with the capacity check, readback
