@@ -686,14 +686,23 @@ __global__ __launch_bounds__(1024) void k_scan(uint64_t* __restrict__ bitmap, ui
     if (fs.regs) {
         const uint64_t first = lane < fs.n_regs ? fs.regs[lane].first_page : ~0ull;
         uint32_t r[kScanFlagWords / 16] = {};
-        for (uint32_t k = 1; k < fs.n_regs; ++k) {
-            const uint64_t f =
-                (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)first, (int)k) |
-                (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(first >> 32), (int)k)
-                    << 32;
+        // a lane per region: the region of a word's first page by one ballot, then
+        // only the regions that start inside the word are looked at one by one
+        // (comparing every page with every start took 11 us for 64 regions)
 #pragma unroll
-            for (uint32_t i = 0; i < kScanFlagWords / 16; ++i)
-                r[i] += f <= (w0 + wv + 16 * i) * 64 + lane;
+        for (uint32_t i = 0; i < kScanFlagWords / 16; ++i) {
+            const uint64_t p0 = (w0 + wv + 16 * i) * 64;
+            if (p0 >= w1 * 64)
+                break;
+            r[i] = (uint32_t)__popcll(__ballot(first <= p0)) - 1;
+            for (uint64_t in = __ballot(first > p0 && first <= p0 + 63); in; in &= in - 1) {
+                const int k = __builtin_ctzll(in);
+                const uint64_t f =
+                    (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)first, k) |
+                    (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(first >> 32), k)
+                        << 32;
+                r[i] += f <= p0 + lane;
+            }
         }
 #pragma unroll
         for (uint32_t i = 0; i < kScanFlagWords / 16; ++i) {
