@@ -12,8 +12,9 @@ namespace crum {
 
 constexpr int kTimingClasses = 7;
 // Pinned buffer of crum_snapshot_noalloc, allocated with the context: the
-// upload (region table, request, counters) and read-back below
-// kNoAllocSortOff, the argument check's interval sort above it.
+// upload (region table, request, counters) first, the dirty count at
+// kNoAllocCountOff, the argument check's interval sort from kNoAllocSortOff on.
+constexpr uint64_t kNoAllocCountOff = (160ull << 10) - 64;
 constexpr uint64_t kNoAllocSortOff = 160ull << 10;
 constexpr uint64_t kNoAllocPinnedBytes = 256ull << 10;
 // Address of crum_snapshot_noalloc's device scratch on `device` (current).
@@ -134,7 +135,19 @@ struct crum_ctx {
     CrcTables* d_tabs = nullptr;
     uint8_t* d_scratch = nullptr;
     size_t scratch_cap = 0;
-    uint8_t* h_pin = nullptr;  // uploads, then readback area
+    // Pinned words of the context that kernels read or write: h_pin (uploaded
+    // tables, then the words that crum_snapshot's scans and crum_restore's header
+    // copy store) and na_pin (the same for crum_snapshot_noalloc).  A call may
+    // return with its kernels still queued, and the next one writes these
+    // words again after a wait for ev_upload alone, so
+    //  - a kernel stores a word only for a call that waits for it before it
+    //    returns: the counts of calls with a host image or in the diff-first
+    //    order of crum_snapshot, the restore's header;
+    //  - a call that uploads either waits for such a word, stored behind the
+    //    upload's reads, or records ev_upload behind them;
+    //  - a call that stops before its waits leaves partial_call set, and the next
+    //    one waits for the whole device.
+    uint8_t* h_pin = nullptr;
     size_t pin_cap = 0;
     hipEvent_t ev_upload = nullptr, ev_done = nullptr, ev_hdr = nullptr;
     std::vector<hipEvent_t> ev_chunk;  // pack of chunk i done

@@ -175,9 +175,9 @@ int crum_snapshot_noalloc(crum_ctx* c, const crum_region* regions, uint32_t n_re
     const NaLayout L = na_layout(n_regions, n_units, W, np_shift ? (W * 64) << np_shift : 0);
     if (L.total > CRUM_NOALLOC_SCRATCH_BYTES)
         return CRUM_ELIMIT;
-    const uint64_t rb_off = round_up(L.upload_end, 256);
-    static_assert(64 * CRUM_NOALLOC_MAX_REGIONS + 1024 <= kNoAllocSortOff,
-                  "upload and read-back below the sort's room");
+    static_assert(64 * CRUM_NOALLOC_MAX_REGIONS + 1024 <= kNoAllocCountOff,
+                  "upload below the count");
+    static_assert(kNoAllocCountOff + 8 <= kNoAllocSortOff, "count below the sort's room");
     static_assert(kNoAllocSortOff + 2 * CRUM_NOALLOC_MAX_REGIONS * 16 <= kNoAllocPinnedBytes,
                   "sort room inside the pinned buffer");
 
@@ -225,15 +225,17 @@ int crum_snapshot_noalloc(crum_ctx* c, const crum_region* regions, uint32_t n_re
     uint32_t* d_partials = reinterpret_cast<uint32_t*>(S + L.partials);
     uint64_t* d_bounds = reinterpret_cast<uint64_t*>(S + L.bounds);
     uint8_t* staging = static_cast<uint8_t*>(d_staging);
-    uint8_t* rb = P + rb_off;
     const uint32_t hdr_blocks = header_blocks(n_regions, W, G);
 
-    uint64_t* h_count = reinterpret_cast<uint64_t*>(rb);
-    *h_count = kNoCount;
+    // stored only for a call that waits for it (see crum_ctx::h_pin)
+    uint64_t* h_count = reinterpret_cast<uint64_t*>(P + kNoAllocCountOff);
     void* d_status = mapped_status(h_status);
     const FlagSource flag_src{d_regs, n_regions, d_flags};
     HostNote note;
-    note.count = h_count;
+    if (h_image) {
+        *h_count = kNoCount;
+        note.count = h_count;
+    }
 
     // after this context's previous call (whose kernels may still use the array)
     c->partial_call = true;
