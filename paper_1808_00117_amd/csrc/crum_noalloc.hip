@@ -55,8 +55,10 @@ NaLayout na_layout(uint64_t n_regs, uint64_t n_units, uint64_t n_words, uint64_t
         off = round_up(off + bytes, 256);
         return o;
     };
-    // as in CallTables, which a call may store here
-    L.reqs = take(std::max<uint64_t>(sizeof(CallTables), offsetof(CallTables, regs) + 64 * n_regs));
+    // laid as in CallTables, which a call may store here; the 512 bytes beside the
+    // region table are part of the limit that callers meet (CRUM_ELIMIT)
+    static_assert(offsetof(CallTables, regs) <= 512, "request, results and counters");
+    L.reqs = take(round_up(64 * std::max<uint64_t>(1, n_regs), 256) + 512);
     L.out = L.reqs + offsetof(CallTables, out);
     L.glob = L.reqs + offsetof(CallTables, glob);
     L.regs = L.reqs + offsetof(CallTables, regs);
