@@ -1037,6 +1037,12 @@ static int restore_fail(crum_status* st, int code, uint64_t D, uint64_t G, uint6
 }
 
 
+// A header and table of at most this many bytes reach the host by one workgroup's
+// stores and a word behind them, a larger one by a copy: a verified rollback of
+// one page a region took 93 us with 2048 regions, 116 with 4096, 207 with 8192 and
+// 380 with 16384 by the kernel, and 107, 168, 181 and 325 by the copy.
+static constexpr uint64_t kHeaderCopyBytes = 192ull << 10;
+
 int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
                  const void* h_image, uint64_t image_bytes, uint32_t flags, void* d_staging,
                  uint64_t staging_bytes, void* stream_, crum_status* h_status)
@@ -1060,7 +1066,7 @@ int crum_restore(crum_ctx* c, const crum_region* regions, uint32_t n_regions,
     if (!h) {
         avail = std::min<uint64_t>(image_bytes, 64 + 32ull * n_regions);
         const uint64_t fetch = round_up(avail, 16);
-        if (fetch <= staging_bytes) {
+        if (fetch <= staging_bytes && avail <= kHeaderCopyBytes) {
             // header and table into the pinned buffer, with a word behind them
             // that the host watches
             CRUM_TRY(ensure_pinned(c, fetch + 16));
