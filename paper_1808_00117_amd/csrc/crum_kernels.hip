@@ -32,6 +32,7 @@
 // one message, combine by a shift by the bytes that follow them; the standard
 // CRC adds crc_init_fix(page bytes).
 #include "crum_dev.h"
+#include "diff_grid.h"
 #include "gf2.h"
 
 #include <algorithm>
@@ -527,12 +528,9 @@ hipError_t launch_diff_first(const CallTables& t, CallTables* to, uint32_t n_reg
 {
     if (group != 2 && group != 4)
         group = 1;
-    const uint64_t need = ((u1 + group - 1) / group + 3) / 4;
-    const uint64_t nb = blocks <= 0 || need < (uint64_t)blocks ? need : (uint64_t)blocks;
-    if (nb > 0x7FFFFFFFull)
-        return hipErrorInvalidValue;
+    const uint32_t nb = std::max(diff_grid(u1, (uint32_t)group, (uint32_t)blocks), 1u);
 #define CRUM_DIFF(NTV, GV)                                                                    \
-    hipLaunchKernelGGL((k_diff_first<NTV, GV>), dim3((unsigned)(nb ? nb : 1)), dim3(256), 0, s, \
+    hipLaunchKernelGGL((k_diff_first<NTV, GV>), dim3(nb), dim3(256), 0, s,                     \
                        t, to, n_regs, u1, unit_flags, (uint32_t)prio)
     switch ((nontemporal ? 8 : 0) + group) {
     case 1: CRUM_DIFF(false, 1); break;
@@ -554,12 +552,9 @@ hipError_t launch_diff(const DevRegion* regs, uint32_t n_regs, uint64_t u0, uint
         return hipSuccess;
     if (group != 2 && group != 4)
         group = 1;
-    const uint64_t need = ((u1 - u0 + group - 1) / group + 3) / 4;
-    const uint64_t nb = blocks <= 0 || need < (uint64_t)blocks ? need : (uint64_t)blocks;
-    if (nb > 0x7FFFFFFFull)
-        return hipErrorInvalidValue;
+    const uint32_t nb = diff_grid(u1 - u0, (uint32_t)group, (uint32_t)blocks);
 #define CRUM_DIFF(NTV, GV)                                                                   \
-    hipLaunchKernelGGL((k_diff<NTV, GV>), dim3((unsigned)nb), dim3(256), 0, s, regs, n_regs, \
+    hipLaunchKernelGGL((k_diff<NTV, GV>), dim3(nb), dim3(256), 0, s, regs, n_regs,           \
                        u0, u1, unit_flags, (uint32_t)prio, cand, stamp)
     if (nontemporal) {
         if (group == 4)
