@@ -417,8 +417,9 @@ void crum_server_destroy(crum_server* server);
 /* Launch and pipeline parameters of a context (defaults in parentheses).
  * They change speed only: every image is the same whatever their values.
  * CRUM_PARAM_DIFF_BLOCKS: largest grid of the diff kernel, in 256-thread
- *   workgroups, each striding over its share of the units (8 per compute unit;
- *   at this default only launches with a candidate set are limited).
+ *   workgroups, each striding over its share of the units; at most 1048576
+ *   (1048576, where launches with a candidate set take at most 8 per compute
+ *   unit).
  *   CRUM_PARAM_PACK_BLOCKS: grid of the pack, verify and scatter kernels (4 per
  *   compute unit).
  * CRUM_PARAM_CHUNK_BYTES / CRUM_PARAM_CHUNK_MAX_BYTES: scanned bytes of the

@@ -325,7 +325,7 @@ int crum_ctx_create(int device, const char* tuning_cache, crum_ctx** out)
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess &&
         cus > 0)
         c->cus = cus;
-    c->shape.diff_blocks = c->cus * 8;
+    c->shape.diff_blocks = (int)kDiffBlocksMax;
     c->shape.pack_blocks = c->cus * 4;
     bool ok = hipMalloc(reinterpret_cast<void**>(&c->d_tabs), sizeof(CrcTables)) == hipSuccess &&
               hipMemcpy(c->d_tabs, &crc_tables(), sizeof(CrcTables), hipMemcpyHostToDevice) ==
@@ -480,7 +480,7 @@ int set_param_raw(crum_ctx* c, int param, uint64_t v)
         return CRUM_EINVAL;
     switch (param) {
     case CRUM_PARAM_DIFF_BLOCKS:
-        if (v > (1u << 20))
+        if (v > kDiffBlocksMax)
             return CRUM_EINVAL;
         c->shape.diff_blocks = (int)v;
         return CRUM_OK;

@@ -2,6 +2,7 @@
 #pragma once
 #include "crum.h"
 #include "crum_dev.h"
+#include "diff_grid.h"
 
 #include <algorithm>
 #include <string>
@@ -231,14 +232,15 @@ int wait_count(const uint64_t* count, hipEvent_t ev, hipStream_t s);
 // is not pinned memory that the device maps at the same address.
 void* mapped_status(crum_status* h_status);
 
-// Grid limit of a diff launch (0: none).  By default every wave of a launch
-// takes one unit (or group) and the dispatcher balances them: 8 GiB in 64 KiB
-// pages 2505 us persistent (8 workgroups per compute unit), 2440 this way, 1.5
-// GiB of 4 KiB pages 487 and 470.  A candidate set leaves most units unread, and
-// those are cheaper to stride over than to dispatch.
+// Grid limit of a diff launch: the parameter, which by default leaves every wave
+// one unit (or group) and the balancing to the dispatcher: 8 GiB in 64 KiB pages
+// 2505 us persistent (8 workgroups per compute unit), 2440 this way, 1.5 GiB of 4
+// KiB pages 487 and 470.  A candidate set leaves most units unread, and those are
+// cheaper to stride over than to dispatch: 8 workgroups per compute unit then.
 inline int ctx_diff_blocks(const crum_ctx* c, bool cand)
 {
-    return c->shape.diff_blocks == c->cus * 8 && !cand ? 0 : c->shape.diff_blocks;
+    return c->shape.diff_blocks == (int)kDiffBlocksMax && cand ? c->cus * 8
+                                                               : c->shape.diff_blocks;
 }
 // Whether a region table needs the diff: units of regions without a shadow
 // are dirty unread, and their flags are not looked at.
