@@ -706,7 +706,7 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
     const uint32_t np_shift = ps > pc_shift ? ps - pc_shift : 0;
     const uint32_t us = std::min<uint32_t>(ps, c->unit_shift_max);
     const int pack_flags = ctx_pack_flags(c, h_image ? 0 : G << ps);
-    const int diff_blocks = ctx_diff_blocks(c, h_cand != nullptr);
+    const int diff_blocks = ctx_diff_blocks(c, h_cand || mostly_new(regions, n_regions));
     const bool need_diff = any_shadow(regions, n_regions);
     std::vector<DevRegion> dregs(std::max<uint32_t>(1, n_regions));
     uint64_t n_pages = 0, n_units = 0;

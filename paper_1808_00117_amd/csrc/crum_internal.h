@@ -235,12 +235,25 @@ void* mapped_status(crum_status* h_status);
 // Grid limit of a diff launch: the parameter, which by default leaves every wave
 // one unit (or group) and the balancing to the dispatcher: 8 GiB in 64 KiB pages
 // 2505 us persistent (8 workgroups per compute unit), 2440 this way, 1.5 GiB of 4
-// KiB pages 487 and 470.  A candidate set leaves most units unread, and those are
-// cheaper to stride over than to dispatch: 8 workgroups per compute unit then.
-inline int ctx_diff_blocks(const crum_ctx* c, bool cand)
+// KiB pages 487 and 470.  In a `sparse` launch most units are not read (a candidate
+// set, or a table where most pages have no shadow), and those are cheaper to stride
+// over than to dispatch: 8 workgroups per compute unit then (8 GiB without a shadow
+// beside 1 MiB with one, diff, scan and capacity check: 64 KiB pages 103 us without
+// a limit and 68 with it, 4 KiB pages 318 and 249; half of 2 GiB shadowed: the same).
+inline int ctx_diff_blocks(const crum_ctx* c, bool sparse)
 {
-    return c->shape.diff_blocks == (int)kDiffBlocksMax && cand ? c->cus * 8
-                                                               : c->shape.diff_blocks;
+    return c->shape.diff_blocks == (int)kDiffBlocksMax && sparse ? c->cus * 8
+                                                                 : c->shape.diff_blocks;
+}
+// Whether most bytes of a region table have no shadow.
+inline bool mostly_new(const crum_region* regs, uint32_t n)
+{
+    uint64_t read = 0, all = 0;
+    for (uint32_t i = 0; i < n; ++i) {
+        all += regs[i].len;
+        read += regs[i].shadow ? regs[i].len : 0;
+    }
+    return 2 * read < all;
 }
 // Whether a region table needs the diff: units of regions without a shadow
 // are dirty unread, and their flags are not looked at.

@@ -189,6 +189,7 @@ int crum_snapshot_noalloc(crum_ctx* c, const crum_region* regions, uint32_t n_re
     CRUM_TRY_C(c->partial_call ? hipDeviceSynchronize() : hipEventSynchronize(c->ev_upload));
     uint8_t* P = c->na_pin;
     const bool need_diff = any_shadow(regions, n_regions);
+    const int diff_blocks = ctx_diff_blocks(c, mostly_new(regions, n_regions));
     // few regions: the tables go to the device as arguments of the diff
     const bool by_args = need_diff && n_regions <= kArgRegions;
     CallTables t{};
@@ -246,14 +247,14 @@ int crum_snapshot_noalloc(crum_ctx* c, const crum_region* regions, uint32_t n_re
         t.req = rq;
         t.glob = gl;
         CRUM_TRY_C(launch_diff_first(t, reinterpret_cast<CallTables*>(S + L.reqs), n_regions,
-                                     n_units, d_flags, ctx_diff_blocks(c, false), c->diff_nt,
-                                     c->diff_prio, stream, ctx_diff_group(c, us)));
+                                     n_units, d_flags, diff_blocks, c->diff_nt, c->diff_prio,
+                                     stream, ctx_diff_group(c, us)));
     } else {
         CRUM_TRY_C(launch_begin(CopyList{}.add(0, P, S, L.upload_end), nullptr, stream));
         if (need_diff)
-            CRUM_TRY_C(launch_diff(d_regs, n_regions, 0, n_units, d_flags,
-                                   ctx_diff_blocks(c, false), c->diff_nt, c->diff_prio, stream,
-                                   nullptr, nullptr, ctx_diff_group(c, us)));
+            CRUM_TRY_C(launch_diff(d_regs, n_regions, 0, n_units, d_flags, diff_blocks,
+                                   c->diff_nt, c->diff_prio, stream, nullptr, nullptr,
+                                   ctx_diff_group(c, us)));
     }
     CRUM_TRY_C(launch_scan(d_bitmap, 0, W, d_prefix, d_bounds, 1, d_reqs, 0, 1, d_out, d_glob,
                            capacity, 0, d_list, stream, flag_src, note));

@@ -303,7 +303,12 @@ int crum_plan_create(crum_ctx* c, const crum_request* reqs, uint32_t n_reqs, voi
         const uint64_t u0 = req_unit0[q0], u1 = req_unit0[q1];
         uint32_t hdr_blocks = 1, min_us = 64;
         bool shadowed = p->diff_timed;  // a timed plan counts a diff for every group
+        uint64_t read = 0;  // units of regions with a shadow
         for (uint32_t q = q0; q < q1; ++q) {
+            for (uint32_t i = 0; i < dreq[q].n_regions; ++i) {
+                const DevRegion& d = dregs[dreq[q].first_region + i];
+                read += d.shadow ? d.len >> d.unit_shift : 0;
+            }
             shadowed |= (dreq[q].flags & kReqShadow) != 0;
             hdr_blocks = std::max(hdr_blocks, header_blocks(dreq[q].n_regions, dreq[q].n_words,
                                                             dreq[q].n_pages));
@@ -318,8 +323,10 @@ int crum_plan_create(crum_ctx* c, const crum_request* reqs, uint32_t n_reqs, voi
         if (gi == 0)
             e = launch_plan_init(d_glob, s);
         if (e == hipSuccess && shadowed)
-            e = launch_diff(d_regs, p->n_regs, u0, u1, d_flags, ctx_diff_blocks(c, false), ctx_diff_nt(c), ctx_diff_prio(c), s,
-                            nullptr, p->d_stamp ? p->d_stamp + 2 * gi : nullptr,
+            e = launch_diff(d_regs, p->n_regs, u0, u1, d_flags,
+                            ctx_diff_blocks(c, 2 * read < u1 - u0), ctx_diff_nt(c),
+                            ctx_diff_prio(c), s, nullptr,
+                            p->d_stamp ? p->d_stamp + 2 * gi : nullptr,
                             ctx_diff_group(c, min_us));
         const FlagSource flag_src{d_regs, p->n_regs, d_flags};
         HostNote note;

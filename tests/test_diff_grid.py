@@ -47,3 +47,51 @@ def test_the_default_and_what_was_the_default_are_two_values():
             crum.crum_ctx_set_param(ctx, crum.CRUM_PARAM_DIFF_BLOCKS, (1 << 20) + 1)
     finally:
         crum.crum_ctx_destroy(ctx)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,n_new", [(4096, 8300), (4096, 20001), (16384, 8300)])
+def test_tables_that_are_mostly_new(P, n_new):
+    """Most pages without a shadow, more units than the limited grid of 8 workgroups per
+    compute unit takes in one stride, and shadowed regions before, between and behind
+    them: a snapshot, the allocation-free one and a plan give the oracle's image."""
+    import numpy as np
+    import torch
+    import oracle
+    import paper_1808_00117_amd as crum
+    from paper_1808_00117_amd.api import regions_of
+    from tests.gpu_util import image_capacity, log, upload
+    log(f"[new] P={P} {n_new} pages")
+    rng = np.random.default_rng(n_new)
+    regs = []
+    for i, n in enumerate((130, n_new, 77, n_new // 2, 300)):
+        cur = rng.integers(0, 256, n * P, dtype=np.uint8)
+        sh = cur.copy()
+        sh[rng.choice(n, n // 5, replace=False) * P + 9] ^= 3
+        regs.append((cur, None if i % 2 else sh, i))
+    _, img, _ = oracle.snapshot(regs, P, seq=6)
+    dev = upload(regs)
+    cap = image_capacity(dev, P)
+    ctx = crum.crum_ctx_create(0)
+    try:
+        status = torch.zeros(64, dtype=torch.uint8, pin_memory=True)
+        stream = torch.cuda.current_stream().cuda_stream
+        table = regions_of(dev)
+
+        def launch(name, staging):
+            if name == "plan":
+                plan = crum.Plan(ctx, [(table, P, 0, 6)], staging.data_ptr(), cap, 0, 0)
+                rc = plan.launch(stream, status.data_ptr())
+                torch.cuda.synchronize()
+                plan.destroy()
+                return rc
+            rc = getattr(crum, name)(ctx, table, P, 0, 6, staging.data_ptr(), cap, 0, 0, stream,
+                                     status.data_ptr())
+            torch.cuda.synchronize()
+            return rc
+        for name in ("crum_snapshot", "crum_snapshot_noalloc", "plan"):
+            staging = torch.zeros(cap, dtype=torch.uint8, device="cuda")
+            assert launch(name, staging) == crum.CRUM_OK
+            assert np.array_equal(staging[:img.size].cpu().numpy(), img), name
+    finally:
+        crum.crum_ctx_destroy(ctx)
