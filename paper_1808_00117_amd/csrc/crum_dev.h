@@ -115,10 +115,15 @@ struct CrcTables {
     uint32_t pad;
 };
 
+// Clock words of a timed diff launch (see launch_diff).
+constexpr uint32_t kStampSlots = 64;
+constexpr uint32_t kStampLine = 16;  // 128 bytes
+constexpr uint32_t kStampWords = kStampLine * (1 + kStampSlots);
+
 enum PackMode { kModePack = 0, kModeVerify = 1, kModeScatter = 2, kModePull = 3 };
 
 struct LaunchShape {
-    int diff_blocks;   // largest grid of a limited diff (256-thread blocks)
+    int diff_blocks;   // largest grid of the diff kernel (256-thread blocks)
     int pack_blocks;   // persistent grid of the pack/verify/scatter kernels
 };
 
@@ -182,10 +187,10 @@ hipError_t launch_begin(const CopyList& list, uint64_t* done, hipStream_t s);
 const CrcTables& crc_tables();  // the constants, in host memory
 // cand (may be null): bitmap over global pages; pages whose bit is clear are
 // flagged clean without being read (they are known to equal their shadow).
-// stamp (may be null): two words, the wall clock at the launch's start and
-// the latest end of its workgroups (stamp[1] must start below any clock
-// value, e.g. zeroed once).
-// blocks: largest grid, 0 for as many as the units need.
+// stamp (may be null): kStampWords words, below any clock value at first (zeroed
+// once): the wall clock at the launch's start in word 0, and the latest end of its
+// workgroups as the largest of words kStampLine, 2 * kStampLine, ...
+// blocks: largest grid.
 // group 2 or 4: each wave takes that many consecutive units (as many 4 KiB
 // units of a region read as one span); other values: one unit per wave.
 hipError_t launch_diff(const DevRegion* regs, uint32_t n_regs, uint64_t u0, uint64_t u1,

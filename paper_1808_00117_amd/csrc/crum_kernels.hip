@@ -418,15 +418,12 @@ __device__ __forceinline__ void diff_unit(const DevRegion* __restrict__ regs, ui
 // a page whose bit is clear is known to equal its shadow, so its units are
 // flagged clean without reading either copy.
 // stamp (may be null): stamp[0] gets the constant-rate wall clock when
-// workgroup 0 starts (the first one dispatched), stamp[1] the largest clock
-// at which one of the last kStampGroups workgroups ends.  Workgroups are
-// dispatched in order and take the same time, so the last to end is one of those
-// (two for every place on the device); with an atomic from each of the 13 000 to 50 000
-// workgroups of a plan's group the stamps made the launch they time 20 % longer (0.31
-// ms against 0.26).  stamp[1] needs no reset between launches: a later launch's
-// clocks exceed every earlier one's.
-constexpr uint32_t kStampGroups = 4096;
-
+// workgroup 0 starts (the first one dispatched), and every workgroup leaves the clock
+// of its end as a maximum in one of kStampSlots words, a cache line apart.  They
+// need no reset between launches: a later launch's clocks exceed every earlier one's.
+// One word for all would serialize the launch it times: 256 MiB of 4 KiB pages took 77 us
+// untimed, 98 with one word for the last 4096 workgroups, 82 this way, 1 GiB 326, 333 and
+// 332.
 template <bool NT, int G>
 __device__ __forceinline__ void diff_units(const DevRegion* __restrict__ regs, uint32_t n_regs,
                                            uint64_t u0, uint64_t u1,
@@ -486,10 +483,11 @@ __device__ __forceinline__ void diff_units(const DevRegion* __restrict__ regs, u
             }
         }
     }
-    if (stamp && blockIdx.x + kStampGroups >= gridDim.x) {
+    if (stamp) {
         __syncthreads();
         if (threadIdx.x == 0)
-            atomicMax(reinterpret_cast<unsigned long long*>(stamp + 1),
+            atomicMax(reinterpret_cast<unsigned long long*>(
+                          stamp + kStampLine * (1 + blockIdx.x % kStampSlots)),
                       (unsigned long long)wall_clock64());
     }
 }

@@ -41,7 +41,7 @@ struct crum_plan {
     std::vector<hipEvent_t> t_group;
     bool timed = false;
     // with the context timing its diff class at plan creation: each group's
-    // diff launch writes its start and end wall clock to d_stamp (2 words per
+    // diff launch writes its start and end wall clocks to d_stamp (kStampWords per
     // group); a launch copies them after h_rb and adds the durations to the
     // context's diff timing
     uint64_t* d_stamp = nullptr;
@@ -246,8 +246,10 @@ int crum_plan_create(crum_ctx* c, const crum_request* reqs, uint32_t n_reqs, voi
     const size_t o_bounds = take(8 * std::max<size_t>(n_groups, 1));
     const size_t o_status = take(40ull * std::max<uint32_t>(n_reqs, 1));
     const size_t o_order = take(4ull * std::max<uint32_t>(n_reqs, 1));
-    const size_t o_stamp = take(16 * std::max<size_t>(n_groups, 1));
-    const size_t rb_bytes = 24 * std::max<size_t>(n_groups, 1);  // ends, then stamps
+    p->diff_timed = ctx_times(c, kTDiff);
+    const size_t stamp_bytes = p->diff_timed ? 8 * kStampWords * n_groups : 0;
+    const size_t o_stamp = take(stamp_bytes);
+    const size_t rb_bytes = 8 * std::max<size_t>(n_groups, 1) + stamp_bytes;  // ends, stamps
     DeviceGuardC g(ctx_device(c));
     auto fail = [&](int code) {
         plan_free(p);
@@ -284,12 +286,11 @@ int crum_plan_create(crum_ctx* c, const crum_request* reqs, uint32_t n_reqs, voi
     p->d_status = M + o_status;
     const LaunchShape shape = ctx_shape(c);
     const CrcTables* tabs = ctx_tables(c);
-    p->diff_timed = ctx_times(c, kTDiff);
     if (p->diff_timed) {
         int khz = 0;
         if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, ctx_device(c)) !=
                 hipSuccess ||
-            khz <= 0 || hipMemset(M + o_stamp, 0, 16 * std::max<size_t>(n_groups, 1)) != hipSuccess)
+            khz <= 0 || (stamp_bytes && hipMemset(M + o_stamp, 0, stamp_bytes) != hipSuccess))
             return fail(CRUM_EHIP);
         p->clock_khz = khz;
         p->d_stamp = reinterpret_cast<uint64_t*>(M + o_stamp);
@@ -326,7 +327,7 @@ int crum_plan_create(crum_ctx* c, const crum_request* reqs, uint32_t n_reqs, voi
             e = launch_diff(d_regs, p->n_regs, u0, u1, d_flags,
                             ctx_diff_blocks(c, 2 * read < u1 - u0), ctx_diff_nt(c),
                             ctx_diff_prio(c), s, nullptr,
-                            p->d_stamp ? p->d_stamp + 2 * gi : nullptr,
+                            p->d_stamp ? p->d_stamp + kStampWords * gi : nullptr,
                             ctx_diff_group(c, min_us));
         const FlagSource flag_src{d_regs, p->n_regs, d_flags};
         HostNote note;
@@ -411,18 +412,22 @@ int crum_plan_launch(crum_plan* p, void* stream_, crum_request_status* h_status)
                                   hipMemcpyDeviceToHost, side));
     uint64_t* h_stamp = reinterpret_cast<uint64_t*>(p->h_rb + 8 * n_groups);
     if (p->diff_timed)
-        CRUM_TRY_C(hipMemcpyAsync(h_stamp, p->d_stamp, 16 * n_groups, hipMemcpyDeviceToHost,
-                                  side));
+        CRUM_TRY_C(hipMemcpyAsync(h_stamp, p->d_stamp, 8 * kStampWords * n_groups,
+                                  hipMemcpyDeviceToHost, side));
     CRUM_TRY_C(hipEventRecord(p->ev_done, side));
     CRUM_TRY_C(hipStreamWaitEvent(stream, p->ev_done, 0));
     p->timed = true;
     if (p->diff_timed) {
         // a plan that times its diff launches returns after its drains end
         CRUM_TRY_C(hipEventSynchronize(p->ev_done));
-        for (size_t gi = 0; gi < n_groups; ++gi)
-            if (p->diff_units[gi] && h_stamp[2 * gi + 1] > h_stamp[2 * gi])
-                ctx_add_timing(c, kTDiff,
-                               (double)(h_stamp[2 * gi + 1] - h_stamp[2 * gi]) / p->clock_khz);
+        for (size_t gi = 0; gi < n_groups; ++gi) {
+            const uint64_t* st = h_stamp + kStampWords * gi;
+            uint64_t end = 0;
+            for (uint32_t i = 1; i <= kStampSlots; ++i)
+                end = std::max(end, st[kStampLine * i]);
+            if (p->diff_units[gi] && end > st[0])
+                ctx_add_timing(c, kTDiff, (double)(end - st[0]) / p->clock_khz);
+        }
     }
     return CRUM_OK;
 }
