@@ -47,6 +47,10 @@ PARAMS = {
     "eager": C.CRUM_PARAM_EAGER,
 }
 
+# Shapes of an earlier CRC step: the library checks and keeps them, and no kernel
+# looks at them any more.  They are named here for the caches that hold them.
+NO_EFFECT = frozenset(("pack_depth", "crc_variant", "pack_prefetch"))
+
 
 def class_key(kind: str, nbytes: int, page_size: int = 0) -> str:
     """Cache key of a workload class: kind "snapshot" (one page size) or
@@ -127,7 +131,9 @@ def search(ctx: int, run: Callable[[], float], space: Dict[str, Iterable[int]],
     `run()` (which returns seconds and must rebuild any state that depends on
     the parameters).  The default shapes are measured first; the spread of
     their runs (slowest minus fastest) is the noise margin, and a candidate
-    replaces the best so far only when it is faster by more than that margin.
+    replaces the best so far only when it is faster by more than that margin,
+    and never for a parameter without effect (NO_EFFECT): a faster run of
+    that is noise.
     Returns (best params, trials, stats) with stats = {default_s, best_s,
     spread_s, gain}."""
     best = current(ctx)
@@ -151,7 +157,7 @@ def search(ctx: int, run: Callable[[], float], space: Dict[str, Iterable[int]],
             cand = dict(best)
             cand[name] = v
             t, _ = measure(cand)
-            if t < best_t - spread:
+            if t < best_t - spread and name not in NO_EFFECT:
                 best, best_t = cand, t
     apply(ctx, best)
     stats = {"default_s": default_t, "best_s": best_t, "spread_s": spread,
