@@ -262,7 +262,10 @@ int crum_snapshot_tracked(crum_ctx* ctx, const crum_region* regions, uint32_t n_
  * CRUM_ELIMIT with nothing enqueued.  Every call on one device shares that
  * device's array: calls that overlap on one device (different contexts, or
  * different threads) race; consecutive calls through one context are
- * ordered.  Timing classes are not recorded by this call. */
+ * ordered.  Timing classes are not recorded by this call.  A call is made
+ * beside a capture, not inside it: on a stream that is itself being captured
+ * it returns CRUM_EHIP, as crum_snapshot does in its chunked and diff-first
+ * orders. */
 #define CRUM_NOALLOC_SCRATCH_BYTES (64ull << 20)
 #define CRUM_NOALLOC_MAX_REGIONS 2048u
 enum { CRUM_ELIMIT = -9 /* input larger than the fixed scratch of crum_snapshot_noalloc */ };
@@ -456,7 +459,8 @@ void crum_server_destroy(crum_server* server);
  *   that stay on the device and restores that write as much (0).
  * CRUM_PARAM_PACK_NT_LOAD: 1 reads the pages in the pack and verify kernels
  *   with non-temporal loads, which are not kept in the caches, except for the
- *   last 256 to 512 MiB verified of an image of more than 256 MiB (1).
+ *   last 256 to 512 MiB verified of an image of more than 256 MiB, and in
+ *   on-demand restores, whose scatter reads the same bytes next (1).
  * CRUM_PARAM_DIFF_GROUP: 4 KiB diff units per wave of the diff kernel, 1, 2
  *   or 4, for launches whose smallest unit is 4 KiB: 2 or 4 units of one
  *   region are read as one span with 8 or 16 loads per array in flight per

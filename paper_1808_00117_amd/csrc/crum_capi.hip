@@ -197,6 +197,18 @@ int wait_count(const uint64_t* count, hipEvent_t ev, hipStream_t s)
     return CRUM_OK;
 }
 
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (!s)
+        return false;  // the null stream cannot be captured
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
 void* mapped_status(crum_status* h_status)
 {
     hipPointerAttribute_t a{};
@@ -681,6 +693,8 @@ static int snapshot_impl(crum_ctx* c, const crum_region* regions, uint32_t n_reg
         (void)hipGetLastError();
     }
     bool eager = !direct && c->eager && capacity >= worst && G > 0;
+    if (!direct && capturing(stream))
+        return CRUM_EHIP;
 
     // ---- chunk plan (page ranges aligned to bitmap words)
     std::vector<uint64_t> cuts{0};

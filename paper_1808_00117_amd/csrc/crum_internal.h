@@ -228,6 +228,12 @@ constexpr uint64_t kNoCount = ~0ull;
 // total: a short spin (the host reads the word as soon as the scan has stored it),
 // then a wait for `ev`, recorded behind the scan, or for `s` when ev is null.
 int wait_count(const uint64_t* count, hipEvent_t ev, hipStream_t s);
+// Whether `s` is being captured into a graph.  A snapshot without a host image, which
+// does not wait for the device, would be captured whole: a replay would read the
+// pinned tables of a later call and use scratch that nothing holds for it, and the
+// events that order the context's calls would no longer be recorded.  One with a
+// host image cannot get its dirty count there.
+bool capturing(hipStream_t s);
 // The address at which kernels may write 32 bytes at h_status, or null when it
 // is not pinned memory that the device maps at the same address.
 void* mapped_status(crum_status* h_status);

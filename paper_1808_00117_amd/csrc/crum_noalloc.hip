@@ -185,6 +185,8 @@ int crum_snapshot_noalloc(crum_ctx* c, const crum_region* regions, uint32_t n_re
 
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     DeviceGuard g(c->device);
+    if (capturing(stream))
+        return CRUM_EHIP;
     // the previous upload from the pinned buffer must have left it
     CRUM_TRY_C(c->partial_call ? hipDeviceSynchronize() : hipEventSynchronize(c->ev_upload));
     uint8_t* P = c->na_pin;
