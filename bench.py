@@ -560,7 +560,7 @@ def bench_batched(args) -> dict:
     same requests into the same host offsets; images compared byte for byte.
     Three plans are timed: the grouped plan (tuned shapes, caller's order),
     the same plan smallest request first, and a one-graph plan (a single group
-    holding all 256 requests: one persistent diff, one drain).  Returns the
+    holding all 256 requests: one diff, one drain).  Returns the
     result dict."""
     import numpy as np
 
@@ -689,7 +689,7 @@ def bench_batched(args) -> dict:
     batched_image = h_images.numpy(cap)[: max(o + b for o, b in zip(offsets, sizes))].copy()
     plan.destroy()
 
-    # one graph for the whole batch: a single group (one persistent diff
+    # one graph for the whole batch: a single group (one diff
     # over every unit of the 256 requests, one scan, one pack, one drain)
     crum.crum_ctx_set_param(ctx, crum.CRUM_PARAM_CHUNK_BYTES, N)
     crum.crum_ctx_set_param(ctx, crum.CRUM_PARAM_CHUNK_MAX_BYTES, N)
@@ -808,7 +808,7 @@ def bench_batched(args) -> dict:
                            "p90": round(percentile(lat_1, 0.9), 2),
                            "p99": round(percentile(lat_1, 0.99), 2)},
             "groups": n_groups_1, "same_images": same_1,
-            "what": "all 256 requests in one captured graph (one persistent diff, one "
+            "what": "all 256 requests in one captured graph (one diff, one "
                     "scan, one pack), drained by one copy when the graph ends"},
         "plain": {"makespan_ms": round(1e3 * t_plain, 2),
                   "gbs": round(N / t_plain / 1e9, 2),

@@ -276,18 +276,21 @@ inline int ctx_diff_group(const crum_ctx* c, uint32_t min_us)
 {
     return min_us == 12 ? c->diff_group : 1;
 }
-// Bytes that the last-level cache holds.  Launches that write more than this
+// Bytes that the last-level cache holds.  Launches that may write more than this
 // and leave it on the device use non-temporal stores: what they would leave
 // behind in the cache is written back while the next kernels read (1.5 GiB of
 // 4 KiB pages with 570 MB packed and as much shadow updated: 994 us with plain
 // stores, 886 with these; a 1 GiB first snapshot: 479 and 448; a rollback that
 // writes 1.6 GB: 699 and 678).  Less than that stays cached and is faster with
 // plain stores (scatter of 189 MB: 70 us, 82 non-temporal); an image that is
-// drained measures the same with both.
+// drained measures the same with both.  A snapshot's bound is the bytes scanned, as
+// its dirty count is not known to the host when the pack is launched; with few pages
+// dirty both kinds of store measure the same (300 MiB to 4 GiB with 1 to 10 % dirty,
+// alone and with a verified rollback from the image behind: within 1 %).
 constexpr uint64_t kCachedBytes = 256ull << 20;
 
-// launch_pack's flags for a launch that may write `device_bytes` and leaves
-// them on the device.
+// launch_pack's flags for a launch that writes at most `device_bytes` that stay on
+// the device.
 inline int ctx_pack_flags(const crum_ctx* c, uint64_t device_bytes)
 {
     return (c->pack_nt || device_bytes > kCachedBytes ? kPackNtStore : 0) |

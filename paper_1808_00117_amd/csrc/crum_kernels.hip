@@ -422,8 +422,8 @@ __device__ __forceinline__ void diff_unit(const DevRegion* __restrict__ regs, ui
 // of its end as a maximum in one of kStampSlots words, a cache line apart.  They
 // need no reset between launches: a later launch's clocks exceed every earlier one's.
 // One word for all would serialize the launch it times: 256 MiB of 4 KiB pages took 77 us
-// untimed, 98 with one word for the last 4096 workgroups, 82 this way, 1 GiB 326, 333 and
-// 332.
+// untimed, 98 with one word for the last 4096 workgroups alone, 82 this way, 1 GiB 326,
+// 333 and 339 (of 64 KiB pages 325, 330 and 326).
 template <bool NT, int G>
 __device__ __forceinline__ void diff_units(const DevRegion* __restrict__ regs, uint32_t n_regs,
                                            uint64_t u0, uint64_t u1,
@@ -615,7 +615,8 @@ __device__ __forceinline__ bool page_dirty(const DevRegion& R, uint64_t g,
 // One wave per bitmap word in [w0, w1): lane l owns global page 64w + l, and a
 // ballot forms the word.  Bound by latency; 2 MiB pages (128 flags each) took
 // 14-18 us a byte at a time and take 5.  (Bits set by the diff itself with atomics
-// cost about 3 ns each: 75 us on 2.4 ms for 8 GiB with 5 % of the units dirty.)
+// cost about 3 ns for each dirty unit: 58 us more for 8 GiB of 64 KiB pages, 9 % of them
+// dirty.)
 __global__ __launch_bounds__(256) void k_bitmap(const DevRegion* __restrict__ regs,
                                                 uint32_t n_regs, uint64_t w0, uint64_t w1,
                                                 const uint8_t* __restrict__ unit_flags,
@@ -1489,8 +1490,9 @@ __device__ __forceinline__ uint32_t message_share(const MessageShare& sp, Load l
 }
 
 // Workgroups for two messages: about two 4 KiB batches for each of their
-// waves, at most max.  The meeting of several workgroups costs 6 us or more
-// (atomics, fences): 154 batches took no longer with two a wave than with one.
+// waves, at most max.  A header of one workgroup takes 6.0 to 6.6 us, of three (64
+// MiB of 4 KiB pages), which meet in atomics, 8.0, of 50 15.4: 154 batches took no
+// longer with two a wave than with one.
 __host__ __device__ __forceinline__ uint32_t message_blocks(uint64_t bytes_a, uint64_t bytes_b,
                                                             uint32_t max)
 {
